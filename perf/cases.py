@@ -82,8 +82,9 @@ def _shape(rng, dim, n_lo, n_hi):
 def draw(rng):
     op = rng.choice(["solve"] * 7 + ["batch", "backbone", "generate"])
     if op == "batch":
-        return dict(op="batch", count=rng.randint(2, 48), pick=rng.randint(1, 10000),
-                    precision=rng.choice(["mixed", "mixed", "fp64"]))
+        precision = rng.choice(["mixed", "mixed", "fp64"])
+        return dict(op="batch", count=rng.randint(2, 36 if precision == "mixed" else 18), pick=rng.randint(1, 10000),
+                    precision=precision)
     dim = rng.choice([2, 3])
     if op == "generate":
         nx, ny, nz = _shape(rng, dim, 1e4, 2048 ** 2 if dim == 2 else 256 ** 3)
@@ -124,6 +125,13 @@ def _field(shape, H, ratio, noise):
     return (phi - phi.mean()) / sd if float(sd) > 0.0 else torch.zeros_like(phi)
 
 
+def _correlated(shape, H, ratio, gen):
+    """FBM node field of a network: the corner of a field on a grid of power-of-two sides, whose transforms are ready."""
+    grid = [1 << (n - 1).bit_length() for n in shape]
+    noise = torch.randn(grid, generator=gen, dtype=torch.float64, device="cuda")
+    return _field(grid, H, ratio, noise)[tuple(slice(0, n) for n in shape)].contiguous()
+
+
 def _edge(a, k, dim):
     """A view of the last plane along lattice direction k (x is the last tensor axis)."""
     return a.select(dim - 1 - k, a.shape[dim - 1 - k] - 1)
@@ -150,11 +158,11 @@ def _bonds(c, gen, shape):
     elif kind == "unit":
         g = [torch.ones(shape, dtype=torch.float64, device="cuda") for _ in range(dim)]
     elif kind == "strat":
-        phi = _field(shape[:1], c["H"], 1.0, torch.randn(shape[:1], **rnd))
+        phi = _correlated(shape[:1], c["H"], 1.0, gen)
         layer, up = c["sigma"] * phi, c["sigma"] * 0.5 * (phi + torch.roll(phi, -1))
         g = [torch.exp(v)[:, None, None].expand(shape).contiguous() for v in (layer, layer, up)]
     else:
-        g = _bonds_of(_field(shape, c["H"], c.get("ratio", 1.0), torch.randn(shape, **rnd)), c["sigma"], True)
+        g = _bonds_of(_correlated(shape, c["H"], c.get("ratio", 1.0), gen), c["sigma"], True)
     for k in range(dim):
         if not periodic:
             _edge(g[k], k, dim).zero_()
