@@ -153,7 +153,8 @@ typedef struct {
     int64_t n_live;     /* interior nodes connected to both faces */
     int64_t passes;     /* pass rounds launched while this network iterated (a round launches
                            one pass kernel per kind of network present; idle rounds after
-                           convergence, until the host notices, are included) */
+                           convergence, until the host notices, are included; of a network
+                           whose passes ran in resident loops, many to a launch, the passes) */
     double t_mask_s;    /* device time: upload, validation and connectivity */
     double t_loop_s;    /* device time from the start of this network's iterations to the
                            end of its last round */

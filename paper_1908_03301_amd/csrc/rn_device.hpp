@@ -50,7 +50,9 @@ struct Scalars {
     double Q_in, Q_out, xr;  // fluxes and x.(b - A x) from the last refresh
     // to 256 bytes: control blocks of different networks share no 128-byte
     // line, so networks placed on different XCDs never write one line
-    uint32_t pad_[4];
+    uint32_t loop_aborts;      // resident loops that did not get all their workgroups started
+    uint32_t loop_failed;      // a wait inside a resident loop gave up
+    uint32_t pad_[2];
 };
 
 constexpr int kRed = 5;          // partial sums per workgroup
@@ -222,6 +224,37 @@ template <typename T>
 hipError_t launch_pass_persist(int dim, int coh, const PassArgs<T> *tab, const uint2 *blk, const int *xoff,
                                Scalars *scal, int nblocks, int64_t round_base, int rounds, int slot, unsigned *err,
                                unsigned long long *queues, hipStream_t st);
+
+// Resident CG loop (rn_loop.hpp): one launch runs up to `limit` CG passes of
+// the one network in `slot`, with its state in registers. `dim` as for
+// launch_pass; tpw and tile_z are the network's. *gate (two words, zero before
+// the launch) admits the workgroups; gate_clear is another launch's gate, to be
+// cleared; part holds loop_part_bytes(); xch two slots of xch_slot words and
+// coef kLoopCoefBytes, both only ever written by these loops, with pass numbers
+// that start at 0 here and do not repeat: a launch uses tag0 .. tag0 + limit - 1.
+struct LoopArgs {
+    unsigned *gate;
+    unsigned *gate_clear;
+    double *part;
+    unsigned long long *xch, *coef;
+    size_t xch_slot;
+    unsigned tag0;
+    int limit;
+};
+constexpr size_t kLoopCoefBytes = 2048;
+constexpr int kLoopRed = 4;             // sums that the CG step uses
+constexpr int kLoopSlots = 4;           // slots of the exchange between workgroups
+constexpr int kLoopGridMax = 1024;      // workgroups of a resident loop
+inline size_t loop_part_bytes() { return (size_t)kLoopSlots * kLoopRed * kLoopGridMax * sizeof(double); }
+// workgroups of this shape that the device holds at once (0: no loop kernel for it)
+template <typename T>
+hipError_t loop_capacity(int dim, int tpw, int tile_z, int *cap);
+// words of one exchange slot of a network of `ntiles` tiles
+template <typename T>
+size_t loop_exchange_words(int dim, int tile_z, int ntiles);
+template <typename T>
+hipError_t launch_loop(int dim, int tpw, int tile_z, int grid, const PassArgs<T> *tab, Scalars *scal, int parity,
+                       int slot, const LoopArgs &r, hipStream_t st);
 
 // tile geometry of the pass kernels: a 2D workgroup tile is 64 kSEG2f x
 // 4 kTY2f (FP32) or 64 kSEG2d x 4 kTY2d (FP64): each wave holds kTY2f / kTY2d

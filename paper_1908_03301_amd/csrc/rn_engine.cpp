@@ -417,6 +417,7 @@ void Pool::free(void *ptr)
 int Engine::init(hipStream_t st, std::string *err)
 {
     (void)st;
+    std::fill(&loop_cap_[0][0][0], &loop_cap_[0][0][0] + sizeof(loop_cap_) / sizeof(int), -1);
     // Graph replay of pass rounds is opt-in (RN_GRAPHS=1): on a launch-bound
     // 128^2 solve it measured 5% slower than direct launches, since the time
     // of a small pass is spent on the device, not in the launch call.
@@ -433,6 +434,10 @@ int Engine::init(hipStream_t st, std::string *err)
     ENG_TRY(hipMalloc(&d_queue_, kQueueWords * sizeof(unsigned long long) * kKinds));
     ENG_TRY(hipMalloc(&d_xoff_, sizeof(int) * 16 * kKinds));
     ENG_TRY(hipHostMalloc((void **)&h_xoff_, sizeof(int) * 16 * kKinds * 2, hipHostMallocDefault));
+    ENG_TRY(hipMalloc(&d_gate_, kGates * kGateBytes));
+    ENG_TRY(hipMemset(d_gate_, 0, kGates * kGateBytes));
+    ENG_TRY(hipMalloc(&d_lpart_, loop_part_bytes()));
+    ENG_TRY(hipMalloc(&d_coef_, kLoopCoefBytes));
     ENG_TRY(hipMalloc(&d_err_, 256));
     ENG_TRY(hipMemset(d_err_, 0, 256));
     ENG_TRY(hipHostMalloc((void **)&h_err_, 256, hipHostMallocDefault));
@@ -463,6 +468,14 @@ void Engine::destroy()
     (void)hipHostFree(h_tabf_);
     (void)hipHostFree(h_tabd_);
     (void)hipHostFree(h_cnt_);
+    (void)hipFree(d_gate_);
+    (void)hipFree(d_lpart_);
+    (void)hipFree(d_coef_);
+    (void)hipFree(d_xch_);
+    d_coef_ = d_xch_ = nullptr;
+    xch_cap_ = 0;
+    d_gate_ = nullptr;
+    d_lpart_ = nullptr;
     (void)hipFree(d_err_);
     (void)hipFree(d_queue_);
     d_queue_ = nullptr;
@@ -661,6 +674,8 @@ int Engine::after_prepare(Net *net, hipStream_t st, std::string *err)
     net->first_chunk = chunk_seq_ + 1;
     net->prev_est = -1.0;
     net->prev_iters = 0;
+    net->loop_ok = true;
+    net->loop_used = false;
     net->phase = NET_ACTIVE;
     active_.push_back(net);
     dirty_ = true;
@@ -825,6 +840,105 @@ int Engine::launch_persistent(int rounds, hipStream_t st, std::string *err)
     return launch_rounds(rounds, st, err);
 }
 
+// Whether a network that iterates alone runs in a resident loop: its
+// workgroups all have to fit the chip at once. Below that size a pass is bound
+// by its chain of round trips, and every shape that fits is faster there. Whole
+// solves over their iterations, one launch per pass against the loop: 128^2
+// mixed 9.0 -> 3.6 us, 201 x 150 FP64 9.1 -> 3.9, 512^2 FP64 11.3 -> 7.1,
+// 1024^2 mixed 16.0 -> 10.4, 1024^2 FP64 21.4 -> 14.6. Several networks share
+// launches instead.
+int Engine::loop_fits(const Net *net, bool *fits, std::string *err)
+{
+    *fits = false;
+    if (persist_ || use_graph_ || !net->loop_ok) return RN_OK;
+    const int k = net->kind, tpw = net->L.tpw;
+    if (tpw < 1 || tpw > kLoopTpw) return RN_OK;
+    const int tz = net->L.dim == 3 ? net->L.tile_z : 0;
+    if (tz >= kLoopTz) return RN_OK;
+    int &cap = loop_cap_[k][tpw - 1][tz];
+    if (cap < 0) {
+        if (kind_fp64(k)) ENG_TRY(loop_capacity<double>(kind_dim(k), tpw, tz, &cap));
+        else ENG_TRY(loop_capacity<float>(kind_dim(k), tpw, tz, &cap));
+    }
+    *fits = net->L.grid <= cap;
+    return RN_OK;
+}
+
+// A chunk of a network in resident loops: each loop runs CG passes until the
+// next refresh (or kLoopLimit of them), which the pass kernel behind it runs.
+// The first two passes of a solve are refreshes. Every launch is a round of
+// its own (parity), whatever number of passes it runs.
+int Engine::launch_loops(Net *net, int *launched, hipStream_t st, std::string *err)
+{
+    const int k = net->kind, dim = kind_dim(k), slot = net->slot;
+    recording_ = timing_;
+    tmirror_ = next_mirror_;
+    if (recording_) {
+        int r = record_timing(-1, st, err);
+        if (r) {
+            recording_ = false;
+            return r;
+        }
+    }
+    // the exchange memory holds nothing but tagged words: zero (no tag) when it
+    // is new and before the tags would start over
+    const int tz = net->L.dim == 3 ? net->L.tile_z : 0;
+    const size_t xch_words = kind_fp64(k) ? loop_exchange_words<double>(dim, tz, net->L.ntiles)
+                                          : loop_exchange_words<float>(dim, tz, net->L.ntiles);
+    const bool grow = 2 * xch_words > xch_cap_, over = loop_tag_ > 0xf0000000u;
+    if (grow) {
+        if (d_xch_) ENG_TRY(hipStreamSynchronize(st));
+        (void)hipFree(d_xch_);
+        d_xch_ = nullptr;
+        xch_cap_ = 0;
+        const size_t cap = std::max<size_t>(2 * xch_words, (size_t)1 << 18);
+        ENG_TRY(hipMalloc(&d_xch_, cap * sizeof(unsigned long long)));
+        xch_cap_ = cap;
+    }
+    if (grow || over) {
+        ENG_TRY(launch_clear_u64(d_xch_, (int)xch_cap_, st));
+        ENG_TRY(launch_clear_u64(d_coef_, (int)(kLoopCoefBytes / sizeof(unsigned long long)), st));
+        if (over) loop_tag_ = 1;
+    }
+    int n = 0;
+    auto one = [&](bool loop) -> int {
+        const int par = (int)(rounds_ & 1);
+        if (loop) {
+            LoopArgs a;
+            a.gate = (unsigned *)(d_gate_ + kGateBytes * gate_);
+            a.gate_clear = (unsigned *)(d_gate_ + kGateBytes * ((gate_ + kGates / 2) % kGates));
+            a.part = d_lpart_;
+            a.xch = d_xch_;
+            a.coef = d_coef_;
+            a.xch_slot = xch_words;
+            a.tag0 = loop_tag_;
+            loop_tag_ += kLoopLimit;
+            a.limit = kLoopLimit;
+            gate_ = (gate_ + 1) % kGates;
+            if (!kind_fp64(k)) ENG_TRY(launch_loop<float>(dim, net->L.tpw, tz, net->L.grid, d_tabf_, d_scal_, par, slot, a, st));
+            else ENG_TRY(launch_loop<double>(dim, net->L.tpw, tz, net->L.grid, d_tabd_, d_scal_, par, slot, a, st));
+        } else if (!kind_fp64(k)) {
+            ENG_TRY(launch_pass<float>(dim, d_tabf_, nullptr, d_scal_, net->L.grid, par, slot, st));
+        } else {
+            ENG_TRY(launch_pass<double>(dim, d_tabd_, nullptr, d_scal_, net->L.grid, par, slot, st));
+        }
+        ++rounds_;
+        ++launches_;
+        ++n;
+        return recording_ ? record_timing(k, st, err) : RN_OK;
+    };
+    int r = RN_OK;
+    if (!net->loop_used) r = one(false);
+    for (int i = 0; i < kLoopsPerChunk && !r; ++i) {
+        r = one(false);
+        if (!r) r = one(true);
+    }
+    recording_ = false;
+    net->loop_used = true;
+    *launched = n;
+    return r;
+}
+
 int Engine::capture(hipStream_t st, std::string *err)
 {
     if (gexec_) {
@@ -859,9 +973,18 @@ int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
         }
     }
     peak_active_ = std::max(peak_active_, (int)active_.size());
-    int kinds = 0;
-    for (int k = 0; k < kKinds; ++k) kinds += nblk_[k] ? 1 : 0;
     tkind_[next_mirror_].clear();
+    if (active_.size() == 1) {
+        bool fits = false;
+        int r = loop_fits(active_[0], &fits, err);
+        if (r) return r;
+        if (fits) {
+            int launched = 0;
+            r = launch_loops(active_[0], &launched, st, err);
+            if (r) return r;
+            return queue_status(launched, st, err);
+        }
+    }
     if (use_graph_ && rounds >= kGraphRounds) {
         // whole graphs only: the chunk is rounded up to a multiple of the
         // graph's (even) round count, so every replay starts on its parity
@@ -891,6 +1014,12 @@ int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
     rounds_ += rounds;
     for (int k = 0; k < kKinds; ++k)
         if (nblk_[k]) launches_ += (persist_ && kind_coh_[k] != 0) ? 1 : rounds;
+    return queue_status(rounds, st, err);
+}
+
+// Queue the read of every control block behind the launches of a chunk.
+int Engine::queue_status(int rounds, hipStream_t st, std::string *err)
+{
     int hi = 0;
     for (Net *n : active_) hi = std::max(hi, n->slot + 1);
     const int b = next_mirror_;
@@ -938,6 +1067,11 @@ int Engine::collect(std::vector<Net *> *finished, bool all, hipStream_t st, std:
                 continue;
             }
             const Scalars &h = h_scal_[b][n->slot];
+            if (h.loop_failed) {
+                if (err) *err = "resident loop: a wait for another workgroup exceeded its bound";
+                return RN_EDEVICE;
+            }
+            if (h.loop_aborts) n->loop_ok = false;   // not all workgroups found room: one launch per pass from here on
             if (h.mode == MODE_DONE) {
                 int r = finalize(n, h, st, err);
                 if (r) return r;
@@ -1000,7 +1134,8 @@ int Engine::finalize(Net *net, const Scalars &h, hipStream_t st, std::string *er
     r.iters = h.iters;
     r.refreshes = h.refreshes;
     r.n_live = net->n_live;
-    r.passes = rounds_ - net->round0;
+    // a resident loop runs many pass rounds in one launch: count the passes then
+    r.passes = net->loop_used ? h.passes : rounds_ - net->round0;
     if (r.status == 0 && !r.converged) r.status = RN_ENOCONV;
     net->status = r.status;
     const double *P_final = (const double *)(base + L.off_P) + (size_t)(h.refreshes & 1) * n;

@@ -1,0 +1,741 @@
+// rn_loop.hpp -- the CG loop of one network with its state on the chip.
+//
+// A pass kernel reads and writes the CG state once per iteration and ends
+// with a chain of dependent round trips: stores, ticket, partial sums, scalar
+// step, kernel end, next launch, control block, tile loads. Below a few
+// million nodes that chain is the iteration, not the bytes (7 us at 128^2, of
+// which the tile's own arithmetic is under 1 us). Here one launch runs many
+// CG passes of one network. Every workgroup keeps its tile's z, u, p, bonds
+// and FP64 field in registers; per pass it sends out only the u of its edge
+// nodes and its four partial sums:
+//   - a neighbour keeps z and p of its halo nodes itself, from the same
+//     arithmetic as their owner, so u is the only value a halo node needs;
+//   - up to kDirect workgroups, each sums everyone's partials in the order of
+//     the pass kernels and runs the scalar step itself: one exchange per pass.
+//     More of them polling all sums would crowd out the sums themselves (512
+//     workgroups waited 8.5 us for them, 128 waited 4), so there workgroup 0
+//     sums, runs the step and sends the coefficients out.
+// Values travel with a pass number (tag) in the same 8-byte word, edge nodes
+// packed per tile (a store per node where they lie cost 3 us a pass), so no
+// flag, counter or fence is waited for: a reader polls the word itself. Two
+// slots alternate: whoever writes pass k + 2 has seen the coefficients of pass
+// k + 1, for which everyone has posted sums, having read pass k before. The
+// sums are bare doubles in four slots: an empty word (all bits set, a NaN no
+// arithmetic here produces) stands until the sum arrives. Having posted pass
+// k, a workgroup empties its words of slot k + 2: everyone has read pass k - 2,
+// which it held, and the emptying is complete (s_waitcnt, a whole pass later)
+// before it posts pass k + 1, so nobody polls the slot for pass k + 2 before.
+//
+// All workgroups have to run at once. They are admitted by a gate: each counts
+// itself in, and the launch goes ahead only if all arrive in time; otherwise
+// every workgroup leaves with nothing changed and the host goes on with one
+// launch per pass. Behind the gate every wait is bounded too (kSpinTicks).
+//
+// The arithmetic and its order are those of the pass kernels (tile by tile,
+// the same reduction tree), so results are the same bits.
+#pragma once
+
+#include "rn_cg.hpp"
+
+#include <algorithm>
+#include <mutex>
+
+namespace rn {
+namespace {
+
+constexpr uint64_t kGateTicks = 50000ull;        // 0.5 ms: longer than any launch takes to start
+constexpr unsigned kGateGo = 1u, kGateNo = 2u;
+constexpr int kDirect = 64;                      // workgroups up to which each sums for itself
+constexpr int kCopies = 32;                      // copies of the coefficients, 64 bytes each
+typedef unsigned long long u64;
+constexpr u64 kEmpty = ~0ull;
+
+__device__ __forceinline__ u64 word_load(const u64 *p)
+{
+    return __hip_atomic_load((const RN_GLOBAL u64 *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void word_store(u64 *p, u64 v)
+{
+    __hip_atomic_store((RN_GLOBAL u64 *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ u64 tagged(unsigned tag, unsigned v) { return ((u64)tag << 32) | v; }
+
+// A value in the exchange: one tagged word (float) or two, `half` words apart
+// (the halves of a double).
+template <typename T> struct Packed;
+template <> struct Packed<float> {
+    u64 a;
+    __device__ __forceinline__ static void post(u64 *p, int half, unsigned tag, float v)
+    {
+        (void)half;
+        word_store(p, tagged(tag, __builtin_bit_cast(unsigned, v)));
+    }
+    __device__ __forceinline__ void look(const u64 *p, int half)
+    {
+        (void)half;
+        a = word_load(p);
+    }
+    __device__ __forceinline__ void zero(unsigned tag) { a = tagged(tag, 0u); }
+    __device__ __forceinline__ bool here(unsigned tag) const { return (unsigned)(a >> 32) == tag; }
+    __device__ __forceinline__ float value() const { return __builtin_bit_cast(float, (unsigned)a); }
+};
+template <> struct Packed<double> {
+    u64 a, b;
+    __device__ __forceinline__ static void post(u64 *p, int half, unsigned tag, double v)
+    {
+        const u64 w = __builtin_bit_cast(u64, v);
+        word_store(p, tagged(tag, (unsigned)w));
+        word_store(p + half, tagged(tag, (unsigned)(w >> 32)));
+    }
+    __device__ __forceinline__ void look(const u64 *p, int half)
+    {
+        a = word_load(p);
+        b = word_load(p + half);
+    }
+    __device__ __forceinline__ void zero(unsigned tag) { a = b = tagged(tag, 0u); }
+    __device__ __forceinline__ bool here(unsigned tag) const
+    {
+        return (unsigned)(a >> 32) == tag && (unsigned)(b >> 32) == tag;
+    }
+    __device__ __forceinline__ double value() const { return __builtin_bit_cast(double, (b << 32) | (a & 0xffffffffull)); }
+};
+
+// A bounded wait: more() is called after a look that found nothing.
+struct Spin {
+    unsigned *failed;
+    uint64_t t0 = 0;
+    unsigned n = 0;
+    bool ok = true;
+    __device__ explicit Spin(Scalars *s) : failed(&s->loop_failed) {}
+    __device__ __forceinline__ bool more()
+    {
+        if ((++n & 255u) == 0) {
+            const uint64_t now = __builtin_amdgcn_s_memrealtime();
+            if (t0 == 0) t0 = now;
+            if (__hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                ok = false;
+            } else if (now - t0 > kSpinTicks) {
+                __hip_atomic_store(failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ok = false;
+            }
+        }
+        return ok;
+    }
+};
+
+// Thread 0: count this workgroup in and learn whether the launch goes ahead.
+__device__ __forceinline__ int pass_gate(unsigned *gate, unsigned grid, Scalars *s)
+{
+    unsigned state = 0;
+    if (__hip_atomic_fetch_add(gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == grid - 1u) {
+        unsigned expected = 0u;
+        __hip_atomic_compare_exchange_strong(gate + 1, &expected, kGateGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        state = expected ? expected : kGateGo;
+    }
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    while (!state) {
+        state = __hip_atomic_load(gate + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!state && __builtin_amdgcn_s_memrealtime() - t0 > kGateTicks) {
+            unsigned expected = 0u;
+            if (__hip_atomic_compare_exchange_strong(gate + 1, &expected, kGateNo, __ATOMIC_RELAXED,
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                __hip_atomic_fetch_add(&s->loop_aborts, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                state = kGateNo;
+            } else {
+                state = expected;
+            }
+        }
+    }
+    return state == kGateGo;
+}
+
+// LDS of the loop's control, the same for every tile family.
+struct LoopShared {
+    double red[kBlock / kWave][kLoopRed], tot[kBlock / kWave][kLoopRed];
+    Scalars sl[kBlock / kWave];
+    int go;
+};
+
+// The coefficients of the next pass, uniform over the wave.
+struct LoopState {
+    double alpha, beta, sa;
+};
+
+// Emptied sums, the control block's copies, the gate. Returns whether the
+// launch goes ahead.
+__device__ __forceinline__ bool loop_begin(LoopShared &sh, LoopState &L, Scalars *s, const LoopArgs &r, int lb,
+                                           int grid)
+{
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    u64 *part = reinterpret_cast<u64 *>(r.part);
+    if (threadIdx.x < kLoopRed)
+        for (int q = 0; q < kLoopSlots; ++q) word_store(part + (q * kLoopRed + threadIdx.x) * grid + lb, kEmpty);
+    if (lane < kScalWords)
+        reinterpret_cast<u64 *>(&sh.sl[w])[lane] = reinterpret_cast<const u64 *>(s)[lane];
+    L.alpha = s->alpha;
+    L.beta = s->beta;
+    L.sa = s->sigma * s->alpha;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, (unsigned)grid, s);
+    __syncthreads();
+    return sh.go != 0;
+}
+
+// This workgroup's four sums (thread sums, waves, then waves in order, as in
+// finish_pass) into pass `it`'s slot, and the slot after next emptied.
+__device__ __forceinline__ void post_sums(LoopShared &sh, const double (&acc)[kLoopRed], const LoopArgs &r, int it,
+                                          int lb, int grid)
+{
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+#pragma unroll
+    for (int k = 0; k < kLoopRed; ++k) {
+        const double v = wave_sum(acc[k]);
+        if (lane == 0) sh.red[w][k] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < kLoopRed) {
+        u64 *part = reinterpret_cast<u64 *>(r.part) + threadIdx.x * grid + lb;
+        double v = 0.0;
+#pragma unroll
+        for (int ww = 0; ww < kBlock / kWave; ++ww) v += sh.red[ww][threadIdx.x];
+        u64 b = __builtin_bit_cast(u64, v);
+        if (b == kEmpty) b ^= 1;                 // still a NaN
+        __builtin_amdgcn_s_waitcnt(0);           // what the last pass emptied is empty
+        word_store(part + (it & (kLoopSlots - 1)) * (kLoopRed * grid), b);
+        if (it > 0) word_store(part + ((it + 2) & (kLoopSlots - 1)) * (kLoopRed * grid), kEmpty);
+    }
+}
+
+// Everyone's sums: thread t adds blocks t, t + kBlock, ... in order, then
+// lanes and waves as in finish_pass. A look loads all words of AHEAD blocks at
+// once, so a word that arrives late costs one round trip however many were
+// missing.
+template <int AHEAD>
+__device__ __forceinline__ void take_blocks(double (&t)[kLoopRed], const u64 *part, int grid, Spin &spin)
+{
+    for (int b0 = threadIdx.x; b0 < grid; b0 += AHEAD * kBlock) {
+        u64 v[AHEAD][kLoopRed];
+        bool missing;
+        do {
+            missing = false;
+#pragma unroll
+            for (int h = 0; h < AHEAD; ++h)
+#pragma unroll
+                for (int k = 0; k < kLoopRed; ++k) {
+                    const int b = b0 + h * kBlock;
+                    v[h][k] = word_load(part + k * grid + (b < grid ? b : b0));
+                }
+#pragma unroll
+            for (int h = 0; h < AHEAD; ++h)
+#pragma unroll
+                for (int k = 0; k < kLoopRed; ++k) missing |= v[h][k] == kEmpty;
+        } while (missing && spin.more());
+#pragma unroll
+        for (int h = 0; h < AHEAD; ++h)
+            if (h == 0 || b0 + h * kBlock < grid)
+#pragma unroll
+                for (int k = 0; k < kLoopRed; ++k) t[k] += __builtin_bit_cast(double, v[h][k]);
+    }
+}
+
+__device__ __forceinline__ void take_sums(LoopShared &sh, double (&t)[kRed], const LoopArgs &r, int it, int grid,
+                                          Spin &spin)
+{
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const u64 *part = reinterpret_cast<const u64 *>(r.part) + (it & (kLoopSlots - 1)) * (kLoopRed * grid);
+    double v[kLoopRed] = {0.0, 0.0, 0.0, 0.0};
+    if (w * kWave < grid) {                       // wave-uniform: waves past the grid hold zeros
+        if (grid <= kBlock) take_blocks<1>(v, part, grid, spin);
+        else take_blocks<2>(v, part, grid, spin);
+#pragma unroll
+        for (int k = 0; k < kLoopRed; ++k) v[k] = wave_sum(v[k]);
+    }
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < kLoopRed; ++k) sh.tot[w][k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRed; ++k) {
+        t[k] = 0.0;
+        if (k < kLoopRed)
+#pragma unroll
+            for (int ww = 0; ww < kBlock / kWave; ++ww) t[k] += sh.tot[ww][k];
+    }
+}
+
+// The scalar step of a pass from its sums: step_after_cg in straight-line
+// code while the recurrence goes on. The pass that ends the loop (a refresh is
+// due, a breakdown, the launch's limit) runs step_after_cg itself. `sl` is this
+// wave's copy of the control block; its pass counts are those of the start
+// until then. Every pass of the loop adds every pending step to the field, so
+// it counts as one that flushes. Returns whether the loop goes on.
+__device__ __forceinline__ bool loop_step(Scalars *sl, LoopState &L, const double (&t)[kRed], int it, int limit)
+{
+    const double pq = t[0], zq = t[1], qq = t[2], rz = t[3];
+    const double root = sqrt(fmax(rz, 0.0));
+    const double alpha = rz / pq;
+    double rho = fma_(alpha * alpha, qq, fma_(-2.0 * alpha, zq, rz));
+    if (!(rho > 0.0)) rho = 0.0;
+    const double rmax = fmax(sl->rmax, root);
+    const double rroot = sqrt(rho);
+    const double beta = rho / rz;
+    const double est = sl->kappa * sl->sigma * rroot / sl->bhat;
+    const bool fine = rz > 0.0 && pq > 0.0 && isfinite(rz) && isfinite(pq) && isfinite(zq) && isfinite(qq);
+    const bool refresh = est <= sl->tol || rho <= 0.0 || sl->iters + it + 1 >= sl->max_iter ||
+                         (sl->delta > 0.0 && rroot <= sl->delta * rmax);
+    const bool on = fine && !refresh && it + 1 < limit;
+    L.sa = sl->sigma * alpha;
+    L.alpha = alpha;
+    L.beta = beta;
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        if (on) {
+            sl->rmax = rmax;
+            sl->est_rel = est;
+            sl->alpha = alpha;
+            sl->beta = beta;
+        } else {
+            sl->passes += it;
+            sl->iters += it;
+            sl->flush = 1;
+            step_after_cg(sl, t);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return on;
+}
+
+// Behind the sums: the coefficients of the next pass and whether there is one.
+// With few workgroups each wave forms them; else workgroup 0 does and the
+// others' waves read one of its copies: words 0..5 the halves of alpha, beta
+// and sigma alpha, word 6 whether the loop ends.
+__device__ __forceinline__ bool loop_turn(LoopShared &sh, LoopState &L, const LoopArgs &r, int it, int lb, int grid,
+                                          Spin &spin)
+{
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const unsigned tag = r.tag0 + (unsigned)it;
+    if (grid <= kDirect || lb == 0) {
+        double t[kRed];
+        take_sums(sh, t, r, it, grid, spin);
+        const bool on = rfl((int)loop_step(&sh.sl[w], L, t, it, r.limit)) != 0;
+        if (grid > kDirect) {
+            const int word = lane & 7;
+            const double d = word < 2 ? L.alpha : (word < 4 ? L.beta : L.sa);
+            const u64 b = __builtin_bit_cast(u64, d);
+            const unsigned half = word >= 6 ? (unsigned)!on : (unsigned)((word & 1) ? b >> 32 : b);
+            word_store(r.coef + (w * 8 + (lane >> 3)) * 8 + word, tagged(tag, half));
+        }
+        return on;
+    }
+    const u64 *c = r.coef + (lb & (kCopies - 1)) * 8 + (lane & 7);
+    u64 v;
+    do v = word_load(c);
+    while (__ballot((unsigned)(v >> 32) != tag) != 0ull && spin.more());
+    const int half = (int)(unsigned)v;
+    auto get = [&](int k) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane(half, 2 * k),
+                       hi = (unsigned)__builtin_amdgcn_readlane(half, 2 * k + 1);
+        return __builtin_bit_cast(double, ((u64)hi << 32) | lo);
+    };
+    L.alpha = get(0);
+    L.beta = get(1);
+    L.sa = get(2);
+    return __builtin_amdgcn_readlane(half, 6) == 0;
+}
+
+// hide(v): the compiler may not carry anything computed from v across passes.
+// Left to itself it keeps every invariant of the loop (diagonals, shifted
+// bonds, addresses, lane masks) in registers and spills the state instead.
+template <typename V>
+__device__ __forceinline__ void hide(V &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void hide_s(int &v) { asm volatile("" : "+s"(v)); }
+
+// ---------------------------------------------------------------- 2D
+// The tile of pass2d_kernel (Tile2D), TPW of them per workgroup: thread, row
+// and segment hold the same nodes. Slots past a periodic edge hold the image
+// of the opposite edge; their u comes from the owner like a halo node's.
+// With two tiles per workgroup the FP64 field sits in LDS (one word per node
+// and thread, touched once per pass), which leaves the registers of four
+// waves per SIMD to the rest of the state.
+// Exchange words of a tile: its first row, last row, first column, last column.
+template <typename T, int SHAPE>
+constexpr int edge_words2d() { return 2 * (Tile2D<T, SHAPE>::COLS + Tile2D<T, SHAPE>::ROWS); }
+
+template <typename T, int SHAPE, int TPW>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void loop2d_kernel(
+    const PassArgs<T> *__restrict__ tab, Scalars *scal, int parity, int slot, LoopArgs r)
+{
+    constexpr int TY = Tile2D<T, SHAPE>::TY, SEG = Tile2D<T, SHAPE>::SEG, NW = kBlock / kWave;
+    constexpr int ROWS = Tile2D<T, SHAPE>::ROWS, COLS = Tile2D<T, SHAPE>::COLS;
+    constexpr int E = edge_words2d<T, SHAPE>(), EW = E * (int)(sizeof(T) / 4);   // values, words of a tile
+    constexpr int kTop = 0, kBottom = COLS, kLeft = 2 * COLS, kRight = 2 * COLS + ROWS;
+    constexpr bool kFieldLds = TPW > 1;
+    constexpr bool kTight = SHAPE == 0;           // many nodes per thread: registers are scarce
+    __shared__ T edge[2][NW][SEG][kWave];         // [0]: first row of each wave, [1]: last row
+    __shared__ LoopShared sh;
+    __shared__ double fl[kFieldLds ? TPW * SEG * TY : 1][kBlock];
+    const PassArgs<T> &a = tab[2 * slot + parity];
+    Scalars *s = scal + slot;
+    if (blockIdx.x == 0 && threadIdx.x < 2) r.gate_clear[threadIdx.x] = 0u;
+    if (s->mode != MODE_CG) return;
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int lb = (int)blockIdx.x, grid = a.grid, first = xcd_remap(lb, grid);
+    const int nx = a.nx, ny = a.ny, ntx = a.ntx, nty = a.nty, wrap = a.wrap;
+    const bool wx = wrap & 1, wy = (wrap >> 1) & 1;
+    const bool jacobi = a.jacobi != 0, xaxis = a.axis == 0;
+    const Step<T> k0 = make_step(a, s);
+    const int64_t passes0 = s->passes;
+    double *__restrict__ P = a.P[s->refreshes & 1];
+    auto colm = [&](int xx) { return xx >= 0 && xx < nx ? xx : (wx && xx == nx ? 0 : (wx && xx == -1 ? nx - 1 : -1)); };
+    auto rowm = [&](int yy) { return yy >= 0 && yy < ny ? yy : (wy && yy == ny ? 0 : (wy && yy == -1 ? ny - 1 : -1)); };
+
+    // ---- state of the tiles
+    T z_[TPW][SEG][TY], u_[TPW][SEG][TY], p_[TPW][SEG][TY], gxv[TPW][SEG][TY], gyv[TPW][SEG][TY + 1];
+    double Pv[kFieldLds ? 1 : TPW][SEG][TY];
+    T ez[TPW][SEG], eu[TPW][SEG], ep[TPW][SEG];    // halo row of the first / last wave
+    T hz[TPW], hu[TPW], hp[TPW], hg[TPW];          // halo column node of this lane
+    unsigned liv = 0;                              // bits (tile, segment, row): interior nodes of the lattice
+    int tx_[TPW], ty_[TPW];                        // tile coordinates; past the lattice: no tile
+    auto bit = [&](int t, int sg, int j) { return 1u << ((t * SEG + sg) * TY + j); };
+    auto colx = [&](int t, int sg) { return tx_[t] * COLS + kWave * sg + lane; };
+    auto rowy = [&](int t, int j) { return ty_[t] * ROWS + w * TY + j; };
+    const bool hleft = lane < TY, hright = lane >= kWave - TY;   // halo column lanes: row y0 + hrow at x0 - 1 / x0 + COLS
+    const int hrow = hleft ? lane : lane - (kWave - TY);
+    // the row of halo nodes this wave keeps: above the tile (first wave), below it (last wave)
+    auto halo_y = [&](int t) { return w == 0 ? rowm(ty_[t] * ROWS - 1) : (w == NW - 1 ? rowm(ty_[t] * ROWS + ROWS) : -1); };
+    auto halo_x = [&](int t) {
+        return (hleft || hright) && rowy(t, hrow) < ny ? colm(hleft ? tx_[t] * COLS - 1 : tx_[t] * COLS + COLS) : -1;
+    };
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        const int tile = first + t * grid;
+        const bool has = tile < a.ntiles;
+        tx_[t] = has ? tile % ntx : ntx + 1;
+        ty_[t] = has ? tile / ntx : nty + 1;
+#pragma unroll
+        for (int sg = 0; sg < SEG; ++sg) {
+            const int x = colx(t, sg), xm = colm(x);
+#pragma unroll
+            for (int j = 0; j < TY; ++j) {
+                const int yy = rowy(t, j), ym = rowm(yy);
+                const bool held = xm >= 0 && ym >= 0;
+                const int i = held ? ym * nx + xm : 0;
+                const T z0 = ldg(a.src.z + i), u0 = ldg(a.src.u + i), p0 = ldg(k0.p1 + i), g0 = ldg(a.gT[0] + i),
+                        g1 = ldg(a.gT[1] + i);
+                double v = ldg(P + i);
+                if (k0.sa3 != 0.0 || k0.sa4 != 0.0)
+                    v = with_steps(v, k0.sa4, (double)ldg(k0.p4 + i), k0.sa3, (double)ldg(k0.p3 + i));
+                if (k0.sa2 != 0.0) v = with_steps(v, k0.sa2, (double)ldg(k0.p2 + i), 0.0, 0.0);
+                z_[t][sg][j] = held ? z0 : T(0);
+                u_[t][sg][j] = held ? u0 : T(0);
+                p_[t][sg][j] = held ? p0 : T(0);
+                gxv[t][sg][j] = held ? g0 : T(0);
+                gyv[t][sg][j + 1] = held ? g1 : T(0);
+                if constexpr (kFieldLds) fl[(t * SEG + sg) * TY + j][threadIdx.x] = v;
+                else Pv[t][sg][j] = v;
+                const bool face = xaxis ? (x == 0 || x == nx - 1) : (yy == 0 || yy == ny - 1);
+                if (x < nx && yy < ny && !face) liv |= bit(t, sg, j);
+            }
+            // bond below the wave: none at y = 0 unless y wraps (then the bond ny-1 -> 0)
+            const int ym = rowm(rowy(t, 0) - 1);
+            const bool below = xm >= 0 && ym >= 0;
+            const T gb = ldg(a.gT[1] + (below ? ym * nx + xm : 0));
+            gyv[t][sg][0] = below ? gb : T(0);
+            const int yh = halo_y(t);
+            const bool hok = x < nx && yh >= 0;
+            const int ri = hok ? yh * nx + x : 0;
+            const T z0 = ldg(a.src.z + ri), u0 = ldg(a.src.u + ri), p0 = ldg(k0.p1 + ri);
+            ez[t][sg] = hok ? z0 : T(0);
+            eu[t][sg] = hok ? u0 : T(0);
+            ep[t][sg] = hok ? p0 : T(0);
+        }
+        const int hx = halo_x(t);
+        const bool hok = hx >= 0;
+        const int ci = hok ? rowy(t, hrow) * nx + hx : 0;
+        const T z0 = ldg(a.src.z + ci), u0 = ldg(a.src.u + ci), p0 = ldg(k0.p1 + ci), g0 = ldg(a.gT[0] + ci);
+        hz[t] = hok ? z0 : T(0);
+        hu[t] = hok ? u0 : T(0);
+        hp[t] = hok ? p0 : T(0);
+        hg[t] = hok && hleft ? g0 : T(0);
+    }
+    LoopState L;
+    const bool admitted = loop_begin(sh, L, s, r, lb, grid);
+
+    int it = 0;
+    for (bool on = admitted; on; ++it) {
+        Spin spin(s);
+        const T alpha = (T)rfl(L.alpha), beta = (T)rfl(L.beta);
+        const double sa = rfl(L.sa);
+        const unsigned tag = r.tag0 + (unsigned)it;
+        u64 *xb = r.xch + (size_t)(it & 1) * r.xch_slot;     // this pass's edge values
+        if constexpr (kTight) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+                for (int sg = 0; sg < SEG; ++sg) {
+#pragma unroll
+                    for (int j = 0; j < TY; ++j) {
+                        hide(gxv[t][sg][j]);
+                        hide(gyv[t][sg][j]);
+                    }
+                    hide(gyv[t][sg][TY]);
+                }
+                hide(hg[t]);
+                hide_s(tx_[t]);
+                hide_s(ty_[t]);
+            }
+            hide(liv);
+        }
+        // z' and p' of the halo
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+            for (int sg = 0; sg < SEG; ++sg) {
+                ez[t][sg] = step_z(ez[t][sg], alpha, eu[t][sg]);
+                ep[t][sg] = step_p(ez[t][sg], beta, ep[t][sg]);
+            }
+            hz[t] = step_z(hz[t], alpha, hu[t]);
+            hp[t] = step_p(hz[t], beta, hp[t]);
+        }
+        double acc[kLoopRed] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            if (t > 0) __syncthreads();            // the previous tile's LDS rows are reused
+            // the pending step, then z' and p' of the tile
+#pragma unroll
+            for (int sg = 0; sg < SEG; ++sg) {
+#pragma unroll
+                for (int j = 0; j < TY; ++j) {
+                    if (sa != 0.0) {
+                        if constexpr (kFieldLds) {
+                            double &f = fl[(t * SEG + sg) * TY + j][threadIdx.x];
+                            f = fma(sa, (double)p_[t][sg][j], f);
+                        } else {
+                            Pv[t][sg][j] = fma(sa, (double)p_[t][sg][j], Pv[t][sg][j]);
+                        }
+                    }
+                    const T zc = step_z(z_[t][sg][j], alpha, u_[t][sg][j]);
+                    z_[t][sg][j] = zc;
+                    p_[t][sg][j] = step_p(zc, beta, p_[t][sg][j]);
+                }
+                edge[0][w][sg][lane] = p_[t][sg][0];
+                edge[1][w][sg][lane] = p_[t][sg][TY - 1];
+            }
+            __syncthreads();
+            T pv[SEG][TY + 2];
+#pragma unroll
+            for (int sg = 0; sg < SEG; ++sg) {
+                pv[sg][0] = w == 0 ? ep[t][sg] : edge[1][w - 1][sg][lane];
+                pv[sg][TY + 1] = w == NW - 1 ? ep[t][sg] : edge[0][w + 1][sg][lane];
+#pragma unroll
+                for (int j = 0; j < TY; ++j) pv[sg][j + 1] = p_[t][sg][j];
+            }
+#pragma unroll
+            for (int j = 0; j < TY; ++j) {
+                const T hl = lane_bcast(hp[t], j);
+                const T hrr = lane_bcast(hp[t], kWave - TY + j);
+                const T hgl = lane_bcast(hg[t], j);
+#pragma unroll
+                for (int sg = 0; sg < SEG; ++sg) {
+                    const T zc = z_[t][sg][j];
+                    const T pc = pv[sg][j + 1];
+                    T pl = lane_below(pc);
+                    T pr = lane_above(pc);
+                    T gxl = lane_below(gxv[t][sg][j]);
+                    const T lj = sg == 0 ? hl : lane_bcast(pv[sg > 0 ? sg - 1 : 0][j + 1], kWave - 1);
+                    const T gj = sg == 0 ? hgl : lane_bcast(gxv[t][sg > 0 ? sg - 1 : 0][j], kWave - 1);
+                    const T rj = sg == SEG - 1 ? hrr : lane_bcast(pv[sg < SEG - 1 ? sg + 1 : 0][j + 1], 0);
+                    if (lane == 0) {
+                        pl = lj;
+                        gxl = gj;
+                    }
+                    if (lane == kWave - 1) pr = rj;
+                    const T gxr = gxv[t][sg][j], gyl = gyv[t][sg][j], gyr = gyv[t][sg][j + 1];
+                    T qv = stencil2d(left_first<T>(sg), gxl, pc - pl, gxr, pc - pr, gyl, pc - pv[sg][j], gyr,
+                                     pc - pv[sg][j + 2]);
+                    const T d = diag_sum(gxl, gxr, gyl, gyr);
+                    const bool live = (liv & bit(t, sg, j)) && d > T(0);
+                    if (!live) qv = T(0);
+                    const T uv = live ? apply_minv(qv, d, jacobi) : T(0);
+                    u_[t][sg][j] = uv;
+                    const double dq = (double)qv, du = (double)uv;
+                    const double dp = (double)pc, dz = live ? (double)zc : 0.0;
+                    acc[0] = fma_(dp, dq, acc[0]);
+                    acc[1] = fma_(dz, dq, acc[1]);
+                    acc[2] = fma_(dq, du, acc[2]);
+                    acc[3] = fma_((double)(jacobi ? d : T(1)) * dz, dz, acc[3]);
+                }
+            }
+        }
+        // u of the tiles' edges: rows as they lie, the columns gathered into
+        // lanes 0 .. 2 TY - 1
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            const int tile = first + t * grid;
+            if (tile >= a.ntiles) continue;        // uniform
+            u64 *xt = xb + (size_t)tile * EW;
+            const int jb = min(ty_[t] * ROWS + ROWS, ny) - 1 - rowy(t, 0);    // last lattice row, if in this wave
+            const int cl = min(COLS, nx - tx_[t] * COLS) - 1;                 // last lattice column of the tile
+            T cv = T(0);
+#pragma unroll
+            for (int j = 0; j < TY; ++j) {
+                const T left = lane_bcast(u_[t][0][j], 0);
+                T right = T(0);
+#pragma unroll
+                for (int sg = 0; sg < SEG; ++sg) {
+                    if (cl >> 6 == sg) right = lane_at(u_[t][sg][j], cl & (kWave - 1));
+                    if (((w == 0 && j == 0) || j == jb) && colx(t, sg) < nx) {
+                        if (w == 0 && j == 0)
+                            Packed<T>::post(xt + kTop + kWave * sg + lane, E, tag, u_[t][sg][j]);
+                        if (j == jb) Packed<T>::post(xt + kBottom + kWave * sg + lane, E, tag, u_[t][sg][j]);
+                    }
+                }
+                if (lane == j) cv = left;
+                if (lane == TY + j) cv = right;
+            }
+            if (lane < 2 * TY && rowy(t, lane < TY ? lane : lane - TY) < ny)
+                Packed<T>::post(xt + (lane < TY ? kLeft + lane : kRight + lane - TY) + w * TY, E, tag, cv);
+        }
+        post_sums(sh, acc, r, it, lb, grid);
+        // u of the halo and the images, from their owners (before the sums,
+        // whose way is longer)
+        Packed<T> ew[TPW][SEG], hw[TPW];
+        bool missing;
+        do {
+            missing = false;
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                const int yh = halo_y(t), hx = halo_x(t);
+                // the neighbour above shows its last row, the one below its first
+                const int ey = w == 0 ? (ty_[t] > 0 ? ty_[t] : nty) - 1 : (ty_[t] + 1 < nty ? ty_[t] + 1 : 0);
+#pragma unroll
+                for (int sg = 0; sg < SEG; ++sg) {
+                    if (yh >= 0 && colx(t, sg) < nx)
+                        ew[t][sg].look(xb + (size_t)(ey * ntx + tx_[t]) * EW + (w == 0 ? kBottom : kTop) + kWave * sg + lane, E);
+                    else ew[t][sg].zero(tag);
+                }
+                if (hx >= 0) {
+                    const int ex = hleft ? (tx_[t] > 0 ? tx_[t] : ntx) - 1 : (tx_[t] + 1 < ntx ? tx_[t] + 1 : 0);
+                    hw[t].look(xb + (size_t)(ty_[t] * ntx + ex) * EW + (hleft ? kRight : kLeft) + w * TY + hrow, E);
+                } else hw[t].zero(tag);
+            }
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+                for (int sg = 0; sg < SEG; ++sg) missing |= !ew[t][sg].here(tag);
+                missing |= !hw[t].here(tag);
+            }
+        } while (missing && spin.more());
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+            for (int sg = 0; sg < SEG; ++sg) {
+                eu[t][sg] = ew[t][sg].value();
+                if (wrap) {                        // uniform
+#pragma unroll
+                    for (int j = 0; j < TY; ++j) {
+                        const int x = colx(t, sg), y = rowy(t, j);
+                        const bool ix = wx && x == nx && y < ny, iy = wy && y == ny && x < nx;
+                        if (ix || iy) {            // image of a node in column 0 or row 0
+                            Packed<T> v;
+                            const u64 *q = xb + (size_t)(ix ? ty_[t] * ntx : tx_[t]) * EW +
+                                           (ix ? kLeft + w * TY + j : kTop + kWave * sg + lane);
+                            do v.look(q, E);
+                            while (!v.here(tag) && spin.more());
+                            u_[t][sg][j] = v.value();
+                        }
+                    }
+                }
+            }
+            hu[t] = hw[t].value();
+        }
+        on = loop_turn(sh, L, r, it, lb, grid, spin);
+        if (__any(!spin.ok)) return;               // a wait gave up: the host fails the context
+    }
+    // ---- the state of the last pass, as a pass kernel leaves it (alpha is the
+    // one pending step). A launch that was turned away moves z and u to the
+    // other parity, where the next round reads them, and no more.
+    const int64_t done = passes0 + it - 1;
+    T *pd = a.pbuf[a.npbuf == 5 ? (int)(done % 5) : (int)(done % 3)];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int sg = 0; sg < SEG; ++sg)
+#pragma unroll
+            for (int j = 0; j < TY; ++j)
+                if (colx(t, sg) < nx && rowy(t, j) < ny) {
+                    const int i = rowy(t, j) * nx + colx(t, sg);
+                    stg(a.dst.z + i, z_[t][sg][j]);
+                    stg(a.dst.u + i, u_[t][sg][j]);
+                    if (!admitted) continue;
+                    stg(pd + i, p_[t][sg][j]);
+                    double v;
+                    if constexpr (kFieldLds) v = fl[(t * SEG + sg) * TY + j][threadIdx.x];
+                    else v = Pv[t][sg][j];
+                    stg(P + i, v);
+                }
+    if (admitted && lb == 0 && threadIdx.x < kScalWords)   // wave 0, which ran the last step on this copy
+        reinterpret_cast<u64 *>(s)[threadIdx.x] = reinterpret_cast<const volatile u64 *>(&sh.sl[0])[threadIdx.x];
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------- launchers
+
+template <typename T>
+static const void *loop_kernel(int dim, int tpw, int tile_z)
+{
+    (void)tile_z;
+    if (dim == 2 && tpw == 1) return reinterpret_cast<const void *>(&loop2d_kernel<T, 0, 1>);
+    if (dim == 2 && tpw == 2) return reinterpret_cast<const void *>(&loop2d_kernel<T, 0, 2>);
+    if (dim == -2 && tpw == 1) return reinterpret_cast<const void *>(&loop2d_kernel<T, 1, 1>);
+    return nullptr;
+}
+
+template <typename T>
+hipError_t loop_capacity(int dim, int tpw, int tile_z, int *cap)
+{
+    *cap = 0;
+    const void *k = loop_kernel<T>(dim, tpw, tile_z);
+    if (!k) return hipSuccess;
+    int dev = 0, cus = 0, per = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, kBlock, 0);
+    if (e != hipSuccess) return e;
+    *cap = std::min(per * cus, kLoopGridMax);
+    return hipSuccess;
+}
+
+template <typename T>
+size_t loop_exchange_words(int dim, int tile_z, int ntiles)
+{
+    (void)tile_z;
+    const size_t values = dim == 2 ? edge_words2d<T, 0>() : edge_words2d<T, 1>();
+    return values * (sizeof(T) / 4) * (size_t)ntiles;
+}
+
+template <typename T>
+hipError_t launch_loop(int dim, int tpw, int tile_z, int grid, const PassArgs<T> *tab, Scalars *scal, int parity,
+                       int slot, const LoopArgs &r, hipStream_t st)
+{
+    const void *k = loop_kernel<T>(dim, tpw, tile_z);
+    if (!k || grid < 1 || grid > kLoopGridMax) return hipErrorInvalidValue;
+    LoopArgs args = r;
+    void *p[] = {(void *)&tab, (void *)&scal, (void *)&parity, (void *)&slot, (void *)&args};
+    return hipLaunchKernel(k, dim3((unsigned)grid), dim3(kBlock), p, 0, st);
+}
+
+template size_t loop_exchange_words<float>(int, int, int);
+template size_t loop_exchange_words<double>(int, int, int);
+template hipError_t loop_capacity<float>(int, int, int, int *);
+template hipError_t loop_capacity<double>(int, int, int, int *);
+template hipError_t launch_loop<float>(int, int, int, int, const PassArgs<float> *, Scalars *, int, int,
+                                       const LoopArgs &, hipStream_t);
+template hipError_t launch_loop<double>(int, int, int, int, const PassArgs<double> *, Scalars *, int, int,
+                                        const LoopArgs &, hipStream_t);
+
+}  // namespace rn
