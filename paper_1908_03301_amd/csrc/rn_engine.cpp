@@ -844,9 +844,9 @@ int Engine::launch_persistent(int rounds, hipStream_t st, std::string *err)
 // workgroups all have to fit the chip at once. Below that size a pass is bound
 // by its chain of round trips, and every shape that fits is faster there. Whole
 // solves over their iterations, one launch per pass against the loop: 128^2
-// mixed 9.0 -> 3.6 us, 201 x 150 FP64 9.1 -> 3.9, 512^2 FP64 11.3 -> 7.1,
-// 1024^2 mixed 16.0 -> 10.4, 1024^2 FP64 21.4 -> 14.6. Several networks share
-// launches instead.
+// mixed 9.0 -> 3.6 us, 201 x 150 FP64 9.1 -> 3.9, 512^2 FP64 10.9 -> 5.1,
+// 1024^2 mixed 16.0 -> 6.4, 1024^2 FP64 21.4 -> 8.0, 2048^2 mixed 34.0 -> 30.4.
+// Several networks share launches instead.
 int Engine::loop_fits(const Net *net, bool *fits, std::string *err)
 {
     *fits = false;

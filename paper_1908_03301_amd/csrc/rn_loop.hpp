@@ -60,6 +60,12 @@ __device__ __forceinline__ void word_store(u64 *p, u64 v)
     __hip_atomic_store((RN_GLOBAL u64 *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// the same at a byte offset of the lane's own from an address all lanes share
+__device__ __forceinline__ u64 *at(u64 *base, unsigned off)
+{
+    return reinterpret_cast<u64 *>(reinterpret_cast<char *>(base) + off);
+}
+
 __device__ __forceinline__ u64 tagged(unsigned tag, unsigned v) { return ((u64)tag << 32) | v; }
 
 // A value in the exchange: one tagged word (float) or two, `half` words apart
@@ -186,7 +192,8 @@ __device__ __forceinline__ bool loop_begin(LoopShared &sh, LoopState &L, Scalars
 }
 
 // This workgroup's four sums (thread sums, waves, then waves in order, as in
-// finish_pass) into pass `it`'s slot, and the slot after next emptied.
+// finish_pass) into pass `it`'s slot, and the slot after next emptied. Wave 0
+// has waited (s_waitcnt) for what it emptied in the pass before.
 __device__ __forceinline__ void post_sums(LoopShared &sh, const double (&acc)[kLoopRed], const LoopArgs &r, int it,
                                           int lb, int grid)
 {
@@ -204,7 +211,6 @@ __device__ __forceinline__ void post_sums(LoopShared &sh, const double (&acc)[kL
         for (int ww = 0; ww < kBlock / kWave; ++ww) v += sh.red[ww][threadIdx.x];
         u64 b = __builtin_bit_cast(u64, v);
         if (b == kEmpty) b ^= 1;                 // still a NaN
-        __builtin_amdgcn_s_waitcnt(0);           // what the last pass emptied is empty
         word_store(part + (it & (kLoopSlots - 1)) * (kLoopRed * grid), b);
         if (it > 0) word_store(part + ((it + 2) & (kLoopSlots - 1)) * (kLoopRed * grid), kEmpty);
     }
@@ -346,6 +352,20 @@ __device__ __forceinline__ bool loop_turn(LoopShared &sh, LoopState &L, const Lo
     return __builtin_amdgcn_readlane(half, 6) == 0;
 }
 
+// Loads and stores at a 32-bit index: a network that fits the chip has its
+// arrays in a few tens of MB, and an offset from a base in scalar registers
+// takes one vector register where an address takes two.
+template <typename T>
+__device__ __forceinline__ T ldi(const T *base, int i)
+{
+    return *reinterpret_cast<const RN_GLOBAL T *>((const RN_GLOBAL char *)base + (unsigned)i * (unsigned)sizeof(T));
+}
+template <typename T>
+__device__ __forceinline__ void sti(T *base, int i, T v)
+{
+    *reinterpret_cast<RN_GLOBAL T *>((RN_GLOBAL char *)base + (unsigned)i * (unsigned)sizeof(T)) = v;
+}
+
 // hide(v): the compiler may not carry anything computed from v across passes.
 // Left to itself it keeps every invariant of the loop (diagonals, shifted
 // bonds, addresses, lane masks) in registers and spills the state instead.
@@ -357,9 +377,13 @@ __device__ __forceinline__ void hide_s(int &v) { asm volatile("" : "+s"(v)); }
 // The tile of pass2d_kernel (Tile2D), TPW of them per workgroup: thread, row
 // and segment hold the same nodes. Slots past a periodic edge hold the image
 // of the opposite edge; their u comes from the owner like a halo node's.
-// With two tiles per workgroup the FP64 field sits in LDS (one word per node
-// and thread, touched once per pass), which leaves the registers of four
-// waves per SIMD to the rest of the state.
+// The FP64 field of the full tile sits in LDS (one word per node and thread,
+// touched once per pass), which leaves the registers of four waves per SIMD to
+// the rest of the state. With two tiles per workgroup that is still too much (z,
+// u, p and the bonds take 84 of a thread's 128 registers, and holding them all
+// spilled 50 words a pass): there the bonds come from memory in every pass,
+// 8 bytes of the plain pass's 39 per node and mostly from the L2, and are on
+// their way while the pass before waits for its sums.
 // Exchange words of a tile: its first row, last row, first column, last column.
 template <typename T, int SHAPE>
 constexpr int edge_words2d() { return 2 * (Tile2D<T, SHAPE>::COLS + Tile2D<T, SHAPE>::ROWS); }
@@ -372,8 +396,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     constexpr int ROWS = Tile2D<T, SHAPE>::ROWS, COLS = Tile2D<T, SHAPE>::COLS;
     constexpr int E = edge_words2d<T, SHAPE>(), EW = E * (int)(sizeof(T) / 4);   // values, words of a tile
     constexpr int kTop = 0, kBottom = COLS, kLeft = 2 * COLS, kRight = 2 * COLS + ROWS;
-    constexpr bool kFieldLds = TPW > 1;
     constexpr bool kTight = SHAPE == 0;           // many nodes per thread: registers are scarce
+    constexpr bool kFieldLds = kTight;
+    constexpr bool kLean = TPW > 1;               // bonds from memory, halo addresses formed anew
     __shared__ T edge[2][NW][SEG][kWave];         // [0]: first row of each wave, [1]: last row
     __shared__ LoopShared sh;
     __shared__ double fl[kFieldLds ? TPW * SEG * TY : 1][kBlock];
@@ -381,7 +406,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     Scalars *s = scal + slot;
     if (blockIdx.x == 0 && threadIdx.x < 2) r.gate_clear[threadIdx.x] = 0u;
     if (s->mode != MODE_CG) return;
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    int lane = threadIdx.x & (kWave - 1);
+    const int w = rfl((int)threadIdx.x / kWave);
     const int lb = (int)blockIdx.x, grid = a.grid, first = xcd_remap(lb, grid);
     const int nx = a.nx, ny = a.ny, ntx = a.ntx, nty = a.nty, wrap = a.wrap;
     const bool wx = wrap & 1, wy = (wrap >> 1) & 1;
@@ -402,13 +428,51 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     auto bit = [&](int t, int sg, int j) { return 1u << ((t * SEG + sg) * TY + j); };
     auto colx = [&](int t, int sg) { return tx_[t] * COLS + kWave * sg + lane; };
     auto rowy = [&](int t, int j) { return ty_[t] * ROWS + w * TY + j; };
-    const bool hleft = lane < TY, hright = lane >= kWave - TY;   // halo column lanes: row y0 + hrow at x0 - 1 / x0 + COLS
-    const int hrow = hleft ? lane : lane - (kWave - TY);
+    // halo column lanes: row y0 + hrow() at x0 - 1 (left) or x0 + COLS (right)
+    auto hleft = [&] { return lane < TY; };
+    auto hrow = [&] { return hleft() ? lane : lane - (kWave - TY); };
     // the row of halo nodes this wave keeps: above the tile (first wave), below it (last wave)
     auto halo_y = [&](int t) { return w == 0 ? rowm(ty_[t] * ROWS - 1) : (w == NW - 1 ? rowm(ty_[t] * ROWS + ROWS) : -1); };
     auto halo_x = [&](int t) {
-        return (hleft || hright) && rowy(t, hrow) < ny ? colm(hleft ? tx_[t] * COLS - 1 : tx_[t] * COLS + COLS) : -1;
+        return (hleft() || lane >= kWave - TY) && rowy(t, hrow()) < ny ? colm(hleft() ? tx_[t] * COLS - 1 : tx_[t] * COLS + COLS) : -1;
     };
+    // bonds of tile t: right and upper of the nodes (0 where a slot holds none
+    // is the arrays' own doing inside the lattice; elsewhere they are not
+    // used), below the wave (none at y = 0 unless y wraps: then ny-1 -> 0) and
+    // left of the tile
+    auto load_bonds = [&](int t) {
+#pragma unroll
+        for (int sg = 0; sg < SEG; ++sg) {
+            const int xm = colm(colx(t, sg)), xc = xm >= 0 ? xm : 0;
+#pragma unroll
+            for (int j = 0; j < TY; ++j) {
+                const int ym = rowm(rowy(t, j));
+                const int i = (ym >= 0 ? ym : 0) * nx + xc;
+                gxv[t][sg][j] = ldi(a.gT[0], i);
+                gyv[t][sg][j + 1] = ldi(a.gT[1], i);
+            }
+            const int ym = rowm(rowy(t, 0) - 1);
+            const T gb = ldi(a.gT[1], (ym >= 0 ? ym : 0) * nx + xc);
+            gyv[t][sg][0] = ym >= 0 ? gb : T(0);
+        }
+        const int hx = halo_x(t);
+        const T g0 = ldi(a.gT[0], (hx >= 0 ? rowy(t, hrow()) * nx + hx : 0));
+        hg[t] = hx >= 0 && hleft() ? g0 : T(0);
+    };
+    // where the halo's words lie in an exchange slot (bytes; kNone: no node):
+    // the neighbour above shows its last row, the one below its first
+    constexpr unsigned kNone = ~0u;
+    auto row_words = [&](int t, int sg) {
+        if (halo_y(t) < 0 || colx(t, sg) >= nx) return kNone;
+        const int ey = w == 0 ? (ty_[t] > 0 ? ty_[t] : nty) - 1 : (ty_[t] + 1 < nty ? ty_[t] + 1 : 0);
+        return (unsigned)((ey * ntx + tx_[t]) * EW + (w == 0 ? kBottom : kTop) + kWave * sg + lane) * 8u;
+    };
+    auto col_words = [&](int t) {
+        if (halo_x(t) < 0) return kNone;
+        const int ex = hleft() ? (tx_[t] > 0 ? tx_[t] : ntx) - 1 : (tx_[t] + 1 < ntx ? tx_[t] + 1 : 0);
+        return (unsigned)((ty_[t] * ntx + ex) * EW + (hleft() ? kRight : kLeft) + w * TY + hrow()) * 8u;
+    };
+    unsigned ro[TPW][SEG], co[TPW];
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
         const int tile = first + t * grid;
@@ -423,43 +487,40 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 const int yy = rowy(t, j), ym = rowm(yy);
                 const bool held = xm >= 0 && ym >= 0;
                 const int i = held ? ym * nx + xm : 0;
-                const T z0 = ldg(a.src.z + i), u0 = ldg(a.src.u + i), p0 = ldg(k0.p1 + i), g0 = ldg(a.gT[0] + i),
-                        g1 = ldg(a.gT[1] + i);
-                double v = ldg(P + i);
+                const T z0 = ldi(a.src.z, i), u0 = ldi(a.src.u, i), p0 = ldi(k0.p1, i);
+                double v = ldi((const double *)P, i);
                 if (k0.sa3 != 0.0 || k0.sa4 != 0.0)
-                    v = with_steps(v, k0.sa4, (double)ldg(k0.p4 + i), k0.sa3, (double)ldg(k0.p3 + i));
-                if (k0.sa2 != 0.0) v = with_steps(v, k0.sa2, (double)ldg(k0.p2 + i), 0.0, 0.0);
+                    v = with_steps(v, k0.sa4, (double)ldi(k0.p4, i), k0.sa3, (double)ldi(k0.p3, i));
+                if (k0.sa2 != 0.0) v = with_steps(v, k0.sa2, (double)ldi(k0.p2, i), 0.0, 0.0);
                 z_[t][sg][j] = held ? z0 : T(0);
                 u_[t][sg][j] = held ? u0 : T(0);
                 p_[t][sg][j] = held ? p0 : T(0);
-                gxv[t][sg][j] = held ? g0 : T(0);
-                gyv[t][sg][j + 1] = held ? g1 : T(0);
                 if constexpr (kFieldLds) fl[(t * SEG + sg) * TY + j][threadIdx.x] = v;
                 else Pv[t][sg][j] = v;
                 const bool face = xaxis ? (x == 0 || x == nx - 1) : (yy == 0 || yy == ny - 1);
                 if (x < nx && yy < ny && !face) liv |= bit(t, sg, j);
             }
-            // bond below the wave: none at y = 0 unless y wraps (then the bond ny-1 -> 0)
-            const int ym = rowm(rowy(t, 0) - 1);
-            const bool below = xm >= 0 && ym >= 0;
-            const T gb = ldg(a.gT[1] + (below ? ym * nx + xm : 0));
-            gyv[t][sg][0] = below ? gb : T(0);
             const int yh = halo_y(t);
             const bool hok = x < nx && yh >= 0;
             const int ri = hok ? yh * nx + x : 0;
-            const T z0 = ldg(a.src.z + ri), u0 = ldg(a.src.u + ri), p0 = ldg(k0.p1 + ri);
+            const T z0 = ldi(a.src.z, ri), u0 = ldi(a.src.u, ri), p0 = ldi(k0.p1, ri);
             ez[t][sg] = hok ? z0 : T(0);
             eu[t][sg] = hok ? u0 : T(0);
             ep[t][sg] = hok ? p0 : T(0);
         }
         const int hx = halo_x(t);
         const bool hok = hx >= 0;
-        const int ci = hok ? rowy(t, hrow) * nx + hx : 0;
-        const T z0 = ldg(a.src.z + ci), u0 = ldg(a.src.u + ci), p0 = ldg(k0.p1 + ci), g0 = ldg(a.gT[0] + ci);
+        const int ci = hok ? rowy(t, hrow()) * nx + hx : 0;
+        const T z0 = ldi(a.src.z, ci), u0 = ldi(a.src.u, ci), p0 = ldi(k0.p1, ci);
         hz[t] = hok ? z0 : T(0);
         hu[t] = hok ? u0 : T(0);
         hp[t] = hok ? p0 : T(0);
-        hg[t] = hok && hleft ? g0 : T(0);
+        if (!kLean || t == 0) load_bonds(t);
+        if constexpr (!kLean) {
+#pragma unroll
+            for (int sg = 0; sg < SEG; ++sg) ro[t][sg] = row_words(t, sg);
+            co[t] = col_words(t);
+        }
     }
     LoopState L;
     const bool admitted = loop_begin(sh, L, s, r, lb, grid);
@@ -475,19 +536,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
             for (int t = 0; t < TPW; ++t) {
 #pragma unroll
-                for (int sg = 0; sg < SEG; ++sg) {
+                for (int sg = 0; !kLean && sg < SEG; ++sg) {
 #pragma unroll
                     for (int j = 0; j < TY; ++j) {
                         hide(gxv[t][sg][j]);
-                        hide(gyv[t][sg][j]);
+                        hide(gyv[t][sg][j + 1]);
                     }
-                    hide(gyv[t][sg][TY]);
+                    hide(gyv[t][sg][0]);
                 }
-                hide(hg[t]);
+                if constexpr (!kLean) hide(hg[t]);
                 hide_s(tx_[t]);
                 hide_s(ty_[t]);
             }
             hide(liv);
+            hide(lane);
         }
         // z' and p' of the halo
 #pragma unroll
@@ -500,13 +562,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             hz[t] = step_z(hz[t], alpha, hu[t]);
             hp[t] = step_p(hz[t], beta, hp[t]);
         }
-        double acc[kLoopRed] = {0.0, 0.0, 0.0, 0.0};
+        // the pending step, then z' and p' of the tiles: after this u is free
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-            if (t > 0) __syncthreads();            // the previous tile's LDS rows are reused
-            // the pending step, then z' and p' of the tile
+        for (int t = 0; t < TPW; ++t)
 #pragma unroll
-            for (int sg = 0; sg < SEG; ++sg) {
+            for (int sg = 0; sg < SEG; ++sg)
 #pragma unroll
                 for (int j = 0; j < TY; ++j) {
                     if (sa != 0.0) {
@@ -520,7 +580,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     const T zc = step_z(z_[t][sg][j], alpha, u_[t][sg][j]);
                     z_[t][sg][j] = zc;
                     p_[t][sg][j] = step_p(zc, beta, p_[t][sg][j]);
+                    if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
                 }
+        double acc[kLoopRed] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            if (t > 0) __syncthreads();            // the previous tile's LDS rows are reused
+            if (kLean && t > 0) load_bonds(t);
+#pragma unroll
+            for (int sg = 0; sg < SEG; ++sg) {
                 edge[0][w][sg][lane] = p_[t][sg][0];
                 edge[1][w][sg][lane] = p_[t][sg][TY - 1];
             }
@@ -568,8 +636,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     acc[2] = fma_(dq, du, acc[2]);
                     acc[3] = fma_((double)(jacobi ? d : T(1)) * dz, dz, acc[3]);
                 }
+                // a row at a time: interleaved rows would hold all their
+                // temporaries at once (four waves per SIMD hide the latency)
+                if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
             }
         }
+        if (w == 0) __builtin_amdgcn_s_waitcnt(0);   // what the last pass emptied is empty (wave 0 posts the sums)
         // u of the tiles' edges: rows as they lie, the columns gathered into
         // lanes 0 .. 2 TY - 1
 #pragma unroll
@@ -589,15 +661,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     if (cl >> 6 == sg) right = lane_at(u_[t][sg][j], cl & (kWave - 1));
                     if (((w == 0 && j == 0) || j == jb) && colx(t, sg) < nx) {
                         if (w == 0 && j == 0)
-                            Packed<T>::post(xt + kTop + kWave * sg + lane, E, tag, u_[t][sg][j]);
-                        if (j == jb) Packed<T>::post(xt + kBottom + kWave * sg + lane, E, tag, u_[t][sg][j]);
+                            Packed<T>::post(at(xt, (unsigned)(kTop + kWave * sg + lane) * 8u), E, tag, u_[t][sg][j]);
+                        if (j == jb) Packed<T>::post(at(xt, (unsigned)(kBottom + kWave * sg + lane) * 8u), E, tag, u_[t][sg][j]);
                     }
                 }
                 if (lane == j) cv = left;
                 if (lane == TY + j) cv = right;
             }
             if (lane < 2 * TY && rowy(t, lane < TY ? lane : lane - TY) < ny)
-                Packed<T>::post(xt + (lane < TY ? kLeft + lane : kRight + lane - TY) + w * TY, E, tag, cv);
+                Packed<T>::post(at(xt, (unsigned)((lane < TY ? kLeft + lane : kRight + lane - TY) + w * TY) * 8u), E, tag, cv);
         }
         post_sums(sh, acc, r, it, lb, grid);
         // u of the halo and the images, from their owners (before the sums,
@@ -608,19 +680,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             missing = false;
 #pragma unroll
             for (int t = 0; t < TPW; ++t) {
-                const int yh = halo_y(t), hx = halo_x(t);
-                // the neighbour above shows its last row, the one below its first
-                const int ey = w == 0 ? (ty_[t] > 0 ? ty_[t] : nty) - 1 : (ty_[t] + 1 < nty ? ty_[t] + 1 : 0);
 #pragma unroll
                 for (int sg = 0; sg < SEG; ++sg) {
-                    if (yh >= 0 && colx(t, sg) < nx)
-                        ew[t][sg].look(xb + (size_t)(ey * ntx + tx_[t]) * EW + (w == 0 ? kBottom : kTop) + kWave * sg + lane, E);
+                    if constexpr (kLean) ro[t][sg] = row_words(t, sg);
+                    if (ro[t][sg] != kNone) ew[t][sg].look(at(xb, ro[t][sg]), E);
                     else ew[t][sg].zero(tag);
                 }
-                if (hx >= 0) {
-                    const int ex = hleft ? (tx_[t] > 0 ? tx_[t] : ntx) - 1 : (tx_[t] + 1 < ntx ? tx_[t] + 1 : 0);
-                    hw[t].look(xb + (size_t)(ty_[t] * ntx + ex) * EW + (hleft ? kRight : kLeft) + w * TY + hrow, E);
-                } else hw[t].zero(tag);
+                if constexpr (kLean) co[t] = col_words(t);
+                if (co[t] != kNone) hw[t].look(at(xb, co[t]), E);
+                else hw[t].zero(tag);
             }
 #pragma unroll
             for (int t = 0; t < TPW; ++t) {
@@ -652,6 +720,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             }
             hu[t] = hw[t].value();
         }
+        if constexpr (kLean) load_bonds(0);        // the next pass's, while this one waits
         on = loop_turn(sh, L, r, it, lb, grid, spin);
         if (__any(!spin.ok)) return;               // a wait gave up: the host fails the context
     }
@@ -668,14 +737,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             for (int j = 0; j < TY; ++j)
                 if (colx(t, sg) < nx && rowy(t, j) < ny) {
                     const int i = rowy(t, j) * nx + colx(t, sg);
-                    stg(a.dst.z + i, z_[t][sg][j]);
-                    stg(a.dst.u + i, u_[t][sg][j]);
+                    sti(a.dst.z, i, z_[t][sg][j]);
+                    sti(a.dst.u, i, u_[t][sg][j]);
                     if (!admitted) continue;
-                    stg(pd + i, p_[t][sg][j]);
+                    sti(pd, i, p_[t][sg][j]);
                     double v;
                     if constexpr (kFieldLds) v = fl[(t * SEG + sg) * TY + j][threadIdx.x];
                     else v = Pv[t][sg][j];
-                    stg(P + i, v);
+                    sti(P, i, v);
                 }
     if (admitted && lb == 0 && threadIdx.x < kScalWords)   // wave 0, which ran the last step on this copy
         reinterpret_cast<u64 *>(s)[threadIdx.x] = reinterpret_cast<const volatile u64 *>(&sh.sl[0])[threadIdx.x];
