@@ -222,6 +222,17 @@ __device__ __forceinline__ T stencil2d(bool left, T gxl, T dl, T gxr, T dr, T gy
     return fma_(gyr, da, q);
 }
 
+// In 3D: the left x bond's product first in FP64, the right one's in FP32.
+template <typename T>
+__device__ __forceinline__ T stencil3d(T gxl, T dl, T gxr, T dr, T gyl, T db, T gyr, T da, T gzl, T dn, T gzr, T du)
+{
+    T q = sizeof(T) == 8 ? fma_(gxr, dr, gxl * dl) : fma_(gxl, dl, gxr * dr);
+    q = fma_(gyl, db, q);
+    q = fma_(gyr, da, q);
+    q = fma_(gzl, dn, q);
+    return fma_(gzr, du, q);
+}
+
 // Scalar update after a CG pass. t = (p.q, z.q, q.D^-1 q, r.z, 0).
 __device__ inline void step_after_cg(Scalars *s, const double *t)
 {

@@ -691,7 +691,7 @@ __device__ __forceinline__ void cg3d_tile(const PassArgs<T> &a, double *__restri
         G.xh = xhok ? xh : T(0);           // no bond left of x = 0
         G.yh = yhok ? yh : T(0);           // no bond below y = 0
     };
-    auto pprime = [&](T z, T u, T p) { return (z - alpha * u) + beta * p; };
+    auto pprime = [&](T z, T u, T p) { return step_p(step_z(z, alpha, u), beta, p); };
     // face planes of the flow axis (z = 0 and z = nz - 1 when the flow is along z)
     const int ax = a.axis;
 
@@ -714,8 +714,8 @@ __device__ __forceinline__ void cg3d_tile(const PassArgs<T> &a, double *__restri
 #pragma unroll
         for (int j = 0; j < kRows; ++j) {
             const bool ok = rok[j];
-            const T z_ = R.z[j] - alpha * R.u[j];
-            pc[j] = lok[j] ? z_ + beta * R.p[j] : T(0);
+            const T z_ = step_z(R.z[j], alpha, R.u[j]);
+            pc[j] = lok[j] ? step_p(z_, beta, R.p[j]) : T(0);
             zvc[j] = ok ? z_ : T(0);
             if (ok) {
                 const int64_t i = rowoff[j] + (int64_t)z0 * sz;
@@ -737,8 +737,8 @@ __device__ __forceinline__ void cg3d_tile(const PassArgs<T> &a, double *__restri
 #pragma unroll
         for (int j = 0; j < kRows; ++j) {
             const bool ok = rok[j] && nlat;
-            const T z_ = R.z[j] - alpha * R.u[j];
-            pn[j] = (lok[j] && nheld) ? z_ + beta * R.p[j] : T(0);
+            const T z_ = step_z(R.z[j], alpha, R.u[j]);
+            pn[j] = (lok[j] && nheld) ? step_p(z_, beta, R.p[j]) : T(0);
             zvn[j] = ok ? z_ : T(0);
             if (ok && nin) {
                 const int64_t i = rowoff[j] + (int64_t)zn * sz;
@@ -762,9 +762,9 @@ __device__ __forceinline__ void cg3d_tile(const PassArgs<T> &a, double *__restri
             if (lane == 0) gxl = gxh;
             const T gyl = j == 0 ? Gc.yh : Gc.y[j - 1];
             const T p0 = pc[j];
-            T qv = gxl * (p0 - lp[b][ly][lane]) + Gc.x[j] * (p0 - lp[b][ly][lane + 2]) +
-                   gyl * (p0 - lp[b][ly - 1][1 + lane]) + Gc.y[j] * (p0 - lp[b][ly + 1][1 + lane]) +
-                   gzm[j] * (p0 - pm[j]) + Gc.z[j] * (p0 - pn[j]);
+            T qv = stencil3d(gxl, p0 - lp[b][ly][lane], Gc.x[j], p0 - lp[b][ly][lane + 2], gyl,
+                             p0 - lp[b][ly - 1][1 + lane], Gc.y[j], p0 - lp[b][ly + 1][1 + lane], gzm[j], p0 - pm[j],
+                             Gc.z[j], p0 - pn[j]);
             const T d = diag_sum(gxl, Gc.x[j], gyl, Gc.y[j], gzm[j], Gc.z[j]);
             const int yy = yw + j;
             const bool face = ax == 0 ? (x == 0 || x == nx - 1)

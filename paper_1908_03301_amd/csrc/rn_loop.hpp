@@ -750,6 +750,364 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         reinterpret_cast<u64 *>(s)[threadIdx.x] = reinterpret_cast<const volatile u64 *>(&sh.sl[0])[threadIdx.x];
 }
 
+// ---------------------------------------------------------------- 3D
+// The tile of pass3d_kernel (64 x 16 x TZ nodes, a thread holds kRows rows of
+// TZ planes), all planes at once: p' of the tile and its halo ring sits in
+// LDS, one barrier per pass. The FP64 field is in LDS too. A thread keeps z
+// and p of the nodes below and above its columns and of one ring node per
+// plane. Two waves per SIMD, so 512 workgroups fit. Bonds stay in registers
+// except with four FP64 planes, where they come from memory in every pass.
+// Exchange words of a tile: lowest plane, highest plane; per plane the first
+// row, last row, first column, last column.
+constexpr int face_words3d(int tz) { return 2 * kTY * kTX + tz * 2 * (kTX + kTY); }
+
+template <typename T, int TZ>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void loop3d_kernel(
+    const PassArgs<T> *__restrict__ tab, Scalars *scal, int parity, int slot, LoopArgs r)
+{
+    constexpr int R = kRows, NW = kBlock / kWave;
+    constexpr int E = face_words3d(TZ), EW = E * (int)(sizeof(T) / 4);
+    constexpr int kLow = 0, kHigh = kTY * kTX, kFirst = 2 * kTY * kTX, kLast = kFirst + TZ * kTX,
+                  kLeft = kLast + TZ * kTX, kRight = kLeft + TZ * kTY;
+    constexpr bool kStream = TZ * (int)sizeof(T) > 16;     // bonds from memory
+    __shared__ T lp[TZ][kTY + 2][kTX + 2];
+    __shared__ double fl[TZ * R][kBlock];
+    __shared__ LoopShared sh;
+    const PassArgs<T> &a = tab[2 * slot + parity];
+    Scalars *s = scal + slot;
+    if (blockIdx.x == 0 && threadIdx.x < 2) r.gate_clear[threadIdx.x] = 0u;
+    if (s->mode != MODE_CG) return;
+    int lane = threadIdx.x & (kWave - 1);
+    const int w = rfl((int)threadIdx.x / kWave);
+    const int lb = (int)blockIdx.x, grid = a.grid, tile = xcd_remap(lb, grid);
+    const int nx = a.nx, ny = a.ny, nz = a.nz, ntx = a.ntx, nty = a.nty, ntz = a.ntz, wrap = a.wrap, ax = a.axis;
+    const int sz = nx * ny;
+    const bool wx = wrap & 1, wy = (wrap >> 1) & 1, wz = (wrap >> 2) & 1;
+    const bool jacobi = a.jacobi != 0, has = tile < a.ntiles;
+    const Step<T> k0 = make_step(a, s);
+    const int64_t passes0 = s->passes;
+    double *__restrict__ P = a.P[s->refreshes & 1];
+    const int tx = has ? tile % ntx : 0, ty = has ? (tile / ntx) % nty : 0, tz = has ? tile / (ntx * nty) : 0;
+    const int x0 = tx * kTX, y0 = ty * kTY, z0 = tz * TZ, yw = y0 + w * R;
+    const int cnt = has ? min(TZ, nz - z0) : 0;             // planes of this tile
+    // plane a lane, row slot or z step holds: its own inside the lattice, the
+    // opposite edge's just past a periodic one, else -1 (as in cg3d_tile)
+    auto colm = [&](int v) { return v >= 0 && v < nx ? v : (wx && v == nx ? 0 : (wx && v == -1 ? nx - 1 : -1)); };
+    auto rowm = [&](int v) { return v >= 0 && v < ny ? v : (wy && v == ny ? 0 : (wy && v == -1 ? ny - 1 : -1)); };
+    auto plm = [&](int v) { return v >= 0 && v < nz ? v : (wz && v == nz ? 0 : (wz && v == -1 ? nz - 1 : -1)); };
+    // this thread's ring node: wave 0 row y0-1, wave 1 row y0+16, wave 2 lanes
+    // 0..15 column x0-1, lanes 16..31 column x0+64 (rows y0..y0+15); the
+    // corners are not needed
+    int hx = -1, hy = -1, hrow = -1, hcol = 0;
+    unsigned hword = 0;                                     // its word in plane 0 (value index)
+    int hstep = 0;                                          // words from plane to plane
+    if (has) {
+        int q = tile;                                       // tile that owns it
+        if (w == 0) {
+            hrow = 0;
+            hcol = 1 + lane;
+            hx = x0 + lane < nx ? x0 + lane : -1;
+            hy = rowm(y0 - 1);
+            q = tile + ((ty > 0 ? ty : nty) - 1 - ty) * ntx;
+            hword = kLast + lane;
+            hstep = kTX;
+        } else if (w == 1) {
+            hrow = kTY + 1;
+            hcol = 1 + lane;
+            hx = x0 + lane < nx ? x0 + lane : -1;
+            hy = rowm(y0 + kTY);
+            q = tile + ((ty + 1 < nty ? ty + 1 : 0) - ty) * ntx;
+            hword = kFirst + lane;
+            hstep = kTX;
+        } else if (w == 2 && lane < 2 * kTY) {
+            const bool left = lane < kTY;
+            const int row = left ? lane : lane - kTY;
+            hrow = 1 + row;
+            hcol = left ? 0 : kTX + 1;
+            hx = colm(left ? x0 - 1 : x0 + kTX);
+            hy = y0 + row < ny ? y0 + row : -1;
+            q = left ? tile + (tx > 0 ? tx : ntx) - 1 - tx : tile + (tx + 1 < ntx ? tx + 1 : 0) - tx;
+            hword = (left ? kRight : kLeft) + row;
+            hstep = kTY;
+        }
+        hword += (unsigned)q * EW;
+    }
+    const bool hok = hx >= 0 && hy >= 0;
+    const int hoff = hok ? hx + nx * hy : 0;
+    // the tiles below and above (the opposite end's when z wraps)
+    const bool lowok = has && plm(z0 - 1) >= 0, higok = has && plm(z0 + cnt) >= 0;
+    const int zlow = lowok ? plm(z0 - 1) : 0, zhig = higok ? plm(z0 + cnt) : 0;
+    const int qlow = tile + ((tz > 0 ? tz : ntz) - 1 - tz) * ntx * nty,
+              qhig = tile + ((tz + 1 < ntz ? tz + 1 : 0) - tz) * ntx * nty;
+
+    // ---- state of the tile
+    T z_[TZ][R], u_[TZ][R], p_[TZ][R], gx[TZ][R], gy[TZ][R], gz[TZ][R], gzl[R], gxh[TZ], gyh[TZ];
+    T lz[R], lu[R], lq[R], gz_[R], gu[R], gq[R];            // z, u, p below and above the columns
+    T hz[TZ], hu[TZ], hp[TZ];                               // ... of the ring nodes
+    unsigned own = 0, liv = 0;                              // bits row: lattice nodes; bits (plane, row): not on a face
+    const int xm = colm(x0 + lane);
+    const bool xok = has && x0 + lane < nx;
+    auto row_off = [&](int j) {                             // clamped x + nx y of row j
+        const int ym = rowm(yw + j);
+        return (xm >= 0 ? xm : nx - 1) + nx * (ym >= 0 ? ym : ny - 1);
+    };
+    auto held = [&](int j) { return has && xm >= 0 && rowm(yw + j) >= 0; };
+    auto load_bonds = [&](int q) {                          // of plane q: right, upper, next; left of the tile, below the wave
+        const int zo = min(z0 + q, nz - 1) * sz;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = row_off(j) + zo;
+            gx[q][j] = ldi(a.gT[0], i);
+            gy[q][j] = ldi(a.gT[1], i);
+            gz[q][j] = ldi(a.gT[2], i);
+        }
+        const int xb = colm(x0 - 1), yb = rowm(yw - 1);
+        const bool xhok = lane < R && xb >= 0 && yw + lane < ny, yhok = xm >= 0 && yb >= 0;
+        const T xh = ldi(a.gT[0], zo + (xhok ? xb + nx * (yw + lane) : 0)),
+                yh = ldi(a.gT[1], zo + (yhok ? xm + nx * yb : 0));
+        gxh[q] = xhok ? xh : T(0);
+        gyh[q] = yhok ? yh : T(0);
+    };
+    auto load_below = [&] {                                 // bonds from the plane below
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const T g = ldi(a.gT[2], row_off(j) + zlow * sz);
+            gzl[j] = lowok && held(j) ? g : T(0);
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+        if (xok && yw + j < ny) own |= 1u << j;
+#pragma unroll
+    for (int q = 0; q < TZ; ++q) {
+        const int zo = min(z0 + q, nz - 1) * sz;
+        const bool in = q < cnt;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = row_off(j) + zo, x = x0 + lane, y = yw + j, z = z0 + q;
+            const bool ok = in && held(j);
+            const T zv = ldi(a.src.z, i), uv = ldi(a.src.u, i), pv = ldi(k0.p1, i);
+            double v = ldi((const double *)P, i);
+            if (k0.sa3 != 0.0 || k0.sa4 != 0.0)
+                v = with_steps(v, k0.sa4, (double)ldi(k0.p4, i), k0.sa3, (double)ldi(k0.p3, i));
+            if (k0.sa2 != 0.0) v = with_steps(v, k0.sa2, (double)ldi(k0.p2, i), 0.0, 0.0);
+            z_[q][j] = ok ? zv : T(0);
+            u_[q][j] = ok ? uv : T(0);
+            p_[q][j] = ok ? pv : T(0);
+            fl[q * R + j][threadIdx.x] = v;
+            const bool face = ax == 0 ? (x == 0 || x == nx - 1) : (ax == 1 ? (y == 0 || y == ny - 1) : (z == 0 || z == nz - 1));
+            if (in && (own >> j & 1u) && !face) liv |= 1u << (q * R + j);
+        }
+        if (!kStream || q == 0) load_bonds(q);
+        const int i = hoff + zo;
+        const T zv = ldi(a.src.z, i), uv = ldi(a.src.u, i), pv = ldi(k0.p1, i);
+        hz[q] = hok && in ? zv : T(0);
+        hu[q] = hok && in ? uv : T(0);
+        hp[q] = hok && in ? pv : T(0);
+    }
+    load_below();
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int il = row_off(j) + zlow * sz, ig = row_off(j) + zhig * sz;
+        const bool ok = own >> j & 1u;
+        const T z1 = ldi(a.src.z, il), u1 = ldi(a.src.u, il), p1 = ldi(k0.p1, il);
+        const T z2 = ldi(a.src.z, ig), u2 = ldi(a.src.u, ig), p2 = ldi(k0.p1, ig);
+        lz[j] = ok && lowok ? z1 : T(0);
+        lu[j] = ok && lowok ? u1 : T(0);
+        lq[j] = ok && lowok ? p1 : T(0);
+        gz_[j] = ok && higok ? z2 : T(0);
+        gu[j] = ok && higok ? u2 : T(0);
+        gq[j] = ok && higok ? p2 : T(0);
+    }
+    LoopState L;
+    const bool admitted = loop_begin(sh, L, s, r, lb, grid);
+
+    int it = 0;
+    for (bool on = admitted; on; ++it) {
+        Spin spin(s);
+        const T alpha = (T)rfl(L.alpha), beta = (T)rfl(L.beta);
+        const double sa = rfl(L.sa);
+        const unsigned tag = r.tag0 + (unsigned)it;
+        u64 *xb = r.xch + (size_t)(it & 1) * r.xch_slot;
+        if constexpr (!kStream) {
+#pragma unroll
+            for (int q = 0; q < TZ; ++q) {
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    hide(gx[q][j]);
+                    hide(gy[q][j]);
+                    hide(gz[q][j]);
+                }
+                hide(gxh[q]);
+                hide(gyh[q]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) hide(gzl[j]);
+        hide(own);
+        hide(liv);
+        hide(hword);
+        hide(lane);
+        // the pending step, then z' and p' of the tile and its halo
+#pragma unroll
+        for (int q = 0; q < TZ; ++q) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (sa != 0.0) {
+                    double &f = fl[q * R + j][threadIdx.x];
+                    f = fma(sa, (double)p_[q][j], f);
+                }
+                z_[q][j] = step_z(z_[q][j], alpha, u_[q][j]);
+                p_[q][j] = step_p(z_[q][j], beta, p_[q][j]);
+                lp[q][1 + w * R + j][1 + lane] = p_[q][j];
+            }
+            hz[q] = step_z(hz[q], alpha, hu[q]);
+            hp[q] = step_p(hz[q], beta, hp[q]);
+            if (hrow >= 0) lp[q][hrow][hcol] = hp[q];
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            lz[j] = step_z(lz[j], alpha, lu[j]);
+            lq[j] = step_p(lz[j], beta, lq[j]);
+            gz_[j] = step_z(gz_[j], alpha, gu[j]);
+            gq[j] = step_p(gz_[j], beta, gq[j]);
+        }
+        __syncthreads();
+        double acc[kLoopRed] = {0.0, 0.0, 0.0, 0.0};
+        // (b) stencil
+#pragma unroll
+        for (int q = 0; q < TZ; ++q) {
+            if constexpr (kStream) {
+                if (q > 0) load_bonds(q);
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int ly = 1 + w * R + j;
+                T gxl = lane_below(gx[q][j]);
+                const T gxe = lane_bcast(gxh[q], j);
+                if (lane == 0) gxl = gxe;
+                const T gyl = j == 0 ? gyh[q] : gy[q][j > 0 ? j - 1 : 0];
+                const T gzm = q == 0 ? gzl[j] : gz[q > 0 ? q - 1 : 0][j];
+                const T p0 = p_[q][j];
+                const T pm = q == 0 ? lq[j] : p_[q > 0 ? q - 1 : 0][j];
+                const T pn = q + 1 < TZ && q + 1 < cnt ? p_[q + 1 < TZ ? q + 1 : q][j] : gq[j];   // cnt: uniform
+                T qv = stencil3d(gxl, p0 - lp[q][ly][lane], gx[q][j], p0 - lp[q][ly][lane + 2], gyl,
+                                 p0 - lp[q][ly - 1][1 + lane], gy[q][j], p0 - lp[q][ly + 1][1 + lane], gzm, p0 - pm,
+                                 gz[q][j], p0 - pn);
+                const T d = diag_sum(gxl, gx[q][j], gyl, gy[q][j], gzm, gz[q][j]);
+                const bool live = (liv & (1u << (q * R + j))) && d > T(0);
+                if (!live) qv = T(0);
+                const T uv = live ? apply_minv(qv, d, jacobi) : T(0);
+                u_[q][j] = uv;
+                const double dp = (double)p0, dq = (double)qv, du = (double)uv;
+                const double dz = live ? (double)z_[q][j] : 0.0;
+                acc[0] = fma_(dp, dq, acc[0]);
+                acc[1] = fma_(dz, dq, acc[1]);
+                acc[2] = fma_(dq, du, acc[2]);
+                acc[3] = fma_((double)(jacobi ? d : T(1)) * dz, dz, acc[3]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (w == 0) __builtin_amdgcn_s_waitcnt(0);   // what the last pass emptied is empty (wave 0 posts the sums)
+        // u of the tile's faces
+        if (has) {
+            u64 *xt = xb + (size_t)tile * EW;
+            const int jb = min(y0 + kTY, ny) - 1 - yw;       // last lattice row, if in this wave
+            const int cl = min(kTX, nx - x0) - 1;            // last lattice column of the tile
+            T cv = T(0);
+#pragma unroll
+            for (int q = 0; q < TZ; ++q) {
+                if (q >= cnt) continue;                      // uniform
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const T uv = u_[q][j];
+                    if (own >> j & 1u) {
+                        const unsigned at_ = (unsigned)((w * R + j) * kTX + lane) * 8u;
+                        if (q == 0) Packed<T>::post(at(xt + kLow, at_), E, tag, uv);
+                        if (q == cnt - 1) Packed<T>::post(at(xt + kHigh, at_), E, tag, uv);
+                        if (w == 0 && j == 0) Packed<T>::post(at(xt + kFirst + q * kTX, (unsigned)lane * 8u), E, tag, uv);
+                        if (j == jb) Packed<T>::post(at(xt + kLast + q * kTX, (unsigned)lane * 8u), E, tag, uv);
+                    }
+                    const T left = lane_bcast(uv, 0), right = lane_at(uv, cl);
+                    if (lane == q * R + j) cv = left;
+                    if (lane == 32 + q * R + j) cv = right;
+                }
+            }
+            const int e = lane & 31, row = e % R, q = e / R; // the columns, gathered into lanes 0.. and 32..
+            if (e < cnt * R && yw + row < ny)
+                Packed<T>::post(at(xt, (unsigned)((lane < 32 ? kLeft : kRight) + q * kTY + w * R + row) * 8u), E, tag, cv);
+        }
+        post_sums(sh, acc, r, it, lb, grid);
+        // u of the halo, from its owners
+        Packed<T> lw[R], gw[R], hw[TZ];
+        bool missing;
+        do {
+            missing = false;
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const unsigned at_ = (unsigned)((w * R + j) * kTX + lane) * 8u;
+                if (lowok && (own >> j & 1u)) lw[j].look(at(xb + (size_t)qlow * EW + kHigh, at_), E);
+                else lw[j].zero(tag);
+                if (higok && (own >> j & 1u)) gw[j].look(at(xb + (size_t)qhig * EW + kLow, at_), E);
+                else gw[j].zero(tag);
+            }
+#pragma unroll
+            for (int q = 0; q < TZ; ++q) {
+                if (hok && q < cnt) hw[q].look(at(xb, (hword + (unsigned)(q * hstep)) * 8u), E);
+                else hw[q].zero(tag);
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) missing |= !lw[j].here(tag) || !gw[j].here(tag);
+#pragma unroll
+            for (int q = 0; q < TZ; ++q) missing |= !hw[q].here(tag);
+        } while (missing && spin.more());
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            lu[j] = lw[j].value();
+            gu[j] = gw[j].value();
+        }
+#pragma unroll
+        for (int q = 0; q < TZ; ++q) hu[q] = hw[q].value();
+        if (wrap & 3) {                                      // uniform: images of column 0 and row 0
+#pragma unroll
+            for (int q = 0; q < TZ; ++q)
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const int x = x0 + lane, y = yw + j;
+                    const bool ix = wx && x == nx && y < ny, iy = wy && y == ny && x < nx;
+                    if (has && q < cnt && (ix || iy)) {
+                        Packed<T> v;
+                        u64 *o = ix ? xb + (size_t)(tile - tx) * EW + kLeft + q * kTY + w * R + j
+                                    : xb + (size_t)(tile - ty * ntx) * EW + kFirst + q * kTX + lane;
+                        do v.look(o, E);
+                        while (!v.here(tag) && spin.more());
+                        u_[q][j] = v.value();
+                    }
+                }
+        }
+        if constexpr (kStream) load_bonds(0);                // the next pass's, while this one waits
+        on = loop_turn(sh, L, r, it, lb, grid, spin);
+        if (__any(!spin.ok)) return;                         // a wait gave up: the host fails the context
+    }
+    // ---- the state of the last pass (see loop2d_kernel)
+    const int64_t done = passes0 + it - 1;
+    T *pd = a.pbuf[a.npbuf == 5 ? (int)(done % 5) : (int)(done % 3)];
+#pragma unroll
+    for (int q = 0; q < TZ; ++q)
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (q < cnt && (own >> j & 1u)) {
+                const int i = x0 + lane + nx * (yw + j) + (z0 + q) * sz;
+                sti(a.dst.z, i, z_[q][j]);
+                sti(a.dst.u, i, u_[q][j]);
+                if (!admitted) continue;
+                sti(pd, i, p_[q][j]);
+                sti(P, i, fl[q * R + j][threadIdx.x]);
+            }
+    if (admitted && lb == 0 && threadIdx.x < kScalWords)
+        reinterpret_cast<u64 *>(s)[threadIdx.x] = reinterpret_cast<const volatile u64 *>(&sh.sl[0])[threadIdx.x];
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
@@ -757,7 +1115,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 template <typename T>
 static const void *loop_kernel(int dim, int tpw, int tile_z)
 {
-    (void)tile_z;
+    if (dim == 3 && tile_z == 2) return reinterpret_cast<const void *>(&loop3d_kernel<T, 2>);
+    if (dim == 3 && tile_z == 4) return reinterpret_cast<const void *>(&loop3d_kernel<T, 4>);
     if (dim == 2 && tpw == 1) return reinterpret_cast<const void *>(&loop2d_kernel<T, 0, 1>);
     if (dim == 2 && tpw == 2) return reinterpret_cast<const void *>(&loop2d_kernel<T, 0, 2>);
     if (dim == -2 && tpw == 1) return reinterpret_cast<const void *>(&loop2d_kernel<T, 1, 1>);
@@ -782,8 +1141,7 @@ hipError_t loop_capacity(int dim, int tpw, int tile_z, int *cap)
 template <typename T>
 size_t loop_exchange_words(int dim, int tile_z, int ntiles)
 {
-    (void)tile_z;
-    const size_t values = dim == 2 ? edge_words2d<T, 0>() : edge_words2d<T, 1>();
+    const size_t values = dim == 3 ? face_words3d(tile_z) : dim == 2 ? edge_words2d<T, 0>() : edge_words2d<T, 1>();
     return values * (sizeof(T) / 4) * (size_t)ntiles;
 }
 

@@ -221,7 +221,7 @@ private:
     int queue_status(int rounds, hipStream_t st, std::string *err);
     char *d_gate_ = nullptr;                 // kGates gates, used in turn, each cleared kGates / 2 launches later
     unsigned long long *d_xch_ = nullptr, *d_coef_ = nullptr;   // edge values and coefficients of the loops
-    size_t xch_cap_ = 0;                     // words of d_xch_ (at most about 20 MB, freed with the engine)
+    size_t xch_cap_ = 0;                     // words of d_xch_ (at most 44 MB, freed with the engine)
     unsigned loop_tag_ = 1;                  // first pass number of the next loop
     double *d_lpart_ = nullptr;              // partial sums of a resident loop
     int gate_ = 0;

@@ -33,13 +33,19 @@ def solve(ctx, g, nx, ny, nz, precision, axis, periodic, tol):
 SIZES_2D = [(3, 3, 1), (16, 5, 1), (63, 7, 1), (64, 8, 1), (65, 9, 1), (128, 4, 1), (129, 33, 1), (250, 131, 1),
             (520, 515, 1), (1030, 700, 1), (1500, 1420, 1)]
 
+# tiles of 64 x 16 x 2 and x 4 nodes: the same edges, and a last tile with fewer planes
+SIZES_3D = [(3, 3, 3), (5, 4, 2), (64, 16, 2), (65, 17, 3), (63, 15, 5), (30, 18, 9), (130, 33, 8), (70, 66, 64),
+            (128, 120, 99)]
+
 
 @pytest.mark.parametrize("precision", [B.RN_MIXED, B.RN_FP64], ids=["mixed", "fp64"])
-@pytest.mark.parametrize("size", SIZES_2D, ids=lambda s: "x".join(map(str, s)))
-@pytest.mark.parametrize("axis,periodic", [(0, False), (0, True), (1, True)])
+@pytest.mark.parametrize("size", SIZES_2D + SIZES_3D, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("axis,periodic", [(0, False), (0, True), (1, True), (2, True)])
 def test_loop_bits(size, precision, axis, periodic, monkeypatch):
     import torch
     nx, ny, nz = size
+    if axis == 2 and nz == 1:
+        pytest.skip("2D")
     big = nx * ny * nz > 100000
     g = network(nx, ny, nz, seed=nx + 7 * ny, occupancy=0.85)
     tol = 1e-3 if big else 1e-8
