@@ -372,11 +372,12 @@ static int backbone_prepare(rn_ctx *ctx, const rn_problem *p, BackbonePrep *b)
             return fail(RN_EDEVICE);
         if (hc[1] != 0) return fail(RN_EINVAL);
     }
-    if (launch_mask(lat, gc, (int *)tr, (unsigned *)(tr + 4 * nn), b->mask, nullptr, cnt, true, st) != hipSuccess)
+    if (launch_mask(lat, gc, (int *)tr, (unsigned *)(tr + 4 * nn), b->mask, nullptr, cnt, true, st,
+                    backbone_tree(n, tr + a256(8 * nn))) != hipSuccess)
         return fail(RN_EDEVICE);
     const int n_axis = p->axis == 0 ? (int)p->nx : (p->axis == 1 ? (int)p->ny : (int)p->nz);
-    if (n_axis >= 3 && launch_backbone(lat, gc, b->mask, tr + a256(8 * nn), cnt + 2, (int *)ctx->h_small, nullptr,
-                                       st) != hipSuccess)
+    if (n_axis >= 3 && launch_backbone(lat, gc, b->mask, (const int *)tr, (unsigned *)(tr + 4 * nn),
+                                       tr + a256(8 * nn), cnt + 2, st) != hipSuccess)
         return fail(RN_EDEVICE);
     if (launch_backbone_prune(lat, gc, g, b->mask, b->uf, b->att, st) != hipSuccess) return fail(RN_EDEVICE);
     if (hipMemcpyAsync(hc, cnt, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -478,12 +479,13 @@ static int compact_solve(rn_ctx *ctx, const rn_problem *p, const rn_opts *o, rn_
             return finish(RN_EDEVICE);
         if (hc[1] != 0) return finish(RN_EINVAL);
     }
-    if (launch_mask(lat, g, (int *)tr, (unsigned *)(tr + 4 * nn), mask, Pl, cnt, o->x0 == RN_X0_LINEAR, st) !=
-        hipSuccess)
+    if (launch_mask(lat, g, (int *)tr, (unsigned *)(tr + 4 * nn), mask, Pl, cnt, o->x0 == RN_X0_LINEAR, st,
+                    backbone ? backbone_tree(n, tr + a256(8 * nn)) : nullptr) != hipSuccess)
         return finish(RN_EDEVICE);
     const int n_axis = p->axis == 0 ? (int)p->nx : (p->axis == 1 ? (int)p->ny : (int)p->nz);
     if (backbone && n_axis >= 3) {
-        if (launch_backbone(lat, g, mask, tr + a256(8 * nn), cnt + 2, (int *)ctx->h_small, nullptr, st) != hipSuccess)
+        if (launch_backbone(lat, g, mask, (const int *)tr, (unsigned *)(tr + 4 * nn), tr + a256(8 * nn), cnt + 2, st) !=
+            hipSuccess)
             return finish(RN_EDEVICE);
         if (launch_backbone_prune(lat, g, nullptr, mask, uf, att, st) != hipSuccess) return finish(RN_EDEVICE);
     }
@@ -1041,7 +1043,6 @@ int rn_build_backbone(rn_ctx *ctx, const rn_problem *p, int64_t *n_live_out, int
     if (st) return st;
     if (!p->mask_out) return RN_EINVAL;
     if (p->mem == RN_MEM_HOST && !host_values_ok(p)) return RN_EINVAL;
-    static_assert(kBackboneStage <= 64, "level offsets staged in the 32-word pinned buffer");
     const int64_t n = p->nx * p->ny * p->nz;
     if (n + 2 > (int64_t)INT32_MAX) return RN_EINVAL;
     std::lock_guard<std::mutex> lk(ctx->call_mu);
@@ -1085,11 +1086,12 @@ int rn_build_backbone(rn_ctx *ctx, const rn_problem *p, int64_t *n_live_out, int
         return done(RN_EDEVICE);
     if (hc[1] != 0) return done(RN_EINVAL);
     if (launch_mask(lat, gd, (int *)(base + off_lab), (unsigned *)(base + off_lab + 4 * nn), mask, nullptr, cnt, true,
-                    ctx->stream) != hipSuccess)
+                    ctx->stream, backbone_tree(n, base + off_bb)) != hipSuccess)
         return done(RN_EDEVICE);
     // with fewer than 3 planes on the flow axis there is no interior node
     const int n_axis = p->axis == 0 ? (int)p->nx : (p->axis == 1 ? (int)p->ny : (int)p->nz);
-    if (n_axis >= 3 && launch_backbone(lat, gd, mask, base + off_bb, cnt + 2, (int *)ctx->h_small, nullptr,
+    if (n_axis >= 3 && launch_backbone(lat, gd, mask, (const int *)(base + off_lab),
+                                       (unsigned *)(base + off_lab + 4 * nn), base + off_bb, cnt + 2,
                                        ctx->stream) != hipSuccess)
         return done(RN_EDEVICE);
     if (hipMemcpyAsync(hc, cnt, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||

@@ -7,41 +7,54 @@
 // S, the outlet face to T and an edge S-T added, it is the vertex set of the
 // biconnected component (block) that holds S-T.
 //
-// Blocks by Tarjan and Vishkin's parallel method, on a breadth-first spanning
-// tree rooted at S:
-//   1. BFS, one launch per level; new vertices are appended to one queue with
-//      one atomic per wave, so each level is a contiguous segment of it. T is
-//      S's first child; S's other children are the live nodes with a bond to
-//      the inlet face, T's children those with a bond to the outlet face that
-//      no lattice node reached first. A vertex stores the direction of its
-//      tree bond (so the second bond between two nodes of a periodic
-//      direction of extent 2 stays a separate, non-tree edge).
-//   2. Subtree sizes nd, level by level from the deepest.
-//   3. Preorder numbers pre, level by level from the root: a child of a
-//      lattice node comes after its siblings of lower direction index;
-//      S's and T's children follow their place in the queue (a scan).
-//   4. low / high: the extreme preorder numbers reachable from a subtree by
-//      one non-tree edge, level by level from the deepest.
-//   5. Tree edges (named by their child vertex) are joined in a lock-free
-//      union-find: a non-tree edge whose ends are not ancestor and
-//      descendant joins the two ends' tree edges; a tree edge (p, v) with p
-//      not the root joins p's when low(v) < pre(p) or high(v) >=
-//      pre(p) + nd(p). The classes are the blocks.
-//   6. The backbone is the set of lattice ends of the tree edges in T's class
+// Blocks by Tarjan and Vishkin's method, on whatever spanning tree the
+// connectivity pass leaves behind, numbered by an Euler tour. Nothing here
+// depends on the depth of the tree (a breadth-first tree took a launch per
+// level and phase, about 6,000 launches and 47 ms on a 2048^2 network near the
+// threshold; bytes alone would take 0.02 ms):
+//   1. Tree. The bonds whose union-find hook succeeded in the connectivity
+//      pass span every component of interior nodes; each live component adds
+//      one bond to the inlet face, and S-T joins T, a leaf. A byte per vertex
+//      holds its tree directions (bit 6: its bond to S).
+//   2. Tour. Arriving at a vertex from direction r, the tour leaves by the
+//      next tree direction after r in circular order, so an arc's successor is
+//      a look at one byte and no list is stored. One vertex in eight (picked by
+//      a hash, so that no regular tree avoids them) starts a walker at its
+//      first arc, which counts arcs until it meets the next start; pointer
+//      jumping ranks the starts (distance to the last one of the component,
+//      whose end is allotted from a counter); the walkers go again and write
+//      positions: in(v), the first arrival at v, and last(v), the last. The
+//      subtree of v is the positions in .. last. Longest walk measured: a few
+//      hundred steps, as for random starts.
+//   3. low / high: the extreme positions joined to a vertex by a non-tree edge
+//      are stored at in(v); minima and maxima over 8, 64, ... positions make
+//      the extremes over a subtree a walk up and down that hierarchy.
+//   4. Joins. Tree edges (named by their child vertex) form classes in a
+//      lock-free union-find ordered by in(): a tree edge (p, v) with p not S
+//      joins p's when low(v) < in(p) or high(v) > last(p), written straight
+//      into the parent words (tree parents come first in that order) and
+//      shortened by pointer jumping; a non-tree edge whose ends are not
+//      ancestor and descendant joins the two ends' tree edges.
+//   5. The backbone is the set of lattice ends of the tree edges in T's class
 //      (T's tree edge is S-T): bit 3 (8) of the mask.
-// Any spanning tree works for the method, so the BFS races (which parent a
-// vertex gets) change the tree but not the blocks: the mask is deterministic.
+// The races decide which tree is built, not the blocks: the mask is
+// deterministic.
 #include "rn_runtime.hpp"
 
 #include <algorithm>
-#include <vector>
 
 namespace rn {
 namespace {
 
 constexpr int kBbBlock = 256;
-constexpr int kBbGrid = 512;              // grid-stride launches over one level
-constexpr uint8_t kParS = 6, kParT = 7, kParNone = 255;
+constexpr int kDirS = 6;                  // tree direction of the bond to S
+constexpr unsigned kStart = 0x80u;        // flag of a vertex whose first arc starts a walker
+constexpr int kSpread = 8;                // vertices per walker
+constexpr int kFan = 8, kFanLevels = 11;  // the hierarchy of minima and maxima
+constexpr unsigned kNone = 0xffffffffu;
+// Positions of the tour: 0 is S (an edge to it reaches below every position),
+// T is 1, the components follow.
+constexpr unsigned kPosT = 1u, kPosFirst = 2u;
 
 struct BbGraph {
     const double *g[3];
@@ -99,239 +112,261 @@ __device__ __forceinline__ int bb_nbr(const BbGraph &G, int v, const int c[3], i
     return G.mask[j] == 3 ? j : -1;
 }
 
-// Parent vertex of v from its tree-bond direction.
-__device__ __forceinline__ int bb_parent(const BbGraph &G, int v, uint8_t pd)
+__device__ __forceinline__ unsigned load_agent(const unsigned *p)
 {
-    if (v == G.T || pd == kParS) return G.S;
-    if (pd == kParT) return G.T;
-    int c[3];
-    coords(G, v, c);
-    double gij;
-    return lat_step(G, v, c, pd, &gij);
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Append the lanes with `take` set to the queue, one atomic per wave.
-__device__ __forceinline__ void wave_append(bool take, int v, int *order, int *tail)
-{
-    const unsigned long long m = __ballot(take);
-    if (m == 0ull) return;
-    const int lane = threadIdx.x & 63;
-    const int leader = __ffsll((long long)m) - 1;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(tail, __popcll(m));
-    base = __shfl(base, leader, 64);
-    if (take) order[base + __popcll(m & ((1ull << lane) - 1ull))] = v;
-}
+// Arrays of the search, all of them for the n lattice vertices unless noted.
+struct BbWork {
+    const int *parent;                    // components of the connectivity pass
+    unsigned *flags;                      // its flags, at the components' roots; bit 2: has its bond to S
+    uint8_t *tree;                        // bit k: the bond to +k is a tree edge; later: on the backbone
+    uint8_t *adj;                         // tree directions, kDirS, kStart; 0 off the live set
+    unsigned *in, *last;                  // n + 2 (T at n + 1)
+    int *uf;                              // n + 2
+    unsigned long long *jump[2];          // per walker: start it leads to (low half), arcs to there
+    unsigned *len, *end;                  // per walker: its arcs; at the last start of a component: end position
+    unsigned *heads;                      // the vertices joined to S by a tree edge
+    int *first;                           // per walker of a vertex group: its vertex or -1
+    unsigned *lo[kFanLevels], *hi[kFanLevels];
+    unsigned *counter;                    // [0] heads, [1] positions
+    int groups;                           // groups of kSpread vertices
+};
 
-__global__ void bb_init(int *lev, uint8_t *pdir, int *nd, int *pre, int *uf, uint8_t *on, int V, int S, int T,
-                        int *order, int *lev_off, int *tail)
+// 1. Tree directions of every live vertex; the first vertex of a component to
+// ask gets its tree bond to S.
+__global__ void bb_tree(BbGraph G, BbWork W)
 {
+    const int V = G.n + 2;
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < V; v += gridDim.x * blockDim.x) {
-        lev[v] = v == S ? 0 : (v == T ? 1 : -1);
-        pdir[v] = v == T ? kParS : kParNone;
-        nd[v] = 1;
-        pre[v] = 0;                     // S keeps 0, the root's number
-        uf[v] = v;
-        on[v] = 0;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        order[0] = S;
-        order[1] = T;
-        lev_off[0] = 0;
-        lev_off[1] = 1;
-        *tail = 2;
-    }
-}
-
-// The live nodes next to face `which` (1 inlet, 2 outlet) with a bond to it
-// join level l as children of S (which = 1) or T (2), unless already seen.
-__global__ void bb_face_children(BbGraph G, int which, int l, int *lev, uint8_t *pdir, int *order, int *tail)
-{
-    const int na = G.axis == 0 ? G.nx : (G.axis == 1 ? G.ny : G.nz);
-    const int ca = which == 1 ? 1 : na - 2;
-    const int m = G.axis == 0 ? G.ny * G.nz : (G.axis == 1 ? G.nx * G.nz : G.nx * G.ny);   // nodes of the plane
-    const int rounds = (m + (int)(gridDim.x * blockDim.x) - 1) / (int)(gridDim.x * blockDim.x);
-    for (int r = 0; r < rounds; ++r) {
-        const int q = r * (int)(gridDim.x * blockDim.x) + blockIdx.x * blockDim.x + threadIdx.x;
-        bool take = false;
-        int v = 0;
-        if (q < m) {
-            int c[3];
-            if (G.axis == 0) { c[0] = ca; c[1] = q % G.ny; c[2] = q / G.ny; }
-            else if (G.axis == 1) { c[0] = q % G.nx; c[1] = ca; c[2] = q / G.nx; }
-            else { c[0] = q % G.nx; c[1] = q / G.nx; c[2] = ca; }
-            v = c[0] + G.nx * (c[1] + G.ny * c[2]);
-            if (G.mask[v] == 3) {
-                const int e = 2 * G.axis + (which == 1 ? 0 : 1);
-                if (bb_nbr(G, v, c, e) == (which == 1 ? G.S : G.T) && atomicCAS(&lev[v], -1, l) == -1) {
-                    pdir[v] = which == 1 ? kParS : kParT;
-                    take = true;
-                }
-            }
-        }
-        wave_append(take, v, order, tail);
-    }
-}
-
-// Expand level l: every lattice vertex of it claims its unseen neighbours for l + 1.
-__global__ void bb_expand(BbGraph G, int l, const int *lev_off, int *lev, uint8_t *pdir, int *order, int *tail)
-{
-    const int b = lev_off[l], e = lev_off[l + 1];
-    const int stride = (int)(gridDim.x * blockDim.x);
-    const int rounds = (e - b + stride - 1) / stride;
-    for (int r = 0; r < rounds; ++r) {
-        const int q = b + r * stride + blockIdx.x * blockDim.x + threadIdx.x;
-        const int v = q < e ? order[q] : G.S;
-        int c[3] = {0, 0, 0};
-        const bool lat = v < G.n;
-        if (lat) coords(G, v, c);
-        for (int d = 0; d < 6; ++d) {
-            bool take = false;
-            int w = -1;
-            if (lat) {
-                w = bb_nbr(G, v, c, d);
-                if (w >= 0 && w < G.n && atomicCAS(&lev[w], -1, l + 1) == -1) {
-                    pdir[w] = (uint8_t)(d ^ 1);
-                    take = true;
-                }
-            }
-            wave_append(take, w, order, tail);
-        }
-    }
-}
-
-__global__ void bb_snap(int *lev_off, const int *tail, int l)
-{
-    if (threadIdx.x == 0) lev_off[l + 2] = *tail;
-}
-
-// Subtree sizes: the vertices of level l add theirs to their parents.
-__global__ void bb_sizes(BbGraph G, int b, int e, const int *order, const uint8_t *pdir, int *nd)
-{
-    for (int q = b + blockIdx.x * blockDim.x + threadIdx.x; q < e; q += gridDim.x * blockDim.x) {
-        const int v = order[q];
-        const int p = bb_parent(G, v, pdir[v]);
-        if (p != G.S) atomicAdd(&nd[p], nd[v]);
-    }
-}
-
-// Preorder numbers of the children of S (the level-1 segment, all of them) or
-// of T (the entries of the level-2 segment whose parent is T): base + the
-// sizes of the earlier children, by one workgroup scanning the segment.
-__global__ void bb_scan_children(int b, int e, const int *order, const uint8_t *pdir, uint8_t want, int base,
-                                 const int *nd, int *pre)
-{
-    constexpr int kPer = 8;
-    __shared__ int wsum[kBbBlock / 64];
-    __shared__ int carry_s;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (threadIdx.x == 0) carry_s = 0;
-    __syncthreads();
-    for (int c0 = b; c0 < e; c0 += kBbBlock * kPer) {
-        int val[kPer], tot = 0;
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int q = c0 + threadIdx.x * kPer + k;
-            int v = 0;
-            if (q < e) {
-                const int u = order[q];
-                v = pdir[u] == want ? nd[u] : 0;
-            }
-            val[k] = v;
-            tot += v;
-        }
-        // inclusive scan of the per-thread totals within the wave, then across waves
-        int inc = tot;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += t;
-        }
-        if (lane == 63) wsum[w] = inc;
-        __syncthreads();
-        int before = carry_s;
-        for (int ww = 0; ww < w; ++ww) before += wsum[ww];
-        int run = before + inc - tot;
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int q = c0 + threadIdx.x * kPer + k;
-            if (q < e) {
-                const int u = order[q];
-                if (pdir[u] == want) pre[u] = base + run;
-            }
-            run += val[k];
-        }
-        __syncthreads();
-        if (threadIdx.x == kBbBlock - 1) carry_s = run;
-        __syncthreads();
-    }
-}
-
-// Preorder numbers of level l's vertices whose parent is a lattice node:
-// pre(parent) + 1 + the sizes of the parent's children of lower direction.
-__global__ void bb_preorder(BbGraph G, int b, int e, const int *order, const uint8_t *pdir, const int *nd,
-                            int *pre)
-{
-    for (int q = b + blockIdx.x * blockDim.x + threadIdx.x; q < e; q += gridDim.x * blockDim.x) {
-        const int v = order[q];
-        const uint8_t pd = pdir[v];
-        if (pd >= kParS) continue;
-        int c[3];
-        coords(G, v, c);
-        double gij;
-        const int p = lat_step(G, v, c, pd, &gij);
-        int cp[3];
-        coords(G, p, cp);
-        const int ev = pd ^ 1;                   // direction from p to v
-        int s = 0;
-        for (int d = 0; d < ev; ++d) {
-            const int u = bb_nbr(G, p, cp, d);
-            if (u >= 0 && u < G.n && pdir[u] == (uint8_t)(d ^ 1)) s += nd[u];
-        }
-        pre[v] = pre[p] + 1 + s;
-    }
-}
-
-// Whether the edge from v in direction d to w is a tree edge.
-__device__ __forceinline__ bool is_tree(const BbGraph &G, int w, uint8_t pv, const uint8_t *pdir, int d)
-{
-    if (w == G.S) return pv == kParS;
-    if (w == G.T) return pv == kParT;
-    return pv == (uint8_t)d || pdir[w] == (uint8_t)(d ^ 1);
-}
-
-// low / high of every visited vertex from its own non-tree edges. T's are
-// left out: T's tree edge goes to the root, where no join looks at them.
-__global__ void bb_lohi_init(BbGraph G, int b, int e, const int *order, const uint8_t *pdir, const int *pre,
-                             int *lo, int *hi)
-{
-    for (int q = b + blockIdx.x * blockDim.x + threadIdx.x; q < e; q += gridDim.x * blockDim.x) {
-        const int v = order[q];
-        int l = pre[v], h = pre[v];
-        if (v < G.n) {
+        W.uf[v] = v;
+        W.in[v] = v == G.T ? kPosT : kNone;
+        W.last[v] = v == G.T ? kPosT : 0u;
+        if (v >= G.n) continue;
+        unsigned bits = 0u;
+        if (G.mask[v] == 3) {
             int c[3];
             coords(G, v, c);
-            const uint8_t pv = pdir[v];
-            for (int d = 0; d < 2 * G.dim; ++d) {
-                const int w = bb_nbr(G, v, c, d);
-                if (w < 0 || is_tree(G, w, pv, pdir, d)) continue;
-                l = min(l, pre[w]);
-                h = max(h, pre[w]);
+            for (int e = 0; e < 2 * G.dim; ++e) {
+                double gij = 0.0;
+                const int j = (e & 1) ? v : lat_step(G, v, c, e, &gij);
+                if (j >= 0 && (W.tree[j] >> (e >> 1) & 1u)) bits |= 1u << e;
+            }
+            if (c[G.axis] == 1 && bb_nbr(G, v, c, 2 * G.axis) == G.S) {
+                int r = v;
+                while (true) {                       // the connectivity pass is over: plain loads
+                    const int q = W.parent[r];
+                    if (q == r) break;
+                    r = q;
+                }
+                if (!(atomicOr(W.flags + r, 4u) & 4u)) {
+                    bits |= 1u << kDirS;
+                    W.heads[atomicAdd(W.counter, 1u)] = (unsigned)v;
+                }
             }
         }
-        lo[v] = l;
-        hi[v] = h;
+        W.adj[v] = (uint8_t)bits;
     }
 }
 
-__global__ void bb_lohi_up(BbGraph G, int b, int e, const int *order, const uint8_t *pdir, int *lo, int *hi)
+// The vertex of each group that starts a walker: the first live one from a
+// hashed place on whose first tree direction is a lattice bond (an arrival
+// from S is a head's).
+__global__ void bb_starts(BbGraph G, BbWork W)
 {
-    for (int q = b + blockIdx.x * blockDim.x + threadIdx.x; q < e; q += gridDim.x * blockDim.x) {
-        const int v = order[q];
-        const int p = bb_parent(G, v, pdir[v]);
-        if (p == G.S) continue;
-        atomicMin(&lo[p], lo[v]);
-        atomicMax(&hi[p], hi[v]);
+    for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < W.groups; g += gridDim.x * blockDim.x) {
+        unsigned h = (unsigned)g * 0x9e3779b1u;
+        h ^= h >> 15;
+        h *= 0x85ebca6bu;
+        h ^= h >> 13;
+        int pick = -1;
+        for (int k = 0; k < kSpread && pick < 0; ++k) {
+            const int v = g * kSpread + (int)((h + (unsigned)k) % kSpread);
+            if (v < G.n && (W.adj[v] & 0x3fu)) pick = v;
+        }
+        W.first[g] = pick;
+        if (pick >= 0) W.adj[pick] = (uint8_t)(W.adj[pick] | kStart);
     }
+}
+
+// One step of the tour: from an arrival at v by direction r (bits: v's byte)
+// to the next arrival. False when the tour leaves to S.
+__device__ __forceinline__ bool tour_step(const BbGraph &G, const uint8_t *adj, int &v, int &r, unsigned &bits)
+{
+    const unsigned dirs = bits & 0x7fu;
+    const unsigned above = dirs & ~((2u << r) - 1u);
+    const int d = __ffs((int)(above ? above : dirs)) - 1;
+    if (d == kDirS) return false;
+    const int k = d >> 1;
+    const int n[3] = {G.nx, G.ny, G.nz};
+    const int st = k == 0 ? 1 : (k == 1 ? G.nx : G.nx * G.ny);
+    int step = (d & 1) ? st : -st;
+    if (G.wrap >> k & 1) {
+        int c[3];
+        coords(G, v, c);
+        if ((d & 1) && c[k] + 1 == n[k]) step = -(n[k] - 1) * st;
+        else if (!(d & 1) && c[k] == 0) step = (n[k] - 1) * st;
+    }
+    v += step;
+    r = d ^ 1;
+    bits = adj[v];
+    return true;
+}
+
+__device__ __forceinline__ bool is_start(unsigned bits, int r)
+{
+    return (bits & kStart) && r == __ffs((int)(bits & 0x7fu)) - 1;
+}
+
+// Where walker i starts: false for a group without one.
+__device__ __forceinline__ bool walker(const BbWork &W, int i, int &v, int &r, unsigned &bits)
+{
+    v = i < W.groups ? W.first[i] : (int)W.heads[i - W.groups];
+    if (v < 0) return false;
+    bits = W.adj[v];
+    r = i < W.groups ? __ffs((int)(bits & 0x7fu)) - 1 : kDirS;
+    return true;
+}
+
+// 2. Walk from every start to the next: its number of arrivals and where it leads.
+__global__ void bb_walk(BbGraph G, BbWork W)
+{
+    const int total = W.groups + (int)W.counter[0];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        int v, r;
+        unsigned bits, len = 0u, to = (unsigned)i;
+        if (walker(W, i, v, r, bits)) {
+            len = 1u;
+            // (a walk visits an arc at most once: the bound is never reached)
+            while (len < 2u * (unsigned)G.n + 2u && tour_step(G, W.adj, v, r, bits)) {
+                if (is_start(bits, r)) {
+                    to = (unsigned)(v / kSpread);
+                    break;
+                }
+                ++len;
+            }
+        }
+        W.len[i] = len;
+        // the last start of a component leads to itself, at distance 0
+        W.jump[0][i] = to == (unsigned)i ? (unsigned long long)to : ((unsigned long long)len << 32) | to;
+    }
+}
+
+__global__ void bb_jump(BbWork W, int from)
+{
+    const int total = W.groups + (int)W.counter[0];
+    const unsigned long long *src = W.jump[from];
+    unsigned long long *dst = W.jump[from ^ 1];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        const unsigned long long a = src[i], b = src[(unsigned)a];
+        dst[i] = (((a >> 32) + (b >> 32)) << 32) | (unsigned)b;
+    }
+}
+
+// Every component's range of positions, noted at its last start.
+__global__ void bb_ranges(BbWork W, int from)
+{
+    const int heads = (int)W.counter[0];
+    for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < heads; h += gridDim.x * blockDim.x) {
+        const unsigned long long a = W.jump[from][W.groups + h];
+        const unsigned t = (unsigned)a, size = (unsigned)(a >> 32) + W.len[t];
+        W.end[t] = kPosFirst + atomicAdd(W.counter + 1, size) + size;
+    }
+}
+
+// Walk again, writing the positions. A vertex of one tree direction is
+// arrived at once.
+__global__ void bb_number(BbGraph G, BbWork W, int from)
+{
+    const int total = W.groups + (int)W.counter[0];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        int v, r;
+        unsigned bits;
+        if (!walker(W, i, v, r, bits)) continue;
+        const unsigned long long a = W.jump[from][i];
+        const unsigned t = (unsigned)a;
+        unsigned pos = W.end[t] - W.len[t] - (unsigned)(a >> 32);
+        for (unsigned k = W.len[i]; k > 0u; --k, ++pos) {
+            if (__popc(bits & 0x7fu) == 1) {
+                W.in[v] = pos;
+                W.last[v] = pos;
+            } else {
+                atomicMin(W.in + v, pos);
+                atomicMax(W.last + v, pos);
+            }
+            if (k > 1u) tour_step(G, W.adj, v, r, bits);
+        }
+    }
+}
+
+// 3. Identities at the positions that are no first arrival.
+__global__ void bb_clear(BbWork W)
+{
+    const unsigned m = kPosFirst + W.counter[1];
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
+        W.lo[0][i] = kNone;
+        W.hi[0][i] = 0u;
+    }
+}
+
+// Whether v's edge in direction e (to w) is a tree edge (T's are not).
+__device__ __forceinline__ bool is_tree(const BbGraph &G, const BbWork &W, int v, int w, int e)
+{
+    if (w >= G.n) return w == G.S && (W.adj[v] >> kDirS & 1u);
+    return W.adj[v] >> e & 1u;
+}
+
+// low / high of every live vertex's own non-tree edges, at its first arrival.
+__global__ void bb_reach(BbGraph G, BbWork W)
+{
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+        if (!W.adj[v]) continue;
+        int c[3];
+        coords(G, v, c);
+        const unsigned at = W.in[v];
+        unsigned l = at, h = at;
+        for (int e = 0; e < 2 * G.dim; ++e) {
+            const int w = bb_nbr(G, v, c, e);
+            if (w < 0 || is_tree(G, W, v, w, e)) continue;
+            const unsigned q = w == G.S ? 0u : W.in[w];
+            l = min(l, q);
+            h = max(h, q);
+        }
+        W.lo[0][at] = l;
+        W.hi[0][at] = h;
+    }
+}
+
+__global__ void bb_level(BbWork W, int level)
+{
+    unsigned below = kPosFirst + W.counter[1];
+    for (int k = 1; k < level; ++k) below = (below + kFan - 1) / kFan;
+    const unsigned m = (below + kFan - 1) / kFan;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
+        unsigned l = kNone, h = 0u;
+        for (unsigned k = i * kFan; k < min(below, (i + 1u) * kFan); ++k) {
+            l = min(l, W.lo[level - 1][k]);
+            h = max(h, W.hi[level - 1][k]);
+        }
+        W.lo[level][i] = l;
+        W.hi[level][i] = h;
+    }
+}
+
+// Tree parent of v: S for a head, else the tree neighbour that comes before it.
+__device__ __forceinline__ int tree_parent(const BbGraph &G, const BbWork &W, int v, const int c[3])
+{
+    const unsigned bits = W.adj[v];
+    if (bits >> kDirS & 1u) return G.S;
+    const unsigned at = W.in[v];
+    for (int e = 0; e < 2 * G.dim; ++e) {
+        if (!(bits >> e & 1u)) continue;
+        double gij;
+        const int w = lat_step(G, v, c, e, &gij);
+        if (W.in[w] < at) return w;
+    }
+    return G.S;                                      // (not reached)
 }
 
 // The union-find reads and writes through the L2 (device scope): a plain load
@@ -347,8 +382,9 @@ __device__ __forceinline__ int uf_find(int *uf, int x)
     int p = uf_get(uf, x);
     while (p != x) {
         const int gp = uf_get(uf, p);
-        // halve the path: gp is an ancestor of x (parents have smaller
-        // indices), and only non-roots are written, never a root a hook targets
+        // halve the path: gp is an ancestor of x (parents come first in the
+        // order of the hooks), and only non-roots are written, never a root a
+        // hook targets
         if (gp != p) __hip_atomic_store(uf + x, gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         x = p;
         p = uf_get(uf, x);
@@ -371,42 +407,114 @@ __device__ __forceinline__ void uf_union(int *uf, int a, int b)
     }
 }
 
-__device__ __forceinline__ bool ancestor(const int *pre, const int *nd, int a, int v)
+// The same with roots hooked in the order of the tour.
+__device__ __forceinline__ void uf_union_tour(int *uf, const unsigned *in, int a, int b)
 {
-    return pre[a] <= pre[v] && pre[v] < pre[a] + nd[a];
+    while (true) {
+        a = uf_find(uf, a);
+        b = uf_find(uf, b);
+        if (a == b) return;
+        if (in[a] < in[b]) {
+            const int t = a;
+            a = b;
+            b = t;
+        }
+        if (atomicCAS(&uf[a], a, b) == a) return;
+    }
 }
 
-// The Tarjan-Vishkin joins for every visited vertex other than S.
-__global__ void bb_join(BbGraph G, int b, int e, const int *order, const uint8_t *pdir, const int *pre,
-                        const int *nd, const int *lo, const int *hi, int *uf)
+// 4. Joins along the tree: low / high over the subtree of v from the hierarchy.
+__global__ void bb_join_tree(BbGraph G, BbWork W)
 {
-    for (int q = b + blockIdx.x * blockDim.x + threadIdx.x; q < e; q += gridDim.x * blockDim.x) {
-        const int v = order[q];
-        const uint8_t pv = pdir[v];
-        const int p = bb_parent(G, v, pv);
-        if (p != G.S && (lo[v] < pre[p] || hi[v] >= pre[p] + nd[p])) uf_union(uf, v, p);
-        if (v >= G.n) continue;
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+        if (!W.adj[v]) continue;
         int c[3];
         coords(G, v, c);
-        for (int d = 0; d < 2 * G.dim; ++d) {
-            const int w = bb_nbr(G, v, c, d);
-            if (w < 0 || w == G.S || is_tree(G, w, pv, pdir, d)) continue;
-            if (!ancestor(pre, nd, w, v) && !ancestor(pre, nd, v, w)) uf_union(uf, v, w);
+        const int p = tree_parent(G, W, v, c);
+        if (p == G.S) continue;
+        const unsigned first = W.in[p], last = W.last[p];
+        unsigned l = W.in[v], r = W.last[v] + 1u;    // positions l .. r - 1
+        bool join = false;
+        for (int k = 0; l < r && !join; ++k) {
+            unsigned lo = kNone, hi = 0u;
+            if (r - l < 2u * kFan || k + 1 == kFanLevels) {
+                for (; l < r; ++l) {
+                    lo = min(lo, W.lo[k][l]);
+                    hi = max(hi, W.hi[k][l]);
+                }
+            } else {
+                for (; l % kFan; ++l) {
+                    lo = min(lo, W.lo[k][l]);
+                    hi = max(hi, W.hi[k][l]);
+                }
+                for (; r % kFan; --r) {
+                    lo = min(lo, W.lo[k][r - 1u]);
+                    hi = max(hi, W.hi[k][r - 1u]);
+                }
+                l /= kFan;
+                r /= kFan;
+            }
+            join = lo < first || hi > last;
+        }
+        if (join) W.uf[v] = p;
+    }
+}
+
+// Shorten the chains of joined tree edges.
+__global__ void bb_shorten(BbGraph G, BbWork W)
+{
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+        if (!W.adj[v]) continue;
+        int p = uf_get(W.uf, v);
+        const int was = p;
+        if (p == v) continue;
+        for (int k = 0; k < 4; ++k) {
+            const int q = uf_get(W.uf, p);
+            if (q == p) break;
+            p = q;
+        }
+        if (p != was) __hip_atomic_store(W.uf + v, p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+__device__ __forceinline__ bool ancestor(const BbWork &W, int a, int v)
+{
+    return W.in[a] <= W.in[v] && W.in[v] <= W.last[a];
+}
+
+// Joins across non-tree edges, each from its -k end (and from the node of an
+// edge to T).
+__global__ void bb_join_cross(BbGraph G, BbWork W)
+{
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+        if (!W.adj[v]) continue;
+        int c[3];
+        coords(G, v, c);
+        for (int e = 0; e < 2 * G.dim; ++e) {
+            const int w = bb_nbr(G, v, c, e);
+            if (w < 0 || w == G.S || (w < G.n && !(e & 1)) || is_tree(G, W, v, w, e)) continue;
+            if (!ancestor(W, w, v) && !ancestor(W, v, w)) uf_union_tour(W.uf, W.in, v, w);
         }
     }
 }
 
-// Lattice ends of the tree edges in T's class.
-__global__ void bb_mark(BbGraph G, int b, int e, const int *order, const uint8_t *pdir, int *uf, uint8_t *on)
+// 5. Lattice ends of the tree edges in T's class.
+__global__ void bb_mark(BbGraph G, BbWork W, uint8_t *on)
 {
-    const int rt = uf_find(uf, G.T);
-    for (int q = b + blockIdx.x * blockDim.x + threadIdx.x; q < e; q += gridDim.x * blockDim.x) {
-        const int v = order[q];
-        if (uf_find(uf, v) != rt) continue;
-        if (v < G.n) on[v] = 1;
-        const int p = bb_parent(G, v, pdir[v]);
+    const int rt = uf_find(W.uf, G.T);
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+        if (!W.adj[v] || uf_find(W.uf, v) != rt) continue;
+        on[v] = 1;
+        int c[3];
+        coords(G, v, c);
+        const int p = tree_parent(G, W, v, c);
         if (p < G.n) on[p] = 1;
     }
+}
+
+__global__ void bb_zero(uint8_t *p, int n)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
 }
 
 __global__ void bb_apply(uint8_t *mask, const uint8_t *on, int n, unsigned long long *count)
@@ -516,89 +624,95 @@ int grid_of(int64_t n)
 
 }  // namespace
 
-size_t backbone_scratch_bytes(int64_t n)
+namespace {
+
+// Carves the arrays of the search from `scratch`; returns the bytes used. The
+// walkers' arrays lie where the hierarchy of minima and maxima comes later.
+size_t backbone_layout(int64_t n, char *scratch, BbWork *W)
 {
     const size_t V = (size_t)n + 2;
-    auto a256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    return 7 * a256(4 * V) + 2 * a256(V) + a256(4 * (V + 40)) + 256;
-}
-
-hipError_t launch_backbone(const Lat &L, const double *const g[3], uint8_t *mask, void *scratch,
-                           unsigned long long *n_backbone, int *h_stage, int *depth_out, hipStream_t st)
-{
-    const int64_t n = L.n;
-    const int V = (int)(n + 2);
-    auto a256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    char *p = (char *)scratch;
+    size_t off = 0;
     auto take = [&](size_t bytes) {
-        char *r = p;
-        p += a256(bytes);
+        char *r = scratch + off;
+        off += (bytes + 255) & ~(size_t)255;
         return r;
     };
-    int *lev = (int *)take(4 * (size_t)V), *nd = (int *)take(4 * (size_t)V), *pre = (int *)take(4 * (size_t)V);
-    int *lo = (int *)take(4 * (size_t)V), *hi = (int *)take(4 * (size_t)V), *uf = (int *)take(4 * (size_t)V);
-    int *order = (int *)take(4 * (size_t)V);
-    uint8_t *pdir = (uint8_t *)take((size_t)V), *on = (uint8_t *)take((size_t)V);
-    int *lev_off = (int *)take(4 * ((size_t)V + 40));
-    int *tail = (int *)take(256);
+    W->tree = (uint8_t *)take(V);
+    W->adj = (uint8_t *)take(V);
+    W->in = (unsigned *)take(4 * V);
+    W->last = (unsigned *)take(4 * V);
+    W->uf = (int *)take(4 * V);
+    W->counter = (unsigned *)take(256);
+    const size_t shared = off;
+    // walkers: one per group and per component that touches both faces (at
+    // most one per node next to the inlet, and none has fewer than one node)
+    W->groups = (int)((n + kSpread - 1) / kSpread);
+    const size_t walkers = (size_t)W->groups + (size_t)(n + 2) / 3;
+    for (auto &j : W->jump) j = (unsigned long long *)take(8 * walkers);
+    W->len = (unsigned *)take(4 * walkers);
+    W->end = (unsigned *)take(4 * walkers);
+    W->heads = (unsigned *)take(4 * ((size_t)(n + 2) / 3));
+    W->first = (int *)take(4 * (size_t)W->groups);
+    const size_t one = off;
+    off = shared;
+    size_t m = 2 * V;                                // positions: a component of k nodes has 2 k - 1
+    for (int l = 0; l < kFanLevels; ++l) {
+        W->lo[l] = (unsigned *)take(4 * m);
+        W->hi[l] = (unsigned *)take(4 * m);
+        m = (m + kFan - 1) / kFan;
+    }
+    return std::max(off, one);
+}
 
+}  // namespace
+
+size_t backbone_scratch_bytes(int64_t n)
+{
+    BbWork W;
+    return backbone_layout(n, nullptr, &W);
+}
+
+uint8_t *backbone_tree(int64_t n, void *scratch)
+{
+    BbWork W;
+    backbone_layout(n, (char *)scratch, &W);
+    return W.tree;
+}
+
+hipError_t launch_backbone(const Lat &L, const double *const g[3], uint8_t *mask, const int *parent, unsigned *flags,
+                           void *scratch, unsigned long long *n_backbone, hipStream_t st)
+{
+    const int64_t n = L.n;
+    BbWork W;
+    backbone_layout(n, (char *)scratch, &W);
+    W.parent = parent;
+    W.flags = flags;
     const BbGraph G = graph_of(L, g, mask);
-
-    hipError_t e;
-    bb_init<<<grid_of(V), kBbBlock, 0, st>>>(lev, pdir, nd, pre, uf, on, V, G.S, G.T, order, lev_off, tail);
-    // 1. BFS: level 0 = S, level 1 = T and S's lattice children
-    bb_face_children<<<kBbGrid, kBbBlock, 0, st>>>(G, 1, 1, lev, pdir, order, tail);
-    bb_snap<<<1, 64, 0, st>>>(lev_off, tail, 0);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // levels l >= 1 in batches of kBatch launches, then one read-back of the
-    // level offsets; a level past the last is empty and does nothing
-    // (h_stage: kBackboneStage pinned ints)
-    constexpr int kBatch = kBackboneStage - 2;
-    std::vector<int> off = {0, 1};       // level offsets read back so far
-    int depth = -1;                      // number of levels, once an empty one is seen
-    for (int l0 = 1; depth < 0; l0 += kBatch) {
-        if (l0 + kBatch + 2 > V + 40) return hipErrorInvalidValue;   // cannot happen: levels <= V
-        for (int l = l0; l < l0 + kBatch; ++l) {
-            bb_expand<<<kBbGrid, kBbBlock, 0, st>>>(G, l, lev_off, lev, pdir, order, tail);
-            if (l == 1) bb_face_children<<<kBbGrid, kBbBlock, 0, st>>>(G, 2, 2, lev, pdir, order, tail);
-            bb_snap<<<1, 64, 0, st>>>(lev_off, tail, l);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        // offsets l0 + 1 .. l0 + kBatch + 1 (the ones this batch wrote)
-        if ((e = hipMemcpyAsync(h_stage, lev_off + l0 + 1, sizeof(int) * (size_t)(kBatch + 1), hipMemcpyDeviceToHost,
-                                st)) != hipSuccess)
-            return e;
-        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-        off.resize((size_t)l0 + 1);
-        for (int k = 0; k <= kBatch; ++k) off.push_back(h_stage[k]);
-        for (int l = l0; l < l0 + kBatch; ++l)
-            if (off[(size_t)l + 1] == off[(size_t)l]) {
-                depth = l;
-                break;
-            }
+    const int gn = grid_of(n), gw = grid_of(W.groups + (n + 2) / 3);
+    hipError_t e = launch_clear_u64((unsigned long long *)W.counter, 1, st);
+    if (e != hipSuccess) return e;
+    bb_tree<<<grid_of(n + 2), kBbBlock, 0, st>>>(G, W);
+    bb_starts<<<grid_of(W.groups), kBbBlock, 0, st>>>(G, W);
+    bb_walk<<<gw, kBbBlock, 0, st>>>(G, W);
+    // a component's list has at most one start per group and its head
+    int from = 0;
+    for (int64_t reach = 1; reach < (int64_t)W.groups + 1; reach *= 2, from ^= 1)
+        bb_jump<<<gw, kBbBlock, 0, st>>>(W, from);
+    bb_ranges<<<grid_of((n + 2) / 3), kBbBlock, 0, st>>>(W, from);
+    bb_number<<<gw, kBbBlock, 0, st>>>(G, W, from);
+    bb_clear<<<grid_of(2 * n), kBbBlock, 0, st>>>(W);
+    bb_reach<<<gn, kBbBlock, 0, st>>>(G, W);
+    int64_t m = 2 * (n + 2);
+    for (int l = 1; l < kFanLevels && m > kFan; ++l) {
+        m = (m + kFan - 1) / kFan;
+        bb_level<<<grid_of(m), kBbBlock, 0, st>>>(W, l);
     }
-    // levels 0 .. depth-1 hold vertices: level l is order[off[l] .. off[l+1])
-    const int nvis = off[depth];
-    // 2. subtree sizes, deepest level first
-    for (int l = depth - 1; l >= 1; --l)
-        bb_sizes<<<grid_of(off[l + 1] - off[l]), kBbBlock, 0, st>>>(G, off[l], off[l + 1], order, pdir, nd);
-    // 3. preorder: S = 0 (never read), S's children, T's children, then the rest by level
-    bb_scan_children<<<1, kBbBlock, 0, st>>>(off[1], off[2], order, pdir, kParS, 1, nd, pre);
-    if (depth > 2) {
-        bb_scan_children<<<1, kBbBlock, 0, st>>>(off[2], off[3], order, pdir, kParT, 2, nd, pre);
-        for (int l = 2; l < depth; ++l)
-            bb_preorder<<<grid_of(off[l + 1] - off[l]), kBbBlock, 0, st>>>(G, off[l], off[l + 1], order, pdir, nd,
-                                                                             pre);
-    }
-    // 4. low / high
-    bb_lohi_init<<<grid_of(nvis - 1), kBbBlock, 0, st>>>(G, 1, nvis, order, pdir, pre, lo, hi);
-    for (int l = depth - 1; l >= 2; --l)
-        bb_lohi_up<<<grid_of(off[l + 1] - off[l]), kBbBlock, 0, st>>>(G, off[l], off[l + 1], order, pdir, lo, hi);
-    // 5. joins, 6. marks
-    bb_join<<<grid_of(nvis - 1), kBbBlock, 0, st>>>(G, 1, nvis, order, pdir, pre, nd, lo, hi, uf);
-    bb_mark<<<grid_of(nvis - 1), kBbBlock, 0, st>>>(G, 1, nvis, order, pdir, uf, on);
-    bb_apply<<<grid_of(n), kBbBlock, 0, st>>>(mask, on, (int)n, n_backbone);
-    if (depth_out) *depth_out = depth;
+    bb_join_tree<<<gn, kBbBlock, 0, st>>>(G, W);
+    for (int64_t reach = 1; reach < n; reach *= 5) bb_shorten<<<gn, kBbBlock, 0, st>>>(G, W);
+    bb_join_cross<<<gn, kBbBlock, 0, st>>>(G, W);
+    bb_zero<<<gn, kBbBlock, 0, st>>>(W.tree, (int)n);
+    bb_mark<<<gn, kBbBlock, 0, st>>>(G, W, W.tree);
+    bb_apply<<<gn, kBbBlock, 0, st>>>(mask, W.tree, (int)n, n_backbone);
     return hipGetLastError();
 }
 

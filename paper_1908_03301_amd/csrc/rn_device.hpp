@@ -127,9 +127,11 @@ struct Lat {
 // launchers (rn_kernels.hip)
 hipError_t launch_validate(const Lat &L, const double *const g[3], unsigned long long *bad, hipStream_t st);
 // linear: the live nodes' initial pressure is the linear profile along the
-// flow axis (else 0); P may be null (mask and live count only)
+// flow axis (else 0); P may be null (mask and live count only); tree (nullable,
+// n bytes): bit k of tree[i] set when the bond i -> i + e_k is in the spanning
+// forest of the interior nodes
 hipError_t launch_mask(const Lat &L, const double *const g[3], int *parent, unsigned *flags, uint8_t *mask,
-                       double *P, unsigned long long *n_live, bool linear, hipStream_t st);
+                       double *P, unsigned long long *n_live, bool linear, hipStream_t st, uint8_t *tree = nullptr);
 template <typename T>
 hipError_t launch_scale(const Lat &L, const double *const g[3], const uint8_t *mask, T *const gT[3], T *vec,
                         int64_t nvec, hipStream_t st);
@@ -168,18 +170,16 @@ template <typename T>
 hipError_t launch_compact_round(const CompactArgs<T> &a, Scalars *s, hipStream_t st);
 hipError_t launch_compact_scatter(const int *idx, int m, const double *P, double *Pl, hipStream_t st);
 
-// Backbone (rn_backbone.hip): with `mask` the connectivity mask of the
-// lattice, set bit 3 on every interior node of the backbone and add their
-// number to *n_backbone (a device counter). `scratch` holds
-// backbone_scratch_bytes(n) device bytes; h_stage is pinned host memory of
-// kBackboneStage ints for the level offsets the breadth-first search reads
-// back (one synchronisation of `st` per kBackboneStage - 2 levels). Needs
-// n + 2 < 2^31 and at least 3 planes on the flow axis. *depth_out (nullable)
-// receives the number of levels of the search.
-constexpr int kBackboneStage = 34;
+// Backbone (rn_backbone.hip): with `mask`, `parent` and `flags` as launch_mask
+// leaves them (called with tree = backbone_tree(n, scratch)), set bit 3 on every
+// interior node of the backbone and add their number to *n_backbone (a device
+// counter). `scratch` holds backbone_scratch_bytes(n) device bytes; flags is
+// written. Needs n + 2 < 2^31 and at least 3 planes on the flow axis. Nothing
+// is read back to the host.
 size_t backbone_scratch_bytes(int64_t n);
-hipError_t launch_backbone(const Lat &L, const double *const g[3], uint8_t *mask, void *scratch,
-                           unsigned long long *n_backbone, int *h_stage, int *depth_out, hipStream_t st);
+uint8_t *backbone_tree(int64_t n, void *scratch);
+hipError_t launch_backbone(const Lat &L, const double *const g[3], uint8_t *mask, const int *parent, unsigned *flags,
+                           void *scratch, unsigned long long *n_backbone, hipStream_t st);
 // With `mask` from launch_backbone (backbone 11, dangling 3): find the pieces
 // of dangling nodes (uf, n ints) and the backbone node each hangs from (att,
 // n ints, at the piece's root) from the bonds g, then, when gw (a writable

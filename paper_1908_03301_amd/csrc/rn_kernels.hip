@@ -1144,12 +1144,15 @@ __device__ __forceinline__ int uf_find(int *parent, int x)
     }
 }
 
-__device__ __forceinline__ void uf_union(int *parent, int a, int b)
+// Returns whether this call joined the two components: the bonds whose union
+// did span every component without a cycle, since a root is hooked once and
+// under a smaller index of another component.
+__device__ __forceinline__ bool uf_union(int *parent, int a, int b)
 {
     while (true) {
         a = uf_find(parent, a);
         b = uf_find(parent, b);
-        if (a == b) return;
+        if (a == b) return false;
         if (a < b) {
             const int t = a;
             a = b;
@@ -1158,7 +1161,7 @@ __device__ __forceinline__ void uf_union(int *parent, int a, int b)
         int expected = a;
         if (__hip_atomic_compare_exchange_strong(parent + a, &expected, b, __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            return;
+            return true;
     }
 }
 
@@ -1172,7 +1175,7 @@ __global__ void uf_init_kernel(int64_t n, int *parent, unsigned *flags)
 
 // Union across every occupied bond joining two interior nodes (a wrap bond
 // joins two nodes of the same plane along the flow axis).
-__global__ void uf_union_kernel(Lat L, const double *g0, const double *g1, const double *g2, int *parent)
+__global__ void uf_union_kernel(Lat L, const double *g0, const double *g1, const double *g2, int *parent, uint8_t *tree)
 {
     const double *g[3] = {g0, g1, g2};
     const int64_t st[3] = {1, L.nx, (int64_t)L.nx * L.ny};
@@ -1180,18 +1183,20 @@ __global__ void uf_union_kernel(Lat L, const double *g0, const double *g1, const
          i += (int64_t)gridDim.x * blockDim.x) {
         int x, y, z;
         coords(L, i, x, y, z);
-        if (face_code(L, x, y, z)) continue;
+        unsigned bits = 0u;
         const int c[3] = {x, y, z};
         const int n[3] = {L.nx, L.ny, L.nz};
-        for (int k = 0; k < L.dim; ++k) {
+        const bool face = face_code(L, x, y, z) != 0;
+        for (int k = 0; k < L.dim && !face; ++k) {
             int64_t j;
             if (c[k] + 1 < n[k]) j = i + st[k];
             else if ((L.wrap >> k) & 1) j = i - (int64_t)(n[k] - 1) * st[k];   // wrap bond (never the flow axis)
             else continue;
             if (!(g[k][i] > 0.0)) continue;
             if (k == L.axis && c[k] + 1 == n[k] - 1) continue;     // neighbour on the outlet face
-            uf_union(parent, (int)i, (int)j);
+            if (uf_union(parent, (int)i, (int)j)) bits |= 1u << k;
         }
+        if (tree) tree[i] = (uint8_t)bits;
     }
 }
 
@@ -1648,12 +1653,12 @@ hipError_t launch_validate(const Lat &L, const double *const g[3], unsigned long
 }
 
 hipError_t launch_mask(const Lat &L, const double *const g[3], int *parent, unsigned *flags, uint8_t *mask,
-                       double *P, unsigned long long *n_live, bool linear, hipStream_t st)
+                       double *P, unsigned long long *n_live, bool linear, hipStream_t st, uint8_t *tree)
 {
     const int gr = grid_for(L.n);
     const double *g2 = L.dim == 3 ? g[2] : nullptr;
     uf_init_kernel<<<gr, kBlock, 0, st>>>(L.n, parent, flags);
-    uf_union_kernel<<<gr, kBlock, 0, st>>>(L, g[0], g[1], g2, parent);
+    uf_union_kernel<<<gr, kBlock, 0, st>>>(L, g[0], g[1], g2, parent, tree);
     uf_flags_kernel<<<gr, kBlock, 0, st>>>(L, g[L.axis], parent, flags);
     mask_final_kernel<<<gr, kBlock, 0, st>>>(L, parent, flags, mask, P, n_live, linear ? 1 : 0);
     return hipGetLastError();
