@@ -525,8 +525,15 @@ __global__ void bb_apply(uint8_t *mask, const uint8_t *on, int n, unsigned long 
             mask[i] |= 8u;
             ++c;
         }
+    // one atomic per workgroup (one per wave, on one address, took 0.4 ms)
+    __shared__ int part[kBbBlock / 64];
     for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(count, (unsigned long long)c);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBbBlock / 64; ++w) c += part[w];
+        if (c) atomicAdd(count, (unsigned long long)c);
+    }
 }
 
 // ---------------------------------------------------------------- solves on the backbone
@@ -712,7 +719,7 @@ hipError_t launch_backbone(const Lat &L, const double *const g[3], uint8_t *mask
     bb_join_cross<<<gn, kBbBlock, 0, st>>>(G, W);
     bb_zero<<<gn, kBbBlock, 0, st>>>(W.tree, (int)n);
     bb_mark<<<gn, kBbBlock, 0, st>>>(G, W, W.tree);
-    bb_apply<<<gn, kBbBlock, 0, st>>>(mask, W.tree, (int)n, n_backbone);
+    bb_apply<<<std::min(gn, 2048), kBbBlock, 0, st>>>(mask, W.tree, (int)n, n_backbone);
     return hipGetLastError();
 }
 
