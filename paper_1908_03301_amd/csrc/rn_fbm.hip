@@ -5,7 +5,7 @@
 // distributed generator; the flow solve does not depend on it.
 //
 // Transforms are hipFFT's double-precision real-to-complex and back; the
-// spectral filter, the standardisation and the bonds are kernels here.
+// spectral filter, which also standardises, and the bonds are kernels here.
 #include "rn_runtime.hpp"
 
 #include <hipfft/hipfft.h>
@@ -16,78 +16,98 @@
 namespace rn {
 namespace {
 
-// Spectral filter on the half spectrum of a real nz x ny x nx grid (x
-// fastest, nxh = nx/2 + 1 modes along x): multiply by the amplitude
-// (sum_k beta_k f_k^2)^-(H + d/2)/2, with f the mode's frequency in cycles per
-// node (f = j/n for j <= (n-1)/2, else (j - n)/n), zero the k = 0 mode, and
-// fold in the 1/N of the inverse transform.
-__global__ void fbm_filter_kernel(hipfftDoubleComplex *spec, int nx, int ny, int nz, int dim, double bx, double by,
-                                  double bz, double expo, double inv_n)
+// Amplitude of the spectral filter on the half spectrum of a real nz x ny x nx
+// grid (x fastest, nxh = nx/2 + 1 modes along x): (sum_k beta_k f_k^2)^expo /
+// N, with f the mode's frequency in cycles per node, N the inverse transform's
+// norm, and 0 at k = 0. It is the same for +-f along y and z, so one power
+// serves up to four modes: computed for each, the powers took twice as long as
+// the filter's bytes.
+struct FbmGrid {
+    int nx, ny, nz, nxh, nyh, nzh;        // nyh = ny/2 + 1 and nzh = nz/2 + 1 frequencies up to sign
+    double b[3], expo, inv_n;
+};
+
+__device__ __forceinline__ double fbm_amplitude(const FbmGrid &F, int jx, int jy, int jz)
 {
-    const int nxh = nx / 2 + 1;
-    const int64_t total = (int64_t)nz * ny * nxh;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int jx = (int)(i % nxh);
-        const int64_t t = i / nxh;
-        const int jy = (int)(t % ny);
-        const int jz = (int)(t / ny);
-        const double fx = (double)jx / nx;   // jx <= nx/2: non-negative frequencies only
-        const double fy = (double)(jy <= (ny - 1) / 2 ? jy : jy - ny) / ny;
-        const double fz = dim == 3 ? (double)(jz <= (nz - 1) / 2 ? jz : jz - nz) / nz : 0.0;
-        const double k2 = bx * fx * fx + by * fy * fy + bz * fz * fz;
-        const double a = k2 > 0.0 ? pow(k2, expo) * inv_n : 0.0;
-        hipfftDoubleComplex v = spec[i];
-        v.x *= a;
-        v.y *= a;
-        spec[i] = v;
+    const double fx = (double)jx / F.nx, fy = (double)jy / F.ny, fz = (double)jz / F.nz;
+    const double k2 = F.b[0] * fx * fx + F.b[1] * fy * fy + F.b[2] * fz * fz;
+    return k2 > 0.0 ? pow(k2, F.expo) * F.inv_n : 0.0;
+}
+
+// The rows of one (|f_y|, |f_z|): visit(row offset) for each of the one, two
+// or four sign pairs.
+template <typename V>
+__device__ __forceinline__ void fbm_rows(const FbmGrid &F, int jy, int jz, V &&visit)
+{
+    const bool my = jy > 0 && 2 * jy != F.ny, mz = jz > 0 && 2 * jz != F.nz;
+    for (int s = 0; s < 4; ++s) {
+        if (((s & 1) && !my) || ((s & 2) && !mz)) continue;
+        const int y = (s & 1) ? F.ny - jy : jy, z = (s & 2) ? F.nz - jz : jz;
+        visit(((int64_t)z * F.ny + y) * F.nxh);
     }
 }
 
-// Block sums in a fixed order: block b adds elements b, b + grid, ... (per
-// thread, in index order), then a tree over the block; a second launch of one
-// block adds the block sums in order. mode 0: sum x; mode 1: sum (x - c)^2.
 constexpr int kRedThreads = 256, kRedBlocks = 1024;
 
-__global__ void fbm_sum_kernel(const double *x, int64_t n, double c, int mode, double *partial)
+__device__ __forceinline__ double fbm_block_sum(double acc)
 {
     __shared__ double sh[kRedThreads];
-    double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double v = mode ? (x[i] - c) * (x[i] - c) : x[i];
-        acc += v;
-    }
     sh[threadIdx.x] = acc;
     __syncthreads();
     for (int s = kRedThreads / 2; s > 0; s >>= 1) {
         if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = sh[0];
+    return sh[0];
 }
 
-__global__ void fbm_total_kernel(const double *partial, int m, double *out)
+// Variance of the filtered field from its spectrum (Parseval; its mean is 0):
+// block sums in a fixed order, then one block adds them and stores 1 / sd (0
+// for a field of zeros). The field is then standardised by the filter itself,
+// in place of two sums over it, a read-back of its mean and a pass that
+// divides (0.25 of 1.09 ms at 256^3).
+__global__ void fbm_power_kernel(const hipfftDoubleComplex *spec, FbmGrid F, double *partial)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double t = 0.0;
-        for (int b = 0; b < m; ++b) t += partial[b];
-        *out = t;
+    double acc = 0.0;
+    const int64_t total = (int64_t)F.nzh * F.nyh * F.nxh;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+        const unsigned u = (unsigned)i, t = u / (unsigned)F.nxh;
+        const int jx = (int)(u - t * (unsigned)F.nxh), jz = (int)(t / (unsigned)F.nyh), jy = (int)(t - (unsigned)jz * (unsigned)F.nyh);
+        const double a = fbm_amplitude(F, jx, jy, jz);
+        double p = 0.0;
+        fbm_rows(F, jy, jz, [&](int64_t row) {
+            const hipfftDoubleComplex v = spec[row + jx];
+            p += (a * v.x) * (a * v.x) + (a * v.y) * (a * v.y);
+        });
+        acc += jx > 0 && 2 * jx != F.nx ? 2.0 * p : p;      // the conjugate half
     }
+    acc = fbm_block_sum(acc);
+    if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
-// (x - mean) / sd with the two sums produced above (sd = 0: all zeros)
-__global__ void fbm_standardise_kernel(double *x, int64_t n, const double *sums)
+__global__ void fbm_scale_kernel(const double *partial, double *scale)
 {
-    const double mean = sums[0] / (double)n;
-    const double var = sums[1] / (double)n;
-    const double inv = var > 0.0 ? 1.0 / sqrt(var) : 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        x[i] = var > 0.0 ? (x[i] - mean) * inv : 0.0;
+    double acc = 0.0;
+    for (int b = threadIdx.x; b < kRedBlocks; b += kRedThreads) acc += partial[b];
+    acc = fbm_block_sum(acc);
+    if (threadIdx.x == 0) *scale = acc > 0.0 ? 1.0 / sqrt(acc) : 0.0;
 }
 
-__global__ void fbm_mean_kernel(const double *sums, int64_t n, double *mean)
+__global__ void fbm_filter_kernel(hipfftDoubleComplex *spec, FbmGrid F, const double *scale)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *mean = sums[0] / (double)n;
+    const double sc = *scale;
+    const int64_t total = (int64_t)F.nzh * F.nyh * F.nxh;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+        const unsigned u = (unsigned)i, t = u / (unsigned)F.nxh;
+        const int jx = (int)(u - t * (unsigned)F.nxh), jz = (int)(t / (unsigned)F.nyh), jy = (int)(t - (unsigned)jz * (unsigned)F.nyh);
+        const double a = fbm_amplitude(F, jx, jy, jz) * sc;
+        fbm_rows(F, jy, jz, [&](int64_t row) {
+            hipfftDoubleComplex v = spec[row + jx];
+            v.x = sc != 0.0 ? v.x * a : 0.0;                // zeros also where the noise is not finite
+            v.y = sc != 0.0 ? v.y * a : 0.0;
+            spec[row + jx] = v;
+        });
+    }
 }
 
 // g_k[i] = exp(sigma (phi_i + phi_{i+e_k}) / 2) on the periodic grid; 0 on the
@@ -96,19 +116,31 @@ __global__ void fbm_bonds_kernel(const double *phi, int nx, int ny, int nz, int 
                                  const double *u0, const double *u1, const double *u2, double occ, double *g0,
                                  double *g1, double *g2)
 {
-    const int64_t n = (int64_t)nx * ny * nz;
-    const int64_t st[3] = {1, nx, (int64_t)nx * ny};
+    // n < 2^31: 32-bit index arithmetic (64-bit divisions took longer than the
+    // exponentials); a node's loads go out together
+    const unsigned n = (unsigned)((int64_t)nx * ny * nz);
+    const int st[3] = {1, nx, nx * ny};
     const int ext[3] = {nx, ny, nz};
     const double *u[3] = {u0, u1, u2};
     double *g[3] = {g0, g1, g2};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int c[3] = {(int)(i % nx), (int)((i / nx) % ny), (int)(i / ((int64_t)nx * ny))};
-        for (int k = 0; k < dim; ++k) {
-            const bool last = c[k] == ext[k] - 1;
-            const int64_t j = last ? i - (int64_t)(ext[k] - 1) * st[k] : i + st[k];
-            double v = exp(sigma * 0.5 * (phi[i] + phi[j]));
-            if (last && !periodic) v = 0.0;
-            if (u[k] && !(u[k][i] < occ)) v = 0.0;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        const unsigned row = i / (unsigned)nx, z = row / (unsigned)ny;
+        const int c[3] = {(int)(i - row * (unsigned)nx), (int)(row - z * (unsigned)ny), (int)z};
+        const double here = phi[i];
+        double there[3], draw[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (k >= dim) break;
+            const int j = c[k] == ext[k] - 1 ? (int)i - (ext[k] - 1) * st[k] : (int)i + st[k];
+            there[k] = phi[j];
+            draw[k] = u[k] ? u[k][i] : -1.0;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (k >= dim) break;
+            double v = exp(sigma * 0.5 * (here + there[k]));
+            if (c[k] == ext[k] - 1 && !periodic) v = 0.0;
+            if (u[k] && !(draw[k] < occ)) v = 0.0;
             g[k][i] = v;
         }
     }
@@ -199,17 +231,20 @@ extern "C" int rn_fbm_field(rn_ctx *ctx, int32_t dim, int64_t nx, int64_t ny, in
     const int64_t n = nx * ny * nz;
     const int64_t nspec = nz * ny * (nx / 2 + 1);
     auto a256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const size_t off_x = 0, off_s = a256(8 * n), off_p = off_s + a256(16 * nspec), off_sum = off_p + a256(8 * kRedBlocks),
-                 total = off_sum + 256;
+    // device callers: the field's own buffer takes the copy of the noise that
+    // the transforms work on
+    const size_t off_x = 0, off_s = mem == RN_MEM_HOST ? a256(8 * n) : 0, off_p = off_s + a256(16 * nspec),
+                 off_sum = off_p + a256(8 * kRedBlocks), total = off_sum + 256;
     Scratch sc(ctx);
     hipError_t he;
     sc.base = (char *)ctx->pool.alloc(total, &he);
     if (!sc.base) return RN_ENOMEM;
-    double *x = (double *)(sc.base + off_x);
+    double *x = mem == RN_MEM_HOST ? (double *)(sc.base + off_x) : field_out;
     hipfftDoubleComplex *spec = (hipfftDoubleComplex *)(sc.base + off_s);
     double *partial = (double *)(sc.base + off_p), *sums = (double *)(sc.base + off_sum);
     const hipStream_t st = ctx->stream;
-    FBM_TRY(hipMemcpyAsync(x, noise, 8 * n, mem == RN_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
+    if (x != noise)
+        FBM_TRY(hipMemcpyAsync(x, noise, 8 * n, mem == RN_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
     FbmPlans *pl = static_cast<FbmPlans *>(ctx->fbm_plans);
     if (!pl || pl->dim != dim || pl->nx != nx || pl->ny != ny || pl->nz != nz) {
         fbm_release(ctx);
@@ -232,25 +267,22 @@ extern "C" int rn_fbm_field(rn_ctx *ctx, int32_t dim, int64_t nx, int64_t ny, in
     FFT_TRY(hipfftSetStream(fwd, st));
     FFT_TRY(hipfftSetStream(inv, st));
     FFT_TRY(hipfftExecD2Z(fwd, x, spec));
-    fbm_filter_kernel<<<grid_of(nspec), 256, 0, st>>>(spec, (int)nx, (int)ny, (int)nz, dim, b[0], b[1],
-                                                       dim == 3 ? b[2] : 0.0, -(H + 0.5 * dim) / 2.0,
-                                                       1.0 / (double)n);
+    FbmGrid F;
+    F.nx = (int)nx;
+    F.ny = (int)ny;
+    F.nz = (int)nz;
+    F.nxh = F.nx / 2 + 1;
+    F.nyh = F.ny / 2 + 1;
+    F.nzh = F.nz / 2 + 1;
+    for (int k = 0; k < 3; ++k) F.b[k] = k < dim ? b[k] : 0.0;
+    F.expo = -(H + 0.5 * dim) / 2.0;
+    F.inv_n = 1.0 / (double)n;
+    fbm_power_kernel<<<kRedBlocks, kRedThreads, 0, st>>>(spec, F, partial);
+    fbm_scale_kernel<<<1, kRedThreads, 0, st>>>(partial, sums);
+    fbm_filter_kernel<<<grid_of((int64_t)F.nzh * F.nyh * F.nxh), 256, 0, st>>>(spec, F, sums);
     FBM_TRY(hipGetLastError());
     FFT_TRY(hipfftExecZ2D(inv, spec, x));
-    // standardise: mean, then the mean square deviation (population), both in a fixed order
-    fbm_sum_kernel<<<kRedBlocks, kRedThreads, 0, st>>>(x, n, 0.0, 0, partial);
-    fbm_total_kernel<<<1, 64, 0, st>>>(partial, kRedBlocks, sums);
-    fbm_mean_kernel<<<1, 64, 0, st>>>(sums, n, sums + 2);
-    FBM_TRY(hipGetLastError());
-    double mean = 0.0;
-    FBM_TRY(hipMemcpyAsync(&mean, sums + 2, 8, hipMemcpyDeviceToHost, st));
-    FBM_TRY(hipStreamSynchronize(st));
-    fbm_sum_kernel<<<kRedBlocks, kRedThreads, 0, st>>>(x, n, mean, 1, partial);
-    fbm_total_kernel<<<1, 64, 0, st>>>(partial, kRedBlocks, sums + 1);
-    fbm_standardise_kernel<<<grid_of(n), 256, 0, st>>>(x, n, sums);
-    FBM_TRY(hipGetLastError());
-    FBM_TRY(hipMemcpyAsync(field_out, x, 8 * n, mem == RN_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice,
-                           st));
+    if (mem == RN_MEM_HOST) FBM_TRY(hipMemcpyAsync(field_out, x, 8 * n, hipMemcpyDeviceToHost, st));
     FBM_TRY(hipStreamSynchronize(st));
     return RN_OK;
 }
