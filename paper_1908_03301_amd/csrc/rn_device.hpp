@@ -227,7 +227,7 @@ hipError_t launch_pass_persist(int dim, int coh, const PassArgs<T> *tab, const u
 
 // Resident CG loop (rn_loop.hpp): one launch runs up to `limit` CG passes of
 // the one network in `slot`, with its state in registers. `dim` as for
-// launch_pass; tpw and tile_z are the network's. *gate (two words, zero before
+// launch_pass; tpw and tile_z are the network's. *gate (three words, zero before
 // the launch) admits the workgroups; gate_clear is another launch's gate, to be
 // cleared; part holds loop_part_bytes(); xch two slots of xch_slot words and
 // coef kLoopCoefBytes, both only ever written by these loops, with pass numbers
@@ -244,16 +244,18 @@ struct LoopArgs {
 constexpr size_t kLoopCoefBytes = 2048;
 constexpr int kLoopRed = 4;             // sums that the CG step uses
 constexpr int kLoopSlots = 4;           // slots of the exchange between workgroups
+constexpr int kLoopLocalMax = 32;       // ... of one on a single XCD
 constexpr int kLoopGridMax = 1024;      // workgroups of a resident loop
 inline size_t loop_part_bytes() { return (size_t)kLoopSlots * kLoopRed * kLoopGridMax * sizeof(double); }
-// workgroups of this shape that the device holds at once (0: no loop kernel for it)
+// workgroups of this shape that the device (one XCD of it: local) holds at once
+// (0: no loop kernel for it)
 template <typename T>
-hipError_t loop_capacity(int dim, int tpw, int tile_z, int *cap);
+hipError_t loop_capacity(int dim, int tpw, int tile_z, bool local, int *cap);
 // words of one exchange slot of a network of `ntiles` tiles
 template <typename T>
 size_t loop_exchange_words(int dim, int tile_z, int ntiles);
 template <typename T>
-hipError_t launch_loop(int dim, int tpw, int tile_z, int grid, const PassArgs<T> *tab, Scalars *scal, int parity,
+hipError_t launch_loop(int dim, int tpw, int tile_z, bool local, int grid, const PassArgs<T> *tab, Scalars *scal, int parity,
                        int slot, const LoopArgs &r, hipStream_t st);
 
 // tile geometry of the pass kernels: a 2D workgroup tile is 64 kSEG2f x

@@ -417,7 +417,7 @@ void Pool::free(void *ptr)
 int Engine::init(hipStream_t st, std::string *err)
 {
     (void)st;
-    std::fill(&loop_cap_[0][0][0], &loop_cap_[0][0][0] + sizeof(loop_cap_) / sizeof(int), -1);
+    std::fill(&loop_cap_[0][0][0][0], &loop_cap_[0][0][0][0] + sizeof(loop_cap_) / sizeof(int), -1);
     // Graph replay of pass rounds is opt-in (RN_GRAPHS=1): on a launch-bound
     // 128^2 solve it measured 5% slower than direct launches, since the time
     // of a small pass is spent on the device, not in the launch call.
@@ -847,7 +847,7 @@ int Engine::launch_persistent(int rounds, hipStream_t st, std::string *err)
 // mixed 9.0 -> 3.6 us, 201 x 150 FP64 9.1 -> 3.9, 512^2 FP64 10.9 -> 5.1,
 // 1024^2 mixed 16.0 -> 6.4, 1024^2 FP64 21.4 -> 8.0, 2048^2 mixed 34.0 -> 30.4.
 // Several networks share launches instead.
-int Engine::loop_fits(const Net *net, bool *fits, std::string *err)
+int Engine::loop_fits(Net *net, bool *fits, std::string *err)
 {
     *fits = false;
     if (persist_ || use_graph_ || !net->loop_ok) return RN_OK;
@@ -855,12 +855,15 @@ int Engine::loop_fits(const Net *net, bool *fits, std::string *err)
     if (tpw < 1 || tpw > kLoopTpw) return RN_OK;
     const int tz = net->L.dim == 3 ? net->L.tile_z : 0;
     if (tz >= kLoopTz) return RN_OK;
-    int &cap = loop_cap_[k][tpw - 1][tz];
-    if (cap < 0) {
-        if (kind_fp64(k)) ENG_TRY(loop_capacity<double>(kind_dim(k), tpw, tz, &cap));
-        else ENG_TRY(loop_capacity<float>(kind_dim(k), tpw, tz, &cap));
+    for (int local = 1; local >= 0 && !*fits; --local) {
+        int &cap = loop_cap_[k][tpw - 1][tz][local];
+        if (cap < 0) {
+            if (kind_fp64(k)) ENG_TRY(loop_capacity<double>(kind_dim(k), tpw, tz, local != 0, &cap));
+            else ENG_TRY(loop_capacity<float>(kind_dim(k), tpw, tz, local != 0, &cap));
+        }
+        *fits = net->L.grid <= cap;
+        net->loop_local = *fits && local;
     }
-    *fits = net->L.grid <= cap;
     return RN_OK;
 }
 
@@ -915,8 +918,8 @@ int Engine::launch_loops(Net *net, int *launched, hipStream_t st, std::string *e
             loop_tag_ += kLoopLimit;
             a.limit = kLoopLimit;
             gate_ = (gate_ + 1) % kGates;
-            if (!kind_fp64(k)) ENG_TRY(launch_loop<float>(dim, net->L.tpw, tz, net->L.grid, d_tabf_, d_scal_, par, slot, a, st));
-            else ENG_TRY(launch_loop<double>(dim, net->L.tpw, tz, net->L.grid, d_tabd_, d_scal_, par, slot, a, st));
+            if (!kind_fp64(k)) ENG_TRY(launch_loop<float>(dim, net->L.tpw, tz, net->loop_local, net->L.grid, d_tabf_, d_scal_, par, slot, a, st));
+            else ENG_TRY(launch_loop<double>(dim, net->L.tpw, tz, net->loop_local, net->L.grid, d_tabd_, d_scal_, par, slot, a, st));
         } else if (!kind_fp64(k)) {
             ENG_TRY(launch_pass<float>(dim, d_tabf_, nullptr, d_scal_, net->L.grid, par, slot, st));
         } else {

@@ -113,6 +113,7 @@ struct Net {
     double prev_est = -1.0;
     int64_t prev_iters = 0;
     bool loop_ok = true;            // may run in resident loops (no launch of one was turned away yet)
+    bool loop_local = false;        // ... on one XCD
     bool loop_used = false;         // a chunk of resident loops was launched
     int64_t first_chunk = 0;        // first chunk whose status mirror covers this network
     // host copies (server path: the caller's buffers stay valid until completion)
@@ -216,7 +217,7 @@ private:
     // long as a chunk of single passes, so other requests wait no longer.
     static constexpr int kGates = 8, kGateBytes = 256, kLoopLimit = 512, kLoopsPerChunk = 2;
     static constexpr int kLoopTpw = 2, kLoopTz = 9;
-    int loop_fits(const Net *net, bool *fits, std::string *err);
+    int loop_fits(Net *net, bool *fits, std::string *err);
     int launch_loops(Net *net, int *launched, hipStream_t st, std::string *err);
     int queue_status(int rounds, hipStream_t st, std::string *err);
     char *d_gate_ = nullptr;                 // kGates gates, used in turn, each cleared kGates / 2 launches later
@@ -225,7 +226,8 @@ private:
     unsigned loop_tag_ = 1;                  // first pass number of the next loop
     double *d_lpart_ = nullptr;              // partial sums of a resident loop
     int gate_ = 0;
-    int loop_cap_[kKinds][kLoopTpw][kLoopTz];   // workgroups that fit at once by kind, tiles, depth; -1 = not asked yet
+    int loop_cap_[kKinds][kLoopTpw][kLoopTz][2];   // workgroups that fit at once by kind, tiles, depth, on all
+                                                // XCDs or one; -1 = not asked yet
     hipStream_t side_ = nullptr;
     unsigned *d_err_ = nullptr, *h_err_ = nullptr;   // a bounded wait gave up (device word, pinned mirror)
     unsigned long long *d_queue_ = nullptr;          // item counters of the persistent launches, kQueueWords per kind
