@@ -845,7 +845,7 @@ int Engine::launch_persistent(int rounds, hipStream_t st, std::string *err)
 // by its chain of round trips, and every shape that fits is faster there. Whole
 // solves over their iterations, one launch per pass against the loop: 128^2
 // mixed 9.0 -> 3.6 us, 201 x 150 FP64 9.1 -> 3.9, 512^2 FP64 10.9 -> 5.1,
-// 1024^2 mixed 16.0 -> 6.4, 1024^2 FP64 21.4 -> 8.0, 2048^2 mixed 34.0 -> 30.4.
+// 1024^2 mixed 16.0 -> 6.4, 1024^2 FP64 21.0 -> 8.0, 2048^2 mixed 34.1 -> 18.3.
 // Several networks share launches instead.
 int Engine::loop_fits(Net *net, bool *fits, std::string *err)
 {

@@ -54,6 +54,7 @@ namespace {
 constexpr uint64_t kGateTicks = 50000ull;        // 0.5 ms: longer than any launch takes to start
 constexpr unsigned kGateGo = 1u, kGateNo = 2u;
 constexpr int kDirect = 64;                      // workgroups up to which each sums for itself
+constexpr int kPerGroup = 2;                     // most workgroups of the pass kernels that one here stands for
 constexpr int kCopies = 32;                      // copies of the coefficients, 64 bytes each
 typedef unsigned long long u64;
 constexpr u64 kEmpty = ~0ull;
@@ -188,7 +189,7 @@ __device__ __forceinline__ int loop_place(const LoopArgs &r, int grid)
 
 // LDS of the loop's control, the same for every tile family.
 struct LoopShared {
-    double red[kBlock / kWave][kLoopRed], tot[kBlock / kWave][kLoopRed];
+    double red[kPerGroup][kBlock / kWave][kLoopRed], tot[kBlock / kWave][kLoopRed];
     Scalars sl[kBlock / kWave];
     int go;
 };
@@ -201,13 +202,15 @@ struct LoopState {
 // Emptied sums, the control block's copies, the gate. Returns whether the
 // launch goes ahead.
 template <bool LOCAL>
-__device__ __forceinline__ bool loop_begin(LoopShared &sh, LoopState &L, Scalars *s, const LoopArgs &r, int lb,
-                                           int grid)
+__device__ __forceinline__ bool loop_begin(LoopShared &sh, LoopState &L, Scalars *s, const LoopArgs &r,
+                                           const int *lbs, int nlb, int grid)
 {
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     u64 *part = reinterpret_cast<u64 *>(r.part);
     if (threadIdx.x < kLoopRed)
-        for (int q = 0; q < kLoopSlots; ++q) word_store<LOCAL>(part + (q * kLoopRed + threadIdx.x) * grid + lb, kEmpty);
+        for (int l = 0; l < nlb && lbs[l] < grid; ++l)
+            for (int q = 0; q < kLoopSlots; ++q)
+                word_store<LOCAL>(part + (q * kLoopRed + threadIdx.x) * grid + lbs[l], kEmpty);
     if (lane < kScalWords)
         reinterpret_cast<u64 *>(&sh.sl[w])[lane] = reinterpret_cast<const u64 *>(s)[lane];
     L.alpha = s->alpha;
@@ -215,34 +218,42 @@ __device__ __forceinline__ bool loop_begin(LoopShared &sh, LoopState &L, Scalars
     L.sa = s->sigma * s->alpha;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, (unsigned)grid, s);
+    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, LOCAL ? (unsigned)grid : gridDim.x, s);
     __syncthreads();
     return sh.go != 0;
 }
 
-// This workgroup's four sums (thread sums, waves, then waves in order, as in
-// finish_pass) into pass `it`'s slot, and the slot after next emptied. Wave 0
-// has waited (s_waitcnt) for what it emptied in the pass before.
-template <bool LOCAL>
-__device__ __forceinline__ void post_sums(LoopShared &sh, const double (&acc)[kLoopRed], const LoopArgs &r, int it,
-                                          int lb, int grid)
+// The four sums of a workgroup of the pass kernels, as in finish_pass: thread
+// sums and waves here, waves in order in post_sums.
+__device__ __forceinline__ void wave_sums(double (&red)[kBlock / kWave][kLoopRed], const double (&acc)[kLoopRed])
 {
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
 #pragma unroll
     for (int k = 0; k < kLoopRed; ++k) {
         const double v = wave_sum(acc[k]);
-        if (lane == 0) sh.red[w][k] = v;
+        if (lane == 0) red[w][k] = v;
     }
+}
+
+// Its sums into pass `it`'s slot, and the slot after next emptied. Wave 0 has
+// waited (s_waitcnt) for what it emptied in the pass before.
+template <bool LOCAL, int NLB>
+__device__ __forceinline__ void post_sums(LoopShared &sh, const LoopArgs &r, int it, const int (&lbs)[NLB], int grid)
+{
     __syncthreads();
     if (threadIdx.x < kLoopRed) {
-        u64 *part = reinterpret_cast<u64 *>(r.part) + threadIdx.x * grid + lb;
-        double v = 0.0;
 #pragma unroll
-        for (int ww = 0; ww < kBlock / kWave; ++ww) v += sh.red[ww][threadIdx.x];
-        u64 b = __builtin_bit_cast(u64, v);
-        if (b == kEmpty) b ^= 1;                 // still a NaN
-        word_store<LOCAL>(part + (it & (kLoopSlots - 1)) * (kLoopRed * grid), b);
-        if (it > 0) word_store<LOCAL>(part + ((it + 2) & (kLoopSlots - 1)) * (kLoopRed * grid), kEmpty);
+        for (int l = 0; l < NLB; ++l) {
+            if (lbs[l] >= grid) continue;        // uniform
+            u64 *part = reinterpret_cast<u64 *>(r.part) + threadIdx.x * grid + lbs[l];
+            double v = 0.0;
+#pragma unroll
+            for (int ww = 0; ww < kBlock / kWave; ++ww) v += sh.red[l][ww][threadIdx.x];
+            u64 b = __builtin_bit_cast(u64, v);
+            if (b == kEmpty) b ^= 1;             // still a NaN
+            word_store<LOCAL>(part + (it & (kLoopSlots - 1)) * (kLoopRed * grid), b);
+            if (it > 0) word_store<LOCAL>(part + ((it + 2) & (kLoopSlots - 1)) * (kLoopRed * grid), kEmpty);
+        }
     }
 }
 
@@ -367,7 +378,7 @@ __device__ __forceinline__ bool loop_turn(LoopShared &sh, LoopState &L, const Lo
         }
         return on;
     }
-    const u64 *c = r.coef + (lb & (kCopies - 1)) * 8 + (lane & 7);
+    const u64 *c = r.coef + (blockIdx.x & (kCopies - 1)) * 8 + (lane & 7);
     u64 v;
     do v = word_load(c);
     while (__ballot((unsigned)(v >> 32) != tag) != 0ull && spin.more());
@@ -405,22 +416,24 @@ __device__ __forceinline__ void hide(V &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void hide_s(int &v) { asm volatile("" : "+s"(v)); }
 
 // ---------------------------------------------------------------- 2D
-// The tile of pass2d_kernel (Tile2D), TPW of them per workgroup: thread, row
-// and segment hold the same nodes. Slots past a periodic edge hold the image
+// The tile of pass2d_kernel (Tile2D), TPW of them per workgroup of that kernel,
+// LB such workgroups to one here: thread, row and segment hold the same nodes. Slots past a periodic edge hold the image
 // of the opposite edge; their u comes from the owner like a halo node's.
 // The FP64 field of the full tile sits in LDS (one word per node and thread,
 // touched once per pass), which leaves the registers of four waves per SIMD to
-// the rest of the state. With two tiles per workgroup that is still too much (z,
-// u, p and the bonds take 84 of a thread's 128 registers, and holding them all
-// spilled 50 words a pass): there the bonds come from memory in every pass,
-// 8 bytes of the plain pass's 39 per node and mostly from the L2, and are on
-// their way while the pass before waits for its sums.
+// the rest of the state. Networks with two tiles per workgroup fill the chip
+// (2048^2 mixed: 2,048 tiles): half as many workgroups of four tiles run at two
+// waves per SIMD, where the registers that every thread needs besides its
+// state are paid for half as often (at four waves 86 of them spilled, and a
+// pass took 32 us instead of the pass kernel's 34). Their bonds come from
+// memory in every pass, 8 bytes of the plain pass's 39 per node and mostly from
+// the L2; the first tile's are on their way while the pass before waits.
 // Exchange words of a tile: its first row, last row, first column, last column.
 template <typename T, int SHAPE>
 constexpr int edge_words2d() { return 2 * (Tile2D<T, SHAPE>::COLS + Tile2D<T, SHAPE>::ROWS); }
 
-template <typename T, int SHAPE, int TPW, bool LOCAL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void loop2d_kernel(
+template <typename T, int SHAPE, int TPW, bool LOCAL, int LB>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ? 2 : 4))) void loop2d_kernel(
     const PassArgs<T> *__restrict__ tab, Scalars *scal, int parity, int slot, LoopArgs r)
 {
     constexpr int TY = Tile2D<T, SHAPE>::TY, SEG = Tile2D<T, SHAPE>::SEG, NW = kBlock / kWave;
@@ -430,16 +443,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     constexpr bool kTight = SHAPE == 0;           // many nodes per thread: registers are scarce
     constexpr bool kFieldLds = kTight;
     constexpr bool kLean = TPW > 1;               // bonds from memory, halo addresses formed anew
+    constexpr int NT = TPW * LB;                  // tiles of this workgroup
     __shared__ T edge[2][NW][SEG][kWave];         // [0]: first row of each wave, [1]: last row
     __shared__ LoopShared sh;
-    __shared__ double fl[kFieldLds ? TPW * SEG * TY : 1][kBlock];
+    __shared__ double fl[kFieldLds ? NT * SEG * TY : 1][kBlock];
     const PassArgs<T> &a = tab[2 * slot + parity];
     Scalars *s = scal + slot;
     const int grid = a.grid, lb = loop_place<LOCAL>(r, grid);
     if (lb < 0 || s->mode != MODE_CG) return;
     int lane = threadIdx.x & (kWave - 1);
     const int w = rfl((int)threadIdx.x / kWave);
-    const int first = xcd_remap(lb, grid);
+    // workgroups of the pass kernel that this one stands for, all of its XCD
+    int lbs[LB];
+#pragma unroll
+    for (int l = 0; l < LB; ++l) lbs[l] = LB == 1 ? lb : (lb & 7) + 8 * ((lb >> 3) * LB + l);
+    auto tile_of = [&](int t) {
+        const int b = lbs[t / TPW];
+        return b < grid ? xcd_remap(b, grid) + t % TPW * grid : a.ntiles;
+    };
     const int nx = a.nx, ny = a.ny, ntx = a.ntx, nty = a.nty, wrap = a.wrap;
     const bool wx = wrap & 1, wy = (wrap >> 1) & 1;
     const bool jacobi = a.jacobi != 0, xaxis = a.axis == 0;
@@ -450,12 +471,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     auto rowm = [&](int yy) { return yy >= 0 && yy < ny ? yy : (wy && yy == ny ? 0 : (wy && yy == -1 ? ny - 1 : -1)); };
 
     // ---- state of the tiles
-    T z_[TPW][SEG][TY], u_[TPW][SEG][TY], p_[TPW][SEG][TY], gxv[TPW][SEG][TY], gyv[TPW][SEG][TY + 1];
-    double Pv[kFieldLds ? 1 : TPW][SEG][TY];
-    T ez[TPW][SEG], eu[TPW][SEG], ep[TPW][SEG];    // halo row of the first / last wave
-    T hz[TPW], hu[TPW], hp[TPW], hg[TPW];          // halo column node of this lane
+    T z_[NT][SEG][TY], u_[NT][SEG][TY], p_[NT][SEG][TY], gxv[NT][SEG][TY], gyv[NT][SEG][TY + 1];
+    double Pv[kFieldLds ? 1 : NT][SEG][TY];
+    T ez[NT][SEG], eu[NT][SEG], ep[NT][SEG];    // halo row of the first / last wave
+    T hz[NT], hu[NT], hp[NT], hg[NT];        // halo column node of this lane
     unsigned liv = 0;                              // bits (tile, segment, row): interior nodes of the lattice
-    int tx_[TPW], ty_[TPW];                        // tile coordinates; past the lattice: no tile
+    int tx_[NT], ty_[NT];                        // tile coordinates; past the lattice: no tile
     auto bit = [&](int t, int sg, int j) { return 1u << ((t * SEG + sg) * TY + j); };
     auto colx = [&](int t, int sg) { return tx_[t] * COLS + kWave * sg + lane; };
     auto rowy = [&](int t, int j) { return ty_[t] * ROWS + w * TY + j; };
@@ -503,10 +524,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const int ex = hleft() ? (tx_[t] > 0 ? tx_[t] : ntx) - 1 : (tx_[t] + 1 < ntx ? tx_[t] + 1 : 0);
         return (unsigned)((ty_[t] * ntx + ex) * EW + (hleft() ? kRight : kLeft) + w * TY + hrow()) * 8u;
     };
-    unsigned ro[TPW][SEG], co[TPW];
+    unsigned ro[NT][SEG], co[NT];
 #pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-        const int tile = first + t * grid;
+    for (int t = 0; t < NT; ++t) {
+        const int tile = tile_of(t);
         const bool has = tile < a.ntiles;
         tx_[t] = has ? tile % ntx : ntx + 1;
         ty_[t] = has ? tile / ntx : nty + 1;
@@ -554,7 +575,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
     }
     LoopState L;
-    const bool admitted = loop_begin<LOCAL>(sh, L, s, r, lb, grid);
+    const bool admitted = loop_begin<LOCAL>(sh, L, s, r, lbs, LB, grid);
 
     int it = 0;
     for (bool on = admitted; on; ++it) {
@@ -565,7 +586,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         u64 *xb = r.xch + (size_t)(it & 1) * r.xch_slot;     // this pass's edge values
         if constexpr (kTight) {
 #pragma unroll
-            for (int t = 0; t < TPW; ++t) {
+            for (int t = 0; t < NT; ++t) {
 #pragma unroll
                 for (int sg = 0; !kLean && sg < SEG; ++sg) {
 #pragma unroll
@@ -584,7 +605,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
         // z' and p' of the halo
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
+        for (int t = 0; t < NT; ++t) {
 #pragma unroll
             for (int sg = 0; sg < SEG; ++sg) {
                 ez[t][sg] = step_z(ez[t][sg], alpha, eu[t][sg]);
@@ -595,9 +616,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
         // the pending step, then z' and p' of the tiles: after this u is free
 #pragma unroll
-        for (int t = 0; t < TPW; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int sg = 0; sg < SEG; ++sg)
+            for (int sg = 0; sg < SEG; ++sg) {
 #pragma unroll
                 for (int j = 0; j < TY; ++j) {
                     if (sa != 0.0) {
@@ -611,11 +632,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     const T zc = step_z(z_[t][sg][j], alpha, u_[t][sg][j]);
                     z_[t][sg][j] = zc;
                     p_[t][sg][j] = step_p(zc, beta, p_[t][sg][j]);
-                    if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
                 }
-        double acc[kLoopRed] = {0.0, 0.0, 0.0, 0.0};
+                if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
+            }
+        double acc[kLoopRed];
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
+        for (int t = 0; t < NT; ++t) {
+            if (t % TPW == 0) acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
             if (t > 0) __syncthreads();            // the previous tile's LDS rows are reused
             if (kLean && t > 0) load_bonds(t);
 #pragma unroll
@@ -671,13 +694,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 // temporaries at once (four waves per SIMD hide the latency)
                 if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
             }
+            if (LB > 1 && t % TPW == TPW - 1) wave_sums(sh.red[t / TPW], acc);
         }
         if (w == 0) __builtin_amdgcn_s_waitcnt(0);   // what the last pass emptied is empty (wave 0 posts the sums)
         // u of the tiles' edges: rows as they lie, the columns gathered into
         // lanes 0 .. 2 TY - 1
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-            const int tile = first + t * grid;
+        for (int t = 0; t < NT; ++t) {
+            const int tile = tile_of(t);
             if (tile >= a.ntiles) continue;        // uniform
             u64 *xt = xb + (size_t)tile * EW;
             const int jb = min(ty_[t] * ROWS + ROWS, ny) - 1 - rowy(t, 0);    // last lattice row, if in this wave
@@ -702,15 +726,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             if (lane < 2 * TY && rowy(t, lane < TY ? lane : lane - TY) < ny)
                 Packed<T>::template post<LOCAL>(at(xt, (unsigned)((lane < TY ? kLeft + lane : kRight + lane - TY) + w * TY) * 8u), E, tag, cv);
         }
-        post_sums<LOCAL>(sh, acc, r, it, lb, grid);
+        if constexpr (LB == 1) wave_sums(sh.red[0], acc);    // the edges are on their way
+        post_sums<LOCAL>(sh, r, it, lbs, grid);
         // u of the halo and the images, from their owners (before the sums,
         // whose way is longer)
-        Packed<T> ew[TPW][SEG], hw[TPW];
+        Packed<T> ew[NT][SEG], hw[NT];
         bool missing;
         do {
             missing = false;
 #pragma unroll
-            for (int t = 0; t < TPW; ++t) {
+            for (int t = 0; t < NT; ++t) {
 #pragma unroll
                 for (int sg = 0; sg < SEG; ++sg) {
                     if constexpr (kLean) ro[t][sg] = row_words(t, sg);
@@ -722,14 +747,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 else hw[t].zero(tag);
             }
 #pragma unroll
-            for (int t = 0; t < TPW; ++t) {
+            for (int t = 0; t < NT; ++t) {
 #pragma unroll
                 for (int sg = 0; sg < SEG; ++sg) missing |= !ew[t][sg].here(tag);
                 missing |= !hw[t].here(tag);
             }
         } while (missing && spin.more());
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
+        for (int t = 0; t < NT; ++t) {
 #pragma unroll
             for (int sg = 0; sg < SEG; ++sg) {
                 eu[t][sg] = ew[t][sg].value();
@@ -761,7 +786,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const int64_t done = passes0 + it - 1;
     T *pd = a.pbuf[a.npbuf == 5 ? (int)(done % 5) : (int)(done % 3)];
 #pragma unroll
-    for (int t = 0; t < TPW; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int sg = 0; sg < SEG; ++sg)
 #pragma unroll
@@ -951,7 +976,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
         gq[j] = ok && higok ? p2 : T(0);
     }
     LoopState L;
-    const bool admitted = loop_begin<false>(sh, L, s, r, lb, grid);
+    const int lbs[1] = {lb};
+    const bool admitted = loop_begin<false>(sh, L, s, r, lbs, 1, grid);
 
     int it = 0;
     for (bool on = admitted; on; ++it) {
@@ -1068,7 +1094,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
             if (e < cnt * R && yw + row < ny)
                 Packed<T>::template post<false>(at(xt, (unsigned)((lane < 32 ? kLeft : kRight) + q * kTY + w * R + row) * 8u), E, tag, cv);
         }
-        post_sums<false>(sh, acc, r, it, lb, grid);
+        wave_sums(sh.red[0], acc);
+        post_sums<false>(sh, r, it, lbs, grid);
         // u of the halo, from its owners
         Packed<T> lw[R], gw[R], hw[TZ];
         bool missing;
@@ -1147,15 +1174,18 @@ template <typename T>
 static const void *loop_kernel(int dim, int tpw, int tile_z, bool local)
 {
     if (dim == -2 && tpw == 1)
-        return local ? reinterpret_cast<const void *>(&loop2d_kernel<T, 1, 1, true>)
-                     : reinterpret_cast<const void *>(&loop2d_kernel<T, 1, 1, false>);
+        return local ? reinterpret_cast<const void *>(&loop2d_kernel<T, 1, 1, true, 1>)
+                     : reinterpret_cast<const void *>(&loop2d_kernel<T, 1, 1, false, 1>);
     if (local) return nullptr;
     if (dim == 3 && tile_z == 2) return reinterpret_cast<const void *>(&loop3d_kernel<T, 2>);
     if (dim == 3 && tile_z == 4) return reinterpret_cast<const void *>(&loop3d_kernel<T, 4>);
-    if (dim == 2 && tpw == 1) return reinterpret_cast<const void *>(&loop2d_kernel<T, 0, 1, false>);
-    if (dim == 2 && tpw == 2) return reinterpret_cast<const void *>(&loop2d_kernel<T, 0, 2, false>);
+    if (dim == 2 && tpw == 1) return reinterpret_cast<const void *>(&loop2d_kernel<T, 0, 1, false, 1>);
+    if (dim == 2 && tpw == 2) return reinterpret_cast<const void *>(&loop2d_kernel<T, 0, 2, false, 2>);
     return nullptr;
 }
+
+// workgroups of the pass kernel that a workgroup of the loop stands for
+static int loop_per_group(int dim, int tpw) { return dim == 2 && tpw == 2 ? 2 : 1; }
 
 template <typename T>
 hipError_t loop_capacity(int dim, int tpw, int tile_z, bool local, int *cap)
@@ -1168,7 +1198,7 @@ hipError_t loop_capacity(int dim, int tpw, int tile_z, bool local, int *cap)
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, kBlock, 0);
     if (e != hipSuccess) return e;
-    *cap = local ? std::min(per * cus / 8, kLoopLocalMax) : std::min(per * cus, kLoopGridMax);
+    *cap = local ? std::min(per * cus / 8, kLoopLocalMax) : std::min(per * cus * loop_per_group(dim, tpw), kLoopGridMax);
     return hipSuccess;
 }
 
@@ -1187,7 +1217,9 @@ hipError_t launch_loop(int dim, int tpw, int tile_z, bool local, int grid, const
     if (!k || grid < 1 || grid > kLoopGridMax) return hipErrorInvalidValue;
     LoopArgs args = r;
     void *p[] = {(void *)&tab, (void *)&scal, (void *)&parity, (void *)&slot, (void *)&args};
-    return hipLaunchKernel(k, dim3((unsigned)(local ? 8 * grid : grid)), dim3(kBlock), p, 0, st);
+    const int per = loop_per_group(dim, tpw);
+    const int launched = local ? 8 * grid : 8 * div_up(grid / 8, per);     // grid is a multiple of 8
+    return hipLaunchKernel(k, dim3((unsigned)launched), dim3(kBlock), p, 0, st);
 }
 
 template size_t loop_exchange_words<float>(int, int, int);
