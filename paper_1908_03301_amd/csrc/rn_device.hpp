@@ -225,13 +225,21 @@ hipError_t launch_pass_persist(int dim, int coh, const PassArgs<T> *tab, const u
                                Scalars *scal, int nblocks, int64_t round_base, int rounds, int slot, unsigned *err,
                                unsigned long long *queues, hipStream_t st);
 
-// Resident CG loop (rn_loop.hpp): one launch runs up to `limit` CG passes of
-// the one network in `slot`, with its state in registers. `dim` as for
-// launch_pass; tpw and tile_z are the network's. *gate (three words, zero before
-// the launch) admits the workgroups; gate_clear is another launch's gate, to be
-// cleared; part holds loop_part_bytes(); xch two slots of xch_slot words and
-// coef kLoopCoefBytes, both only ever written by these loops, with pass numbers
-// that start at 0 here and do not repeat: a launch uses tag0 .. tag0 + limit - 1.
+// Resident CG loops (rn_loop.hpp): one launch runs up to `limit` CG passes of
+// the one network in `slot`, or of every network of the table `blk`, with their
+// state in registers. `dim` as for launch_pass; tpw and tile_z are the
+// networks'. Entry blk[b] = (network, member << 16 | block of the network),
+// members numbered from 0, each network's blocks in order from a multiple of 8.
+// gate: kLoopMembers gates of kLoopGateWords words, zero before the launch, a
+// member's workgroups admitted by its own; gate_clear: another launch's, to be
+// cleared. part holds loop_part_bytes(), a member's from its first workgroup
+// (net[member].block0, counted as the pass kernel's); xch two slots of xch_slot
+// words, a member's from net[member].xch; coef kLoopCoefBytes a member. xch and
+// coef are only ever written by these loops, with pass numbers that start at 0
+// here and do not repeat: a launch uses tag0 .. tag0 + limit - 1.
+struct LoopNet {
+    unsigned block0, xch;
+};
 struct LoopArgs {
     unsigned *gate;
     unsigned *gate_clear;
@@ -240,22 +248,28 @@ struct LoopArgs {
     size_t xch_slot;
     unsigned tag0;
     int limit;
+    const uint2 *blk;        // nullptr: one network
+    const LoopNet *net;
 };
+constexpr int kLoopMembers = 64, kLoopGateWords = 16;
 constexpr size_t kLoopCoefBytes = 2048;
 constexpr int kLoopRed = 4;             // sums that the CG step uses
 constexpr int kLoopSlots = 4;           // slots of the exchange between workgroups
 constexpr int kLoopLocalMax = 32;       // ... of one on a single XCD
 constexpr int kLoopGridMax = 1024;      // workgroups of a resident loop
 inline size_t loop_part_bytes() { return (size_t)kLoopSlots * kLoopRed * kLoopGridMax * sizeof(double); }
-// workgroups of this shape that the device (one XCD of it: local) holds at once
-// (0: no loop kernel for it)
+// workgroups of this shape's loop that the device (one XCD of it: local) holds
+// at once (0: no loop kernel for it)
 template <typename T>
 hipError_t loop_capacity(int dim, int tpw, int tile_z, bool local, int *cap);
 // words of one exchange slot of a network of `ntiles` tiles
+// workgroups that a loop launches for a network of `grid` workgroups
+int loop_blocks(int dim, int tpw, int grid);
+// `blocks`: of the one network (its grid when local), or of the whole table
 template <typename T>
 size_t loop_exchange_words(int dim, int tile_z, int ntiles);
 template <typename T>
-hipError_t launch_loop(int dim, int tpw, int tile_z, bool local, int grid, const PassArgs<T> *tab, Scalars *scal, int parity,
+hipError_t launch_loop(int dim, int tpw, int tile_z, bool local, int blocks, const PassArgs<T> *tab, Scalars *scal, int parity,
                        int slot, const LoopArgs &r, hipStream_t st);
 
 // tile geometry of the pass kernels: a 2D workgroup tile is 64 kSEG2f x

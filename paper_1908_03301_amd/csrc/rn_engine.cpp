@@ -437,7 +437,9 @@ int Engine::init(hipStream_t st, std::string *err)
     ENG_TRY(hipMalloc(&d_gate_, kGates * kGateBytes));
     ENG_TRY(hipMemset(d_gate_, 0, kGates * kGateBytes));
     ENG_TRY(hipMalloc(&d_lpart_, loop_part_bytes()));
-    ENG_TRY(hipMalloc(&d_coef_, kLoopCoefBytes));
+    ENG_TRY(hipMalloc(&d_coef_, kLoopMembers * kLoopCoefBytes));
+    ENG_TRY(hipMalloc(&d_gang_, sizeof(GangTables)));
+    ENG_TRY(hipHostMalloc((void **)&h_gang_, 2 * sizeof(GangTables), hipHostMallocDefault));
     ENG_TRY(hipMalloc(&d_err_, 256));
     ENG_TRY(hipMemset(d_err_, 0, 256));
     ENG_TRY(hipHostMalloc((void **)&h_err_, 256, hipHostMallocDefault));
@@ -471,6 +473,9 @@ void Engine::destroy()
     (void)hipFree(d_gate_);
     (void)hipFree(d_lpart_);
     (void)hipFree(d_coef_);
+    (void)hipFree(d_gang_);
+    (void)hipHostFree(h_gang_);
+    d_gang_ = h_gang_ = nullptr;
     (void)hipFree(d_xch_);
     d_coef_ = d_xch_ = nullptr;
     xch_cap_ = 0;
@@ -840,14 +845,13 @@ int Engine::launch_persistent(int rounds, hipStream_t st, std::string *err)
     return launch_rounds(rounds, st, err);
 }
 
-// Whether a network that iterates alone runs in a resident loop: its
-// workgroups all have to fit the chip at once. Below that size a pass is bound
+// Whether a network runs in resident loops: its workgroups all have to fit the
+// chip at once. Below that size a pass is bound
 // by its chain of round trips, and every shape that fits is faster there. Whole
 // solves over their iterations, one launch per pass against the loop: 128^2
 // mixed 9.0 -> 3.6 us, 201 x 150 FP64 9.1 -> 3.9, 512^2 FP64 10.9 -> 5.1,
 // 1024^2 mixed 16.0 -> 6.4, 1024^2 FP64 21.0 -> 8.0, 2048^2 mixed 34.1 -> 18.3.
-// Several networks share launches instead.
-int Engine::loop_fits(Net *net, bool *fits, std::string *err)
+int Engine::loop_fits(Net *net, bool alone, bool *fits, std::string *err)
 {
     *fits = false;
     if (persist_ || use_graph_ || !net->loop_ok) return RN_OK;
@@ -855,16 +859,170 @@ int Engine::loop_fits(Net *net, bool *fits, std::string *err)
     if (tpw < 1 || tpw > kLoopTpw) return RN_OK;
     const int tz = net->L.dim == 3 ? net->L.tile_z : 0;
     if (tz >= kLoopTz) return RN_OK;
-    for (int local = 1; local >= 0 && !*fits; --local) {
+    for (int local = alone ? 1 : 0; local >= 0 && !*fits; --local) {
         int &cap = loop_cap_[k][tpw - 1][tz][local];
         if (cap < 0) {
             if (kind_fp64(k)) ENG_TRY(loop_capacity<double>(kind_dim(k), tpw, tz, local != 0, &cap));
             else ENG_TRY(loop_capacity<float>(kind_dim(k), tpw, tz, local != 0, &cap));
         }
-        *fits = net->L.grid <= cap;
+        *fits = (local ? net->L.grid : loop_blocks(kind_dim(k), tpw, net->L.grid)) <= cap;
         net->loop_local = *fits && local;
     }
     return RN_OK;
+}
+
+// Words of one exchange slot of a network in resident loops.
+size_t Engine::loop_words(const Net *net) const
+{
+    const int k = net->kind, tz = net->L.dim == 3 ? net->L.tile_z : 0;
+    return kind_fp64(k) ? loop_exchange_words<double>(kind_dim(k), tz, net->L.ntiles)
+                        : loop_exchange_words<float>(kind_dim(k), tz, net->L.ntiles);
+}
+
+// Exchange memory of two slots of `words` words. It holds nothing but tagged
+// words: zero (no tag) when it is new and before the tags would start over.
+int Engine::loop_memory(size_t words, hipStream_t st, std::string *err)
+{
+    const bool grow = 2 * words > xch_cap_, over = loop_tag_ > 0xf0000000u;
+    if (grow) {
+        if (d_xch_) ENG_TRY(hipStreamSynchronize(st));
+        (void)hipFree(d_xch_);
+        d_xch_ = nullptr;
+        xch_cap_ = 0;
+        const size_t cap = std::max<size_t>(2 * words, (size_t)1 << 18);
+        ENG_TRY(hipMalloc(&d_xch_, cap * sizeof(unsigned long long)));
+        xch_cap_ = cap;
+    }
+    if (grow || over) {
+        ENG_TRY(launch_clear_u64(d_xch_, (int)xch_cap_, st));
+        ENG_TRY(launch_clear_u64(d_coef_, (int)(kLoopMembers * kLoopCoefBytes / sizeof(unsigned long long)), st));
+        if (over) loop_tag_ = 1;
+    }
+    return RN_OK;
+}
+
+// Arguments of the next loop launch: its gates (kGates sets in turn) and tags.
+LoopArgs Engine::loop_args(size_t words, int limit)
+{
+    LoopArgs a;
+    a.gate = (unsigned *)(d_gate_ + kGateBytes * gate_);
+    a.gate_clear = (unsigned *)(d_gate_ + kGateBytes * ((gate_ + kGates / 2) % kGates));
+    gate_ = (gate_ + 1) % kGates;
+    a.part = d_lpart_;
+    a.xch = d_xch_;
+    a.coef = d_coef_;
+    a.xch_slot = words;
+    a.tag0 = loop_tag_;
+    loop_tag_ += (unsigned)limit;
+    a.limit = limit;
+    a.blk = nullptr;
+    a.net = nullptr;
+    return a;
+}
+
+// A chunk of several networks that all fit resident loops, those of one shape
+// (kernel) together. Of each shape as many networks as the chip holds run at
+// once, taken in turn from the active list, chunk by chunk; the others wait.
+// (All of them in one launch per pass is bound by its bytes or by its tail,
+// see launch_rounds; a batch of 48 networks of 64^2 to 1024^2 and 32^3 to 128^3
+// took 579 ms that way.) A cycle is a pass of every network (a refresh where
+// one is due) and a loop of up to kGangLimit passes: networks that reach a
+// refresh earlier wait for the others, hence the small limit. The rounds of a
+// chunk are even in number, so the parities of waiting networks stay right.
+int Engine::launch_gangs(int *launched, hipStream_t st, std::string *err)
+{
+    struct Gang {
+        int kind, tpw, tz;
+        std::vector<Net *> nets;
+        size_t words = 0;
+        int pass0 = 0, npass = 0, loop0 = 0, nloop = 0, net0 = 0;
+    };
+    std::vector<Gang> gangs;
+    for (Net *n : active_) {
+        const int tz = n->L.dim == 3 ? n->L.tile_z : 0;
+        Gang *g = nullptr;
+        for (Gang &q : gangs)
+            if (q.kind == n->kind && q.tpw == n->L.tpw && q.tz == tz) g = &q;
+        if (!g) {
+            gangs.push_back({n->kind, n->L.tpw, tz, {}});
+            g = &gangs.back();
+        }
+        g->nets.push_back(n);
+    }
+    half_ ^= 1;
+    GangTables *h = h_gang_ + half_;
+    size_t most = 0;
+    int np = 0, nl = 0, nn = 0;
+    for (Gang &g : gangs) {
+        // the ones that have waited longest first (a stable order otherwise)
+        std::stable_sort(g.nets.begin(), g.nets.end(),
+                         [](const Net *a, const Net *b) { return a->gang_seq < b->gang_seq; });
+        const int cap = loop_cap_[g.kind][g.tpw - 1][g.tz][0], dim = kind_dim(g.kind);
+        std::vector<Net *> in;
+        int blocks = 0;
+        for (Net *n : g.nets) {
+            const int m = loop_blocks(dim, n->L.tpw, n->L.grid);
+            if (blocks + m > cap || (int)in.size() == kLoopMembers) continue;
+            in.push_back(n);
+            blocks += m;
+        }
+        g.nets.swap(in);
+        g.pass0 = np;
+        g.loop0 = nl;
+        g.net0 = nn;
+        int member = 0, block0 = 0;
+        for (Net *n : g.nets) {
+            n->gang_seq = chunk_seq_ + 1;
+            n->loop_used = true;
+            for (int b = 0; b < n->L.grid; ++b) h->pass[np++] = make_uint2((unsigned)n->slot, (unsigned)b);
+            const int m = loop_blocks(dim, n->L.tpw, n->L.grid);
+            for (int b = 0; b < m; ++b) h->loop[nl++] = make_uint2((unsigned)n->slot, (unsigned)(member << 16 | b));
+            h->net[nn++] = LoopNet{(unsigned)block0, (unsigned)g.words};
+            g.words += loop_words(n);
+            block0 += n->L.grid;
+            ++member;
+        }
+        g.npass = block0;
+        g.nloop = blocks;
+        most = std::max(most, g.words);
+    }
+    int r = loop_memory(most, st, err);
+    if (r) return r;
+    ENG_TRY(hipMemcpyAsync(d_gang_, h, sizeof(GangTables), hipMemcpyHostToDevice, st));
+    recording_ = timing_;
+    tmirror_ = next_mirror_;
+    if (recording_) r = record_timing(-1, st, err);
+    for (int c = 0; c < kGangCycles && !r; ++c)
+        for (int loop = 0; loop < 2 && !r; ++loop) {
+            const int par = (int)(rounds_ & 1);
+            for (const Gang &g : gangs) {
+                const int dim = kind_dim(g.kind);
+                hipError_t e;
+                if (loop) {
+                    LoopArgs a = loop_args(g.words, kGangLimit);
+                    a.blk = d_gang_->loop + g.loop0;
+                    a.net = d_gang_->net + g.net0;
+                    e = kind_fp64(g.kind)
+                            ? launch_loop<double>(dim, g.tpw, g.tz, false, g.nloop, d_tabd_, d_scal_, par, -1, a, st)
+                            : launch_loop<float>(dim, g.tpw, g.tz, false, g.nloop, d_tabf_, d_scal_, par, -1, a, st);
+                } else {
+                    const uint2 *blk = d_gang_->pass + g.pass0;
+                    e = kind_fp64(g.kind) ? launch_pass<double>(dim, d_tabd_, blk, d_scal_, g.npass, par, -1, st)
+                                          : launch_pass<float>(dim, d_tabf_, blk, d_scal_, g.npass, par, -1, st);
+                }
+                if (e != hipSuccess) {
+                    if (err) *err = std::string("resident loops: ") + hipGetErrorString(e);
+                    r = RN_EDEVICE;
+                    break;
+                }
+                ++launches_;
+                if (recording_ && (r = record_timing(g.kind, st, err))) break;
+            }
+            ++rounds_;
+        }
+    recording_ = false;
+    *launched = 2 * kGangCycles;
+    return r;
 }
 
 // A chunk of a network in resident loops: each loop runs CG passes until the
@@ -883,43 +1041,21 @@ int Engine::launch_loops(Net *net, int *launched, hipStream_t st, std::string *e
             return r;
         }
     }
-    // the exchange memory holds nothing but tagged words: zero (no tag) when it
-    // is new and before the tags would start over
     const int tz = net->L.dim == 3 ? net->L.tile_z : 0;
-    const size_t xch_words = kind_fp64(k) ? loop_exchange_words<double>(dim, tz, net->L.ntiles)
-                                          : loop_exchange_words<float>(dim, tz, net->L.ntiles);
-    const bool grow = 2 * xch_words > xch_cap_, over = loop_tag_ > 0xf0000000u;
-    if (grow) {
-        if (d_xch_) ENG_TRY(hipStreamSynchronize(st));
-        (void)hipFree(d_xch_);
-        d_xch_ = nullptr;
-        xch_cap_ = 0;
-        const size_t cap = std::max<size_t>(2 * xch_words, (size_t)1 << 18);
-        ENG_TRY(hipMalloc(&d_xch_, cap * sizeof(unsigned long long)));
-        xch_cap_ = cap;
-    }
-    if (grow || over) {
-        ENG_TRY(launch_clear_u64(d_xch_, (int)xch_cap_, st));
-        ENG_TRY(launch_clear_u64(d_coef_, (int)(kLoopCoefBytes / sizeof(unsigned long long)), st));
-        if (over) loop_tag_ = 1;
+    const size_t words = loop_words(net);
+    int r = loop_memory(words, st, err);
+    if (r) {
+        recording_ = false;
+        return r;
     }
     int n = 0;
     auto one = [&](bool loop) -> int {
         const int par = (int)(rounds_ & 1);
         if (loop) {
-            LoopArgs a;
-            a.gate = (unsigned *)(d_gate_ + kGateBytes * gate_);
-            a.gate_clear = (unsigned *)(d_gate_ + kGateBytes * ((gate_ + kGates / 2) % kGates));
-            a.part = d_lpart_;
-            a.xch = d_xch_;
-            a.coef = d_coef_;
-            a.xch_slot = xch_words;
-            a.tag0 = loop_tag_;
-            loop_tag_ += kLoopLimit;
-            a.limit = kLoopLimit;
-            gate_ = (gate_ + 1) % kGates;
-            if (!kind_fp64(k)) ENG_TRY(launch_loop<float>(dim, net->L.tpw, tz, net->loop_local, net->L.grid, d_tabf_, d_scal_, par, slot, a, st));
-            else ENG_TRY(launch_loop<double>(dim, net->L.tpw, tz, net->loop_local, net->L.grid, d_tabd_, d_scal_, par, slot, a, st));
+            const LoopArgs a = loop_args(words, kLoopLimit);
+            const int blocks = net->loop_local ? net->L.grid : loop_blocks(dim, net->L.tpw, net->L.grid);
+            if (!kind_fp64(k)) ENG_TRY(launch_loop<float>(dim, net->L.tpw, tz, net->loop_local, blocks, d_tabf_, d_scal_, par, slot, a, st));
+            else ENG_TRY(launch_loop<double>(dim, net->L.tpw, tz, net->loop_local, blocks, d_tabd_, d_scal_, par, slot, a, st));
         } else if (!kind_fp64(k)) {
             ENG_TRY(launch_pass<float>(dim, d_tabf_, nullptr, d_scal_, net->L.grid, par, slot, st));
         } else {
@@ -930,7 +1066,6 @@ int Engine::launch_loops(Net *net, int *launched, hipStream_t st, std::string *e
         ++n;
         return recording_ ? record_timing(k, st, err) : RN_OK;
     };
-    int r = RN_OK;
     if (!net->loop_used) r = one(false);
     for (int i = 0; i < kLoopsPerChunk && !r; ++i) {
         r = one(false);
@@ -967,25 +1102,24 @@ int Engine::capture(hipStream_t st, std::string *err)
 int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
 {
     if (active_.empty()) return RN_OK;
+    peak_active_ = std::max(peak_active_, (int)active_.size());
+    tkind_[next_mirror_].clear();
+    bool fits = !persist_ && !use_graph_;
+    for (size_t i = 0; i < active_.size() && fits; ++i) {
+        int r = loop_fits(active_[i], active_.size() == 1, &fits, err);
+        if (r) return r;
+    }
+    if (fits) {
+        int launched = 0;
+        int r = active_.size() == 1 ? launch_loops(active_[0], &launched, st, err) : launch_gangs(&launched, st, err);
+        return r ? r : queue_status(launched, st, err);
+    }
     if (dirty_) {
         int r = rebuild(st, err);
         if (r) return r;
         if (gexec_) {
             (void)hipGraphExecDestroy(gexec_);
             gexec_ = nullptr;
-        }
-    }
-    peak_active_ = std::max(peak_active_, (int)active_.size());
-    tkind_[next_mirror_].clear();
-    if (active_.size() == 1) {
-        bool fits = false;
-        int r = loop_fits(active_[0], &fits, err);
-        if (r) return r;
-        if (fits) {
-            int launched = 0;
-            r = launch_loops(active_[0], &launched, st, err);
-            if (r) return r;
-            return queue_status(launched, st, err);
         }
     }
     if (use_graph_ && rounds >= kGraphRounds) {

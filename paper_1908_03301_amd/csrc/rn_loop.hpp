@@ -171,20 +171,37 @@ __device__ __forceinline__ int pass_gate(unsigned *gate, unsigned grid, Scalars 
     return state == kGateGo;
 }
 
-// The place of this workgroup in the network's grid, -1: none. One launch per
-// place, or (LOCAL) per place and XCD, those on XCD 0 counting themselves in.
+// This workgroup's network and its place in it, -1: none. One workgroup is
+// launched per place, or (LOCAL) per place and XCD, those on XCD 0 counting
+// themselves in. r: the launch's arguments, made this network's.
+struct Place {
+    int slot, lb;
+};
+
 template <bool LOCAL>
-__device__ __forceinline__ int loop_place(const LoopArgs &r, int grid)
+__device__ __forceinline__ Place loop_place(LoopArgs &r, int slot)
 {
-    if (blockIdx.x == 0 && threadIdx.x < 3) r.gate_clear[threadIdx.x] = 0u;
-    if constexpr (!LOCAL) return (int)blockIdx.x;
-    __shared__ int place;
-    if (__builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20)) & 7) return -1;   // XCC_ID
-    if (threadIdx.x == 0)
-        place = (int)__hip_atomic_fetch_add(r.gate + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    const int lb = __builtin_amdgcn_readfirstlane(place);
-    return lb < grid ? lb : -1;
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < 3 * kLoopMembers; i += kBlock) r.gate_clear[i / 3 * kLoopGateWords + i % 3] = 0u;
+    Place p = {slot, (int)blockIdx.x};
+    if constexpr (LOCAL) {
+        __shared__ int place;
+        if (__builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20)) & 7) return {slot, -1};   // XCC_ID
+        if (threadIdx.x == 0)
+            place = (int)__hip_atomic_fetch_add(r.gate + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        p.lb = __builtin_amdgcn_readfirstlane(place);
+    } else if (r.blk) {
+        const uint2 e = r.blk[blockIdx.x];
+        const unsigned m = e.y >> 16;
+        p.slot = (int)e.x;
+        p.lb = (int)(e.y & 0xffffu);
+        r.gate += m * kLoopGateWords;
+        r.coef += m * (kLoopCoefBytes / sizeof(u64));
+        r.part += r.net[m].block0 * (kLoopSlots * kLoopRed);
+        r.xch += r.net[m].xch;
+    }
+    return p;
 }
 
 // LDS of the loop's control, the same for every tile family.
@@ -218,7 +235,7 @@ __device__ __forceinline__ bool loop_begin(LoopShared &sh, LoopState &L, Scalars
     L.sa = s->sigma * s->alpha;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, LOCAL ? (unsigned)grid : gridDim.x, s);
+    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, (unsigned)(8 * div_up(grid >> 3, nlb)), s);
     __syncthreads();
     return sh.go != 0;
 }
@@ -378,7 +395,7 @@ __device__ __forceinline__ bool loop_turn(LoopShared &sh, LoopState &L, const Lo
         }
         return on;
     }
-    const u64 *c = r.coef + (blockIdx.x & (kCopies - 1)) * 8 + (lane & 7);
+    const u64 *c = r.coef + (lb & (kCopies - 1)) * 8 + (lane & 7);
     u64 v;
     do v = word_load(c);
     while (__ballot((unsigned)(v >> 32) != tag) != 0ull && spin.more());
@@ -447,10 +464,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
     __shared__ T edge[2][NW][SEG][kWave];         // [0]: first row of each wave, [1]: last row
     __shared__ LoopShared sh;
     __shared__ double fl[kFieldLds ? NT * SEG * TY : 1][kBlock];
-    const PassArgs<T> &a = tab[2 * slot + parity];
-    Scalars *s = scal + slot;
-    const int grid = a.grid, lb = loop_place<LOCAL>(r, grid);
-    if (lb < 0 || s->mode != MODE_CG) return;
+    const Place at_ = loop_place<LOCAL>(r, slot);
+    if (at_.lb < 0) return;
+    const PassArgs<T> &a = tab[2 * at_.slot + parity];
+    Scalars *s = scal + at_.slot;
+    const int grid = a.grid, lb = at_.lb;
+    if (lb >= grid || s->mode != MODE_CG) return;
     int lane = threadIdx.x & (kWave - 1);
     const int w = rfl((int)threadIdx.x / kWave);
     // workgroups of the pass kernel that this one stands for, all of its XCD
@@ -829,10 +848,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     __shared__ T lp[TZ][kTY + 2][kTX + 2];
     __shared__ double fl[TZ * R][kBlock];
     __shared__ LoopShared sh;
-    const PassArgs<T> &a = tab[2 * slot + parity];
-    Scalars *s = scal + slot;
-    const int grid = a.grid, lb = loop_place<false>(r, grid);
-    if (lb < 0 || s->mode != MODE_CG) return;
+    const Place at_ = loop_place<false>(r, slot);
+    if (at_.lb < 0) return;
+    const PassArgs<T> &a = tab[2 * at_.slot + parity];
+    Scalars *s = scal + at_.slot;
+    const int grid = a.grid, lb = at_.lb;
+    if (s->mode != MODE_CG) return;
     int lane = threadIdx.x & (kWave - 1);
     const int w = rfl((int)threadIdx.x / kWave);
     const int tile = xcd_remap(lb, grid);
@@ -1079,9 +1100,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
                 for (int j = 0; j < R; ++j) {
                     const T uv = u_[q][j];
                     if (own >> j & 1u) {
-                        const unsigned at_ = (unsigned)((w * R + j) * kTX + lane) * 8u;
-                        if (q == 0) Packed<T>::template post<false>(at(xt + kLow, at_), E, tag, uv);
-                        if (q == cnt - 1) Packed<T>::template post<false>(at(xt + kHigh, at_), E, tag, uv);
+                        const unsigned wo = (unsigned)((w * R + j) * kTX + lane) * 8u;
+                        if (q == 0) Packed<T>::template post<false>(at(xt + kLow, wo), E, tag, uv);
+                        if (q == cnt - 1) Packed<T>::template post<false>(at(xt + kHigh, wo), E, tag, uv);
                         if (w == 0 && j == 0) Packed<T>::template post<false>(at(xt + kFirst + q * kTX, (unsigned)lane * 8u), E, tag, uv);
                         if (j == jb) Packed<T>::template post<false>(at(xt + kLast + q * kTX, (unsigned)lane * 8u), E, tag, uv);
                     }
@@ -1103,10 +1124,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
             missing = false;
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                const unsigned at_ = (unsigned)((w * R + j) * kTX + lane) * 8u;
-                if (lowok && (own >> j & 1u)) lw[j].look(at(xb + (size_t)qlow * EW + kHigh, at_), E);
+                const unsigned wo = (unsigned)((w * R + j) * kTX + lane) * 8u;
+                if (lowok && (own >> j & 1u)) lw[j].look(at(xb + (size_t)qlow * EW + kHigh, wo), E);
                 else lw[j].zero(tag);
-                if (higok && (own >> j & 1u)) gw[j].look(at(xb + (size_t)qhig * EW + kLow, at_), E);
+                if (higok && (own >> j & 1u)) gw[j].look(at(xb + (size_t)qhig * EW + kLow, wo), E);
                 else gw[j].zero(tag);
             }
 #pragma unroll
@@ -1187,6 +1208,8 @@ static const void *loop_kernel(int dim, int tpw, int tile_z, bool local)
 // workgroups of the pass kernel that a workgroup of the loop stands for
 static int loop_per_group(int dim, int tpw) { return dim == 2 && tpw == 2 ? 2 : 1; }
 
+int loop_blocks(int dim, int tpw, int grid) { return 8 * div_up(grid / 8, loop_per_group(dim, tpw)); }   // grid: a multiple of 8
+
 template <typename T>
 hipError_t loop_capacity(int dim, int tpw, int tile_z, bool local, int *cap)
 {
@@ -1198,7 +1221,7 @@ hipError_t loop_capacity(int dim, int tpw, int tile_z, bool local, int *cap)
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, kBlock, 0);
     if (e != hipSuccess) return e;
-    *cap = local ? std::min(per * cus / 8, kLoopLocalMax) : std::min(per * cus * loop_per_group(dim, tpw), kLoopGridMax);
+    *cap = local ? std::min(per * cus / 8, kLoopLocalMax) : std::min(per * cus, kLoopGridMax / loop_per_group(dim, tpw));
     return hipSuccess;
 }
 
@@ -1210,16 +1233,14 @@ size_t loop_exchange_words(int dim, int tile_z, int ntiles)
 }
 
 template <typename T>
-hipError_t launch_loop(int dim, int tpw, int tile_z, bool local, int grid, const PassArgs<T> *tab, Scalars *scal, int parity,
-                       int slot, const LoopArgs &r, hipStream_t st)
+hipError_t launch_loop(int dim, int tpw, int tile_z, bool local, int blocks, const PassArgs<T> *tab, Scalars *scal,
+                       int parity, int slot, const LoopArgs &r, hipStream_t st)
 {
     const void *k = loop_kernel<T>(dim, tpw, tile_z, local);
-    if (!k || grid < 1 || grid > kLoopGridMax) return hipErrorInvalidValue;
+    if (!k || blocks < 1 || blocks > kLoopGridMax) return hipErrorInvalidValue;
     LoopArgs args = r;
     void *p[] = {(void *)&tab, (void *)&scal, (void *)&parity, (void *)&slot, (void *)&args};
-    const int per = loop_per_group(dim, tpw);
-    const int launched = local ? 8 * grid : 8 * div_up(grid / 8, per);     // grid is a multiple of 8
-    return hipLaunchKernel(k, dim3((unsigned)launched), dim3(kBlock), p, 0, st);
+    return hipLaunchKernel(k, dim3((unsigned)(local ? 8 * blocks : blocks)), dim3(kBlock), p, 0, st);
 }
 
 template size_t loop_exchange_words<float>(int, int, int);

@@ -114,6 +114,7 @@ struct Net {
     int64_t prev_iters = 0;
     bool loop_ok = true;            // may run in resident loops (no launch of one was turned away yet)
     bool loop_local = false;        // ... on one XCD
+    int64_t gang_seq = 0;           // last chunk it ran in beside others
     bool loop_used = false;         // a chunk of resident loops was launched
     int64_t first_chunk = 0;        // first chunk whose status mirror covers this network
     // host copies (server path: the caller's buffers stay valid until completion)
@@ -212,22 +213,35 @@ private:
     static constexpr int kXcdMaxGrid = 256;  // largest network (workgroups per pass) placed on one XCD
     static constexpr int kQueueWords = 8 * 32;   // per kind: 8 item counters, 256 bytes apart
     int *d_xoff_ = nullptr, *h_xoff_ = nullptr;  // per kind, 9 table offsets (16 ints), host staging x2
-    // resident loops (rn_loop.hpp) of a network that iterates alone. A chunk is
-    // kLoopsPerChunk loops; kLoopLimit passes of one take 2 to 5 ms, about as
+    // resident loops (rn_loop.hpp). A chunk of a network alone is
+    // kLoopsPerChunk loops; kLoopLimit passes of one take 2 to 9 ms, about as
     // long as a chunk of single passes, so other requests wait no longer.
-    static constexpr int kGates = 8, kGateBytes = 256, kLoopLimit = 512, kLoopsPerChunk = 2;
+    static constexpr int kGates = 8, kLoopLimit = 512, kLoopsPerChunk = 2, kGangLimit = 128, kGangCycles = 2;
+    static constexpr int kGateBytes = kLoopMembers * kLoopGateWords * 4;
     static constexpr int kLoopTpw = 2, kLoopTz = 9;
-    int loop_fits(Net *net, bool *fits, std::string *err);
+    // tables of a chunk of several networks: at most kLoopGridMax workgroups
+    // and kLoopMembers networks of each of the loop kernels' shapes
+    static constexpr int kGangShapes = 10;
+    struct GangTables {
+        uint2 pass[kGangShapes * kLoopGridMax], loop[kGangShapes * kLoopGridMax];
+        LoopNet net[kGangShapes * kLoopMembers];
+    };
+    GangTables *d_gang_ = nullptr, *h_gang_ = nullptr;   // host staging x2
+    int loop_fits(Net *net, bool alone, bool *fits, std::string *err);
+    size_t loop_words(const Net *net) const;
+    int loop_memory(size_t words, hipStream_t st, std::string *err);
+    LoopArgs loop_args(size_t words, int limit);
     int launch_loops(Net *net, int *launched, hipStream_t st, std::string *err);
+    int launch_gangs(int *launched, hipStream_t st, std::string *err);
     int queue_status(int rounds, hipStream_t st, std::string *err);
-    char *d_gate_ = nullptr;                 // kGates gates, used in turn, each cleared kGates / 2 launches later
+    char *d_gate_ = nullptr;                 // kGates sets of gates, used in turn, each cleared kGates / 2 launches later
     unsigned long long *d_xch_ = nullptr, *d_coef_ = nullptr;   // edge values and coefficients of the loops
     size_t xch_cap_ = 0;                     // words of d_xch_ (at most 44 MB, freed with the engine)
     unsigned loop_tag_ = 1;                  // first pass number of the next loop
     double *d_lpart_ = nullptr;              // partial sums of a resident loop
     int gate_ = 0;
-    int loop_cap_[kKinds][kLoopTpw][kLoopTz][2];   // workgroups that fit at once by kind, tiles, depth, on all
-                                                // XCDs or one; -1 = not asked yet
+    int loop_cap_[kKinds][kLoopTpw][kLoopTz][2];   // loop workgroups that fit at once by kind, tiles, depth, on
+                                                // all XCDs or one; -1 = not asked yet
     hipStream_t side_ = nullptr;
     unsigned *d_err_ = nullptr, *h_err_ = nullptr;   // a bounded wait gave up (device word, pinned mirror)
     unsigned long long *d_queue_ = nullptr;          // item counters of the persistent launches, kQueueWords per kind

@@ -58,3 +58,25 @@ def test_loop_bits(size, precision, axis, periodic, monkeypatch):
         got, p1 = solve(loop, g, nx, ny, nz, precision, axis, periodic, tol)
         assert got == want
         assert torch.equal(p0, p1)
+
+
+@pytest.mark.parametrize("precision", [B.RN_MIXED, B.RN_FP64], ids=["mixed", "fp64"])
+def test_gang_bits(precision, monkeypatch):
+    """Networks that run in loops beside each other, more than the chip holds at once, of every loop
+    kernel's shape: each gives the bits of its own solve with one launch per pass."""
+    import torch
+    sizes = [(70, 60, 1), (64, 8, 1), (200, 150, 1), (520, 515, 1), (700, 600, 1), (900, 850, 1), (1030, 700, 1),
+             (20, 18, 17), (64, 48, 40), (70, 66, 64), (100, 96, 60), (128, 120, 99), (120, 128, 90)]
+    nets = [(s, network(*s, seed=i, occupancy=0.9)) for i, s in enumerate(sizes)]
+    monkeypatch.setenv("RN_GRAPHS", "1")
+    plain = B.Context(0)
+    monkeypatch.delenv("RN_GRAPHS")
+    gang = B.Context(0)
+    want = [solve(plain, g, *s, precision, 0, False, 1e-5) for s, g in nets]
+    p = [torch.zeros(g[0].shape, dtype=torch.float64, device="cuda") for _, g in nets]
+    probs = [B.problem(dim=len(g), nx=s[0], ny=s[1], nz=s[2], axis=0, g=g, p_out=q) for (s, g), q in zip(nets, p)]
+    torch.cuda.synchronize()
+    for _ in range(2):
+        for r, q, (w, pw) in zip(gang.solve_batch(probs, B.opts(precision, 1e-5)), p, want):
+            assert (r.K, r.G, r.Q_in, r.Q_out, r.rel_resid, r.iters, r.refreshes) == w
+            assert torch.equal(q, pw)
