@@ -1193,6 +1193,19 @@ UfBlock uf_block(const Lat &L)
     return B;
 }
 
+// Root of a node of the block, halving its path (only a node that is no root is
+// rewritten, to an ancestor): in a full lattice chains grow along whole rows.
+__device__ __forceinline__ int lds_find(int *lab, int x)
+{
+    while (true) {
+        const int p = __hip_atomic_load(lab + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (p == x) return x;
+        const int q = __hip_atomic_load(lab + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (q != p) __hip_atomic_store(lab + x, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        x = q;
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void uf_local_kernel(Lat L, UfBlock B, const double *g0, const double *g1,
                                                           const double *g2, int *parent, unsigned *flags,
                                                           uint8_t *tree)
@@ -1221,8 +1234,8 @@ __global__ __launch_bounds__(kBlock) void uf_local_kernel(Lat L, UfBlock B, cons
                 if (!(g[k][i] > 0.0)) continue;
                 int a = l, b = l + lst[k];
                 while (true) {
-                    for (int p; (p = __hip_atomic_load(lab + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != a;) a = p;
-                    for (int p; (p = __hip_atomic_load(lab + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != b;) b = p;
+                    a = lds_find(lab, a);
+                    b = lds_find(lab, b);
                     if (a == b) break;
                     if (a < b) {
                         const int s = a;
