@@ -400,7 +400,8 @@ typedef struct {
     int64_t finishing;    /* outputs being copied back */
     int64_t bytes_in_use; /* device bytes held by networks */
     int64_t budget;       /* the context's HBM budget */
-    int64_t launches;     /* pass kernel launches issued so far */
+    int64_t launches;     /* pass kernel launches issued so far; of a network that ran in resident
+                             loops, many passes to a launch, its passes, once it has finished */
     int64_t peak_active;  /* most networks that have shared one pass launch */
     /* With rn_set_timing on: device time of the pass kernel launches, by the
      * path that ran them (RN_PATH_*) and their inner precision (RN_FP64,

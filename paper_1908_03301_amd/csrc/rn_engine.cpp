@@ -689,8 +689,11 @@ int Engine::after_prepare(Net *net, hipStream_t st, std::string *err)
 
 int Engine::rebuild(hipStream_t st, std::string *err)
 {
+    std::vector<Net *> shared;             // networks of the shared rounds
+    for (Net *n : active_)
+        if (!n->in_loop) shared.push_back(n);
     int count[kKinds] = {};
-    for (Net *n : active_) count[n->kind] += n->L.grid;
+    for (Net *n : shared) count[n->kind] += n->L.grid;
     for (int k = 0; k < kKinds; ++k) {
         if (count[k] > blk_cap_[k]) {
             const int cap = std::max(count[k], blk_cap_[k] * 3 / 2 + 1024);
@@ -712,7 +715,7 @@ int Engine::rebuild(hipStream_t st, std::string *err)
         single_[k] = -1;
         if (!count[k]) continue;
         int nets = 0;
-        for (Net *n : active_)
+        for (Net *n : shared)
             if (n->kind == k) {
                 ++nets;
                 single_[k] = n->slot;
@@ -723,7 +726,7 @@ int Engine::rebuild(hipStream_t st, std::string *err)
         // each network on one XCD (2, when every network of the kind is small
         // enough that one XCD's workgroups hold a pass of it)
         int grid_max = 0;
-        for (Net *n : active_)
+        for (Net *n : shared)
             if (n->kind == k) grid_max = std::max(grid_max, n->L.grid);
         kind_coh_[k] = persist_mode_ == 1 ? 1 : ((persist_mode_ == 2 && grid_max <= kXcdMaxGrid) ? 2 : 0);
         uint2 *h = h_blk_[k] + (size_t)half_ * blk_cap_[k];
@@ -734,7 +737,7 @@ int Engine::rebuild(hipStream_t st, std::string *err)
             // with the fewest workgroups so far; the table lists XCD 0's
             // networks, then XCD 1's, and so on
             std::vector<Net *> nk;
-            for (Net *n : active_)
+            for (Net *n : shared)
                 if (n->kind == k) nk.push_back(n);
             std::stable_sort(nk.begin(), nk.end(), [](const Net *a, const Net *b) { return a->L.grid > b->L.grid; });
             int64_t load[8] = {};
@@ -755,7 +758,7 @@ int Engine::rebuild(hipStream_t st, std::string *err)
             xo[8] = m;
             single_[k] = -1;
         } else {
-            for (Net *n : active_)
+            for (Net *n : shared)
                 if (n->kind == k)
                     for (int b = 0; b < n->L.grid; ++b) h[m++] = make_uint2((unsigned)n->slot, (unsigned)b);
             xo[0] = 0;
@@ -920,8 +923,8 @@ LoopArgs Engine::loop_args(size_t words, int limit)
     return a;
 }
 
-// A chunk of several networks that all fit resident loops, those of one shape
-// (kernel) together. Of each shape as many networks as the chip holds run at
+// The part of a chunk that runs several networks in resident loops, those of
+// one shape (kernel) together. Of each shape as many networks as the chip holds run at
 // once, taken in turn from the active list, chunk by chunk; the others wait.
 // (All of them in one launch per pass is bound by its bytes or by its tail,
 // see launch_rounds; a batch of 48 networks of 64^2 to 1024^2 and 32^3 to 128^3
@@ -929,7 +932,7 @@ LoopArgs Engine::loop_args(size_t words, int limit)
 // one is due) and a loop of up to kGangLimit passes: networks that reach a
 // refresh earlier wait for the others, hence the small limit. The rounds of a
 // chunk are even in number, so the parities of waiting networks stay right.
-int Engine::launch_gangs(int *launched, hipStream_t st, std::string *err)
+int Engine::launch_gangs(bool first, int *launched, hipStream_t st, std::string *err)
 {
     struct Gang {
         int kind, tpw, tz;
@@ -939,6 +942,7 @@ int Engine::launch_gangs(int *launched, hipStream_t st, std::string *err)
     };
     std::vector<Gang> gangs;
     for (Net *n : active_) {
+        if (!n->in_loop) continue;
         const int tz = n->L.dim == 3 ? n->L.tile_z : 0;
         Gang *g = nullptr;
         for (Gang &q : gangs)
@@ -949,8 +953,8 @@ int Engine::launch_gangs(int *launched, hipStream_t st, std::string *err)
         }
         g->nets.push_back(n);
     }
-    half_ ^= 1;
-    GangTables *h = h_gang_ + half_;
+    gang_half_ ^= 1;
+    GangTables *h = h_gang_ + gang_half_;
     size_t most = 0;
     int np = 0, nl = 0, nn = 0;
     for (Gang &g : gangs) {
@@ -991,7 +995,7 @@ int Engine::launch_gangs(int *launched, hipStream_t st, std::string *err)
     ENG_TRY(hipMemcpyAsync(d_gang_, h, sizeof(GangTables), hipMemcpyHostToDevice, st));
     recording_ = timing_;
     tmirror_ = next_mirror_;
-    if (recording_) r = record_timing(-1, st, err);
+    if (recording_ && first) r = record_timing(-1, st, err);   // else the shared rounds began the chunk's record
     for (int c = 0; c < kGangCycles && !r; ++c)
         for (int loop = 0; loop < 2 && !r; ++loop) {
             const int par = (int)(rounds_ & 1);
@@ -1015,7 +1019,6 @@ int Engine::launch_gangs(int *launched, hipStream_t st, std::string *err)
                     r = RN_EDEVICE;
                     break;
                 }
-                ++launches_;
                 if (recording_ && (r = record_timing(g.kind, st, err))) break;
             }
             ++rounds_;
@@ -1062,7 +1065,6 @@ int Engine::launch_loops(Net *net, int *launched, hipStream_t st, std::string *e
             ENG_TRY(launch_pass<double>(dim, d_tabd_, nullptr, d_scal_, net->L.grid, par, slot, st));
         }
         ++rounds_;
-        ++launches_;
         ++n;
         return recording_ ? record_timing(k, st, err) : RN_OK;
     };
@@ -1104,16 +1106,22 @@ int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
     if (active_.empty()) return RN_OK;
     peak_active_ = std::max(peak_active_, (int)active_.size());
     tkind_[next_mirror_].clear();
-    bool fits = !persist_ && !use_graph_;
-    for (size_t i = 0; i < active_.size() && fits; ++i) {
-        int r = loop_fits(active_[i], active_.size() == 1, &fits, err);
+    // networks that fit resident loops run in those, the others in shared rounds
+    size_t loops = 0;
+    for (Net *n : active_) {
+        bool fits = false;
+        int r = loop_fits(n, active_.size() == 1, &fits, err);
         if (r) return r;
+        if (fits != n->in_loop) dirty_ = true;
+        n->in_loop = fits;
+        loops += fits ? 1 : 0;
     }
-    if (fits) {
+    if (loops == active_.size()) {
         int launched = 0;
-        int r = active_.size() == 1 ? launch_loops(active_[0], &launched, st, err) : launch_gangs(&launched, st, err);
+        int r = loops == 1 ? launch_loops(active_[0], &launched, st, err) : launch_gangs(true, &launched, st, err);
         return r ? r : queue_status(launched, st, err);
     }
+    if (loops) rounds += rounds & 1;   // the networks in loops sit out an even number of rounds
     if (dirty_) {
         int r = rebuild(st, err);
         if (r) return r;
@@ -1151,6 +1159,12 @@ int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
     rounds_ += rounds;
     for (int k = 0; k < kKinds; ++k)
         if (nblk_[k]) launches_ += (persist_ && kind_coh_[k] != 0) ? 1 : rounds;
+    if (loops) {
+        int launched = 0;
+        int r = launch_gangs(false, &launched, st, err);
+        if (r) return r;
+        rounds += launched;
+    }
     return queue_status(rounds, st, err);
 }
 
@@ -1273,6 +1287,7 @@ int Engine::finalize(Net *net, const Scalars &h, hipStream_t st, std::string *er
     r.n_live = net->n_live;
     // a resident loop runs many pass rounds in one launch: count the passes then
     r.passes = net->loop_used ? h.passes : rounds_ - net->round0;
+    if (net->loop_used) launches_ += h.passes;
     if (r.status == 0 && !r.converged) r.status = RN_ENOCONV;
     net->status = r.status;
     const double *P_final = (const double *)(base + L.off_P) + (size_t)(h.refreshes & 1) * n;

@@ -113,6 +113,7 @@ struct Net {
     double prev_est = -1.0;
     int64_t prev_iters = 0;
     bool loop_ok = true;            // may run in resident loops (no launch of one was turned away yet)
+    bool in_loop = false;           // runs in resident loops this chunk
     bool loop_local = false;        // ... on one XCD
     int64_t gang_seq = 0;           // last chunk it ran in beside others
     bool loop_used = false;         // a chunk of resident loops was launched
@@ -226,13 +227,14 @@ private:
         uint2 pass[kGangShapes * kLoopGridMax], loop[kGangShapes * kLoopGridMax];
         LoopNet net[kGangShapes * kLoopMembers];
     };
+    int gang_half_ = 0;
     GangTables *d_gang_ = nullptr, *h_gang_ = nullptr;   // host staging x2
     int loop_fits(Net *net, bool alone, bool *fits, std::string *err);
     size_t loop_words(const Net *net) const;
     int loop_memory(size_t words, hipStream_t st, std::string *err);
     LoopArgs loop_args(size_t words, int limit);
     int launch_loops(Net *net, int *launched, hipStream_t st, std::string *err);
-    int launch_gangs(int *launched, hipStream_t st, std::string *err);
+    int launch_gangs(bool first, int *launched, hipStream_t st, std::string *err);
     int queue_status(int rounds, hipStream_t st, std::string *err);
     char *d_gate_ = nullptr;                 // kGates sets of gates, used in turn, each cleared kGates / 2 launches later
     unsigned long long *d_xch_ = nullptr, *d_coef_ = nullptr;   // edge values and coefficients of the loops

@@ -63,10 +63,10 @@ def test_loop_bits(size, precision, axis, periodic, monkeypatch):
 @pytest.mark.parametrize("precision", [B.RN_MIXED, B.RN_FP64], ids=["mixed", "fp64"])
 def test_gang_bits(precision, monkeypatch):
     """Networks that run in loops beside each other, more than the chip holds at once, of every loop
-    kernel's shape: each gives the bits of its own solve with one launch per pass."""
+    kernel's shape, and one that fits none: each gives the bits of its own solve with one launch per pass."""
     import torch
     sizes = [(70, 60, 1), (64, 8, 1), (200, 150, 1), (520, 515, 1), (700, 600, 1), (900, 850, 1), (1030, 700, 1),
-             (20, 18, 17), (64, 48, 40), (70, 66, 64), (100, 96, 60), (128, 120, 99), (120, 128, 90)]
+             (20, 18, 17), (200, 180, 50), (64, 48, 40), (70, 66, 64), (100, 96, 60), (128, 120, 99), (120, 128, 90)]
     nets = [(s, network(*s, seed=i, occupancy=0.9)) for i, s in enumerate(sizes)]
     monkeypatch.setenv("RN_GRAPHS", "1")
     plain = B.Context(0)
