@@ -232,19 +232,21 @@ extern "C" int rn_fbm_field(rn_ctx *ctx, int32_t dim, int64_t nx, int64_t ny, in
     const int64_t nspec = nz * ny * (nx / 2 + 1);
     auto a256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
     // device callers: the field's own buffer takes the copy of the noise that
-    // the transforms work on
-    const size_t off_x = 0, off_s = mem == RN_MEM_HOST ? a256(8 * n) : 0, off_p = off_s + a256(16 * nspec),
+    // the transforms work on, if it is aligned for their 16-byte accesses and
+    // shares no memory with the noise
+    const uintptr_t fa = reinterpret_cast<uintptr_t>(field_out), na = reinterpret_cast<uintptr_t>(noise);
+    const bool direct = mem == RN_MEM_DEVICE && (fa & 15) == 0 && (fa + 8 * n <= na || na + 8 * n <= fa);
+    const size_t off_x = 0, off_s = direct ? 0 : a256(8 * n), off_p = off_s + a256(16 * nspec),
                  off_sum = off_p + a256(8 * kRedBlocks), total = off_sum + 256;
     Scratch sc(ctx);
     hipError_t he;
     sc.base = (char *)ctx->pool.alloc(total, &he);
     if (!sc.base) return RN_ENOMEM;
-    double *x = mem == RN_MEM_HOST ? (double *)(sc.base + off_x) : field_out;
+    double *x = direct ? field_out : (double *)(sc.base + off_x);
     hipfftDoubleComplex *spec = (hipfftDoubleComplex *)(sc.base + off_s);
     double *partial = (double *)(sc.base + off_p), *sums = (double *)(sc.base + off_sum);
     const hipStream_t st = ctx->stream;
-    if (x != noise)
-        FBM_TRY(hipMemcpyAsync(x, noise, 8 * n, mem == RN_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
+    FBM_TRY(hipMemcpyAsync(x, noise, 8 * n, mem == RN_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
     FbmPlans *pl = static_cast<FbmPlans *>(ctx->fbm_plans);
     if (!pl || pl->dim != dim || pl->nx != nx || pl->ny != ny || pl->nz != nz) {
         fbm_release(ctx);
@@ -282,7 +284,9 @@ extern "C" int rn_fbm_field(rn_ctx *ctx, int32_t dim, int64_t nx, int64_t ny, in
     fbm_filter_kernel<<<grid_of((int64_t)F.nzh * F.nyh * F.nxh), 256, 0, st>>>(spec, F, sums);
     FBM_TRY(hipGetLastError());
     FFT_TRY(hipfftExecZ2D(inv, spec, x));
-    if (mem == RN_MEM_HOST) FBM_TRY(hipMemcpyAsync(field_out, x, 8 * n, hipMemcpyDeviceToHost, st));
+    if (!direct)
+        FBM_TRY(hipMemcpyAsync(field_out, x, 8 * n,
+                               mem == RN_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, st));
     FBM_TRY(hipStreamSynchronize(st));
     return RN_OK;
 }
