@@ -215,8 +215,9 @@ private:
     static constexpr int kQueueWords = 8 * 32;   // per kind: 8 item counters, 256 bytes apart
     int *d_xoff_ = nullptr, *h_xoff_ = nullptr;  // per kind, 9 table offsets (16 ints), host staging x2
     // resident loops (rn_loop.hpp). A chunk of a network alone is
-    // kLoopsPerChunk loops; kLoopLimit passes of one take 2 to 9 ms, about as
-    // long as a chunk of single passes, so other requests wait no longer.
+    // kLoopsPerChunk loops of up to kLoopLimit passes (half as many of a network
+    // that fills the chip), 2 to 5 ms: about as long as a chunk of single
+    // passes, so other requests wait no longer.
     static constexpr int kGates = 8, kLoopLimit = 512, kLoopsPerChunk = 2, kGangLimit = 128, kGangCycles = 2;
     static constexpr int kGateBytes = kLoopMembers * kLoopGateWords * 4;
     static constexpr int kLoopTpw = 2, kLoopTz = 9;
