@@ -276,7 +276,10 @@ __global__ void bb_ranges(BbWork W, int from)
 }
 
 // Walk again, writing the positions. A vertex of one tree direction is
-// arrived at once.
+// arrived at once; one of two directions writes a word for each, which
+// bb_clear puts in order. The others, about a quarter of the vertices of a
+// 2048^2 network, take atomics, which this launch is bound by (there 269 us,
+// 484 with atomics for the vertices of two directions too).
 __global__ void bb_number(BbGraph G, BbWork W, int from)
 {
     const int total = W.groups + (int)W.counter[0];
@@ -288,9 +291,12 @@ __global__ void bb_number(BbGraph G, BbWork W, int from)
         const unsigned t = (unsigned)a;
         unsigned pos = W.end[t] - W.len[t] - (unsigned)(a >> 32);
         for (unsigned k = W.len[i]; k > 0u; --k, ++pos) {
-            if (__popc(bits & 0x7fu) == 1) {
+            const unsigned dirs = bits & 0x7fu, rest = dirs & (dirs - 1u);
+            if (rest == 0u) {
                 W.in[v] = pos;
                 W.last[v] = pos;
+            } else if ((rest & (rest - 1u)) == 0u) {
+                (rest >> r & 1u ? W.last : W.in)[v] = pos;
             } else {
                 atomicMin(W.in + v, pos);
                 atomicMax(W.last + v, pos);
@@ -300,9 +306,17 @@ __global__ void bb_number(BbGraph G, BbWork W, int from)
     }
 }
 
-// 3. Identities at the positions that are no first arrival.
-__global__ void bb_clear(BbWork W)
+// First and last arrival in order; 3. identities at the positions that are no
+// first arrival.
+__global__ void bb_clear(BbGraph G, BbWork W)
 {
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+        const unsigned a = W.in[v], b = W.last[v];
+        if (a > b && a != kNone) {
+            W.in[v] = b;
+            W.last[v] = a;
+        }
+    }
     const unsigned m = kPosFirst + W.counter[1];
     for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
         W.lo[0][i] = kNone;
@@ -707,7 +721,7 @@ hipError_t launch_backbone(const Lat &L, const double *const g[3], uint8_t *mask
         bb_jump<<<gw, kBbBlock, 0, st>>>(W, from);
     bb_ranges<<<grid_of((n + 2) / 3), kBbBlock, 0, st>>>(W, from);
     bb_number<<<gw, kBbBlock, 0, st>>>(G, W, from);
-    bb_clear<<<grid_of(2 * n), kBbBlock, 0, st>>>(W);
+    bb_clear<<<grid_of(2 * n), kBbBlock, 0, st>>>(G, W);
     bb_reach<<<gn, kBbBlock, 0, st>>>(G, W);
     int64_t m = 2 * (n + 2);
     for (int l = 1; l < kFanLevels && m > kFan; ++l) {
