@@ -260,7 +260,7 @@ int rn_build_mask_noalloc(rn_ctx *ctx, const rn_problem *prob, int64_t *n_live_o
  * outlet-face node visiting no node twice. Equivalently, with each face
  * contracted to one vertex and an edge added between the two, the nodes of
  * the biconnected component holding that edge. Computed on the device
- * (a breadth-first spanning tree and Tarjan and Vishkin's joins); the result
+ * (a spanning tree, its Euler tour and Tarjan and Vishkin's joins); the result
  * does not depend on the order in which the device visits nodes.
  * Writes prob->mask_out (required): the mask of rn_build_mask with bit3 (8)
  * set on backbone nodes, so backbone nodes are 11 and other live nodes stay
