@@ -375,6 +375,18 @@ constexpr int kModeWord = (int)(offsetof(Scalars, mode) / 8);
 static_assert(offsetof(Scalars, mode) == 0, "mode is the low half of the first control block word");
 constexpr int kPassesWord = (int)(offsetof(Scalars, passes) / 8);
 static_assert(offsetof(Scalars, passes) % 8 == 0 && kModeWord != kPassesWord, "control block words");
+constexpr int kLoopWord = (int)(offsetof(Scalars, loop_aborts) / 8);
+static_assert(offsetof(Scalars, loop_aborts) % 8 == 0 && offsetof(Scalars, loop_failed) == offsetof(Scalars, loop_aborts) + 4,
+              "the word of a resident loop's refusals and failures");
+
+// Word t of the control block at the end of a resident loop, from the copy
+// that the loop ran its steps on. The word of refusals and failures stays as
+// it is: any workgroup may have given up a wait after the copy was made, and
+// its flag has to reach the host.
+__host__ __device__ inline void store_loop_end(unsigned long long *s, const volatile unsigned long long *copy, int t)
+{
+    if (t < kScalWords && t != kLoopWord) s[t] = copy[t];
+}
 
 __device__ __forceinline__ unsigned long long prefetch_scalars(const Scalars *s)
 {

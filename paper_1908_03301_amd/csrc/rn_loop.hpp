@@ -821,8 +821,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
                     else v = Pv[t][sg][j];
                     sti(P, i, v);
                 }
-    if (admitted && lb == 0 && threadIdx.x < kScalWords)   // wave 0, which ran the last step on this copy
-        reinterpret_cast<u64 *>(s)[threadIdx.x] = reinterpret_cast<const volatile u64 *>(&sh.sl[0])[threadIdx.x];
+    if (admitted && lb == 0)                               // wave 0 ran the last step on this copy
+        store_loop_end(reinterpret_cast<u64 *>(s), reinterpret_cast<const volatile u64 *>(&sh.sl[0]), (int)threadIdx.x);
 }
 
 // ---------------------------------------------------------------- 3D
@@ -1183,8 +1183,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
                 sti(pd, i, p_[q][j]);
                 sti(P, i, fl[q * R + j][threadIdx.x]);
             }
-    if (admitted && lb == 0 && threadIdx.x < kScalWords)
-        reinterpret_cast<u64 *>(s)[threadIdx.x] = reinterpret_cast<const volatile u64 *>(&sh.sl[0])[threadIdx.x];
+    if (admitted && lb == 0)
+        store_loop_end(reinterpret_cast<u64 *>(s), reinterpret_cast<const volatile u64 *>(&sh.sl[0]), (int)threadIdx.x);
 }
 
 }  // namespace
