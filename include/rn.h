@@ -183,7 +183,10 @@ int rn_opts_default(rn_opts *opts);
  *   RN_PERSIST=2  the same with each network of a kind of small networks
  *                 placed on one XCD (other kinds: one launch per round);
  *   RN_GRAPHS=1   rounds replayed from a captured hipGraph;
- *   otherwise one launch per round and kind.
+ *   otherwise one launch per round and kind, and many rounds of a network
+ *   that fits the chip in one launch (a resident loop); with RN_LOOPS=0 none
+ *   of those, with RN_LOOPS=2 every resident loop is turned away at its start,
+ *   as it is where other work holds the chip (a check of that path).
  * Errors: RN_EINVAL (NULL out, bad device), RN_EDEVICE.
  */
 int rn_create(int device, size_t hbm_budget_bytes, rn_ctx **out);

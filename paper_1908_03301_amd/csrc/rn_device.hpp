@@ -250,6 +250,7 @@ struct LoopArgs {
     int limit;
     const uint2 *blk;        // nullptr: one network
     const LoopNet *net;
+    int turn_away;           // 1: the gate admits nobody (a check of what follows then)
 };
 constexpr int kLoopMembers = 64, kLoopGateWords = 16;
 constexpr size_t kLoopCoefBytes = 2048;

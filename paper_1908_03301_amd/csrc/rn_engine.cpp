@@ -431,6 +431,10 @@ int Engine::init(hipStream_t st, std::string *err)
     persist_mode_ = (pe && pe[0] == '1') ? 1 : ((pe && pe[0] == '2') ? 2 : 0);
     persist_ = persist_mode_ != 0;
     if (persist_) use_graph_ = false;
+    // RN_LOOPS=0: no resident loops. RN_LOOPS=2: every one is turned away at its
+    // gate, as where another stream holds the CUs (a check of that path).
+    const char *lo = std::getenv("RN_LOOPS");
+    loops_mode_ = lo && (lo[0] == '0' || lo[0] == '2') ? lo[0] - '0' : 1;
     ENG_TRY(hipMalloc(&d_queue_, kQueueWords * sizeof(unsigned long long) * kKinds));
     ENG_TRY(hipMalloc(&d_xoff_, sizeof(int) * 16 * kKinds));
     ENG_TRY(hipHostMalloc((void **)&h_xoff_, sizeof(int) * 16 * kKinds * 2, hipHostMallocDefault));
@@ -857,7 +861,7 @@ int Engine::launch_persistent(int rounds, hipStream_t st, std::string *err)
 int Engine::loop_fits(Net *net, bool alone, bool *fits, std::string *err)
 {
     *fits = false;
-    if (persist_ || use_graph_ || !net->loop_ok) return RN_OK;
+    if (persist_ || use_graph_ || !loops_mode_ || !net->loop_ok) return RN_OK;
     const int k = net->kind, tpw = net->L.tpw;
     if (tpw < 1 || tpw > kLoopTpw) return RN_OK;
     const int tz = net->L.dim == 3 ? net->L.tile_z : 0;
@@ -920,6 +924,7 @@ LoopArgs Engine::loop_args(size_t words, int limit)
     a.limit = limit;
     a.blk = nullptr;
     a.net = nullptr;
+    a.turn_away = loops_mode_ == 2 ? 1 : 0;
     return a;
 }
 

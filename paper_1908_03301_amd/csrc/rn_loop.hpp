@@ -27,7 +27,7 @@
 // before it posts pass k + 1, so nobody polls the slot for pass k + 2 before.
 //
 // The workgroups of a small 2D network all run on one XCD (LOCAL): eight times as many
-// are launched, those elsewhere leave at once, the others claim their place.
+// are launched, those there claim their place, the others leave.
 // Every word then stays in that XCD's L2: stores need not go through to memory
 // (plain ones reach the L2; loads are device-scope, since a CU's L1 may hold a
 // line another CU has since written). One workgroup per CU gains (128^2 mixed,
@@ -36,8 +36,12 @@
 //
 // All workgroups have to run at once. They are admitted by a gate: each counts
 // itself in, and the launch goes ahead only if all arrive in time; otherwise
-// every workgroup leaves with nothing changed and the host goes on with one
-// launch per pass. Behind the gate every wait is bounded too (kSpinTicks).
+// they move z and u to the parity of the next round, change nothing else, and
+// the host goes on with one launch per pass. Who moves what does not depend on
+// who got a place: the dispatcher need not have dealt the workgroups of a LOCAL
+// launch evenly to the XCDs (a stream with a CU mask, another partition mode),
+// so the first of them wait for the gate's answer wherever they are.
+// Behind the gate every wait is bounded too (kSpinTicks).
 //
 // The arithmetic and its order are those of the pass kernels (tile by tile,
 // the same reduction tree), so results are the same bits.
@@ -144,11 +148,13 @@ struct Spin {
     }
 };
 
-// Thread 0: count this workgroup in and learn whether the launch goes ahead.
-__device__ __forceinline__ int pass_gate(unsigned *gate, unsigned grid, Scalars *s)
+// Thread 0: learn whether the launch goes ahead. A workgroup with a place
+// counts itself in; `places` of them open the gate.
+__device__ __forceinline__ int pass_gate(unsigned *gate, bool has_place, unsigned places, Scalars *s)
 {
     unsigned state = 0;
-    if (__hip_atomic_fetch_add(gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == grid - 1u) {
+    if (has_place &&
+        __hip_atomic_fetch_add(gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == places - 1u) {
         unsigned expected = 0u;
         __hip_atomic_compare_exchange_strong(gate + 1, &expected, kGateGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
@@ -156,6 +162,7 @@ __device__ __forceinline__ int pass_gate(unsigned *gate, unsigned grid, Scalars 
     }
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
     while (!state) {
+        if (!has_place) __builtin_amdgcn_s_sleep(127);   // 3 us: nobody waits for this one
         state = __hip_atomic_load(gate + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (!state && __builtin_amdgcn_s_memrealtime() - t0 > kGateTicks) {
             unsigned expected = 0u;
@@ -171,9 +178,12 @@ __device__ __forceinline__ int pass_gate(unsigned *gate, unsigned grid, Scalars 
     return state == kGateGo;
 }
 
-// This workgroup's network and its place in it, -1: none. One workgroup is
-// launched per place, or (LOCAL) per place and XCD, those on XCD 0 counting
-// themselves in. r: the launch's arguments, made this network's.
+// This workgroup's network and its place in it (kNoPlace and any number past
+// the network's workgroups: none). One workgroup is launched per place, or
+// (LOCAL) per place and XCD, those on XCD 0 claiming one. r: the launch's
+// arguments, made this network's. With turn_away the gate waits for a
+// workgroup that was never launched, or no XCD is the one.
+constexpr int kNoPlace = 1 << 30;
 struct Place {
     int slot, lb;
 };
@@ -186,7 +196,8 @@ __device__ __forceinline__ Place loop_place(LoopArgs &r, int slot)
     Place p = {slot, (int)blockIdx.x};
     if constexpr (LOCAL) {
         __shared__ int place;
-        if (__builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20)) & 7) return {slot, -1};   // XCC_ID
+        const int xcd = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20)) & 7;   // XCC_ID
+        if (xcd || r.turn_away) return {slot, kNoPlace};
         if (threadIdx.x == 0)
             place = (int)__hip_atomic_fetch_add(r.gate + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
@@ -216,6 +227,14 @@ struct LoopState {
     double alpha, beta, sa;
 };
 
+// The gate's answer for the whole workgroup.
+__device__ __forceinline__ bool loop_gate(LoopShared &sh, bool has_place, int places, Scalars *s, const LoopArgs &r)
+{
+    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, has_place, (unsigned)(places + (r.turn_away ? 1 : 0)), s);
+    __syncthreads();
+    return sh.go != 0;
+}
+
 // Emptied sums, the control block's copies, the gate. Returns whether the
 // launch goes ahead.
 template <bool LOCAL>
@@ -235,9 +254,7 @@ __device__ __forceinline__ bool loop_begin(LoopShared &sh, LoopState &L, Scalars
     L.sa = s->sigma * s->alpha;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, (unsigned)(8 * div_up(grid >> 3, nlb)), s);
-    __syncthreads();
-    return sh.go != 0;
+    return loop_gate(sh, true, 8 * div_up(grid >> 3, nlb), s, r);
 }
 
 // The four sums of a workgroup of the pass kernels, as in finish_pass: thread
@@ -425,6 +442,18 @@ __device__ __forceinline__ void sti(T *base, int i, T v)
     *reinterpret_cast<RN_GLOBAL T *>((RN_GLOBAL char *)base + (unsigned)i * (unsigned)sizeof(T)) = v;
 }
 
+// A LOCAL launch that was turned away: workgroup b of `blocks` moves its share
+// of z and u to the parity that the next round reads.
+template <typename T>
+__device__ __forceinline__ void move_state(const PassArgs<T> &a, int b, int blocks)
+{
+    const int n = a.nx * a.ny * a.nz;
+    for (int i = b * kBlock + (int)threadIdx.x; i < n; i += blocks * kBlock) {
+        sti(a.dst.z, i, ldi(a.src.z, i));
+        sti(a.dst.u, i, ldi(a.src.u, i));
+    }
+}
+
 // hide(v): the compiler may not carry anything computed from v across passes.
 // Left to itself it keeps every invariant of the loop (diagonals, shifted
 // bonds, addresses, lane masks) in registers and spills the state instead.
@@ -465,11 +494,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
     __shared__ LoopShared sh;
     __shared__ double fl[kFieldLds ? NT * SEG * TY : 1][kBlock];
     const Place at_ = loop_place<LOCAL>(r, slot);
-    if (at_.lb < 0) return;
     const PassArgs<T> &a = tab[2 * at_.slot + parity];
     Scalars *s = scal + at_.slot;
     const int grid = a.grid, lb = at_.lb;
-    if (lb >= grid || s->mode != MODE_CG) return;
+    if constexpr (LOCAL) {
+        if (s->mode != MODE_CG) return;
+        if (lb >= grid) {                          // no place
+            if ((int)blockIdx.x < grid && !loop_gate(sh, false, grid, s, r)) move_state(a, (int)blockIdx.x, grid);
+            return;
+        }
+    } else if (lb >= grid || s->mode != MODE_CG) {
+        return;
+    }
     int lane = threadIdx.x & (kWave - 1);
     const int w = rfl((int)threadIdx.x / kWave);
     // workgroups of the pass kernel that this one stands for, all of its XCD
@@ -802,6 +838,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
     // ---- the state of the last pass, as a pass kernel leaves it (alpha is the
     // one pending step). A launch that was turned away moves z and u to the
     // other parity, where the next round reads them, and no more.
+    if constexpr (LOCAL)
+        if (!admitted) {
+            if ((int)blockIdx.x < grid) move_state(a, (int)blockIdx.x, grid);
+            return;
+        }
     const int64_t done = passes0 + it - 1;
     T *pd = a.pbuf[a.npbuf == 5 ? (int)(done % 5) : (int)(done % 3)];
 #pragma unroll
@@ -849,7 +890,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     __shared__ double fl[TZ * R][kBlock];
     __shared__ LoopShared sh;
     const Place at_ = loop_place<false>(r, slot);
-    if (at_.lb < 0) return;
     const PassArgs<T> &a = tab[2 * at_.slot + parity];
     Scalars *s = scal + at_.slot;
     const int grid = a.grid, lb = at_.lb;

@@ -228,6 +228,7 @@ private:
         uint2 pass[kGangShapes * kLoopGridMax], loop[kGangShapes * kLoopGridMax];
         LoopNet net[kGangShapes * kLoopMembers];
     };
+    int loops_mode_ = 1;                     // RN_LOOPS: 0 none, 1, 2 every one turned away
     int gang_half_ = 0;
     GangTables *d_gang_ = nullptr, *h_gang_ = nullptr;   // host staging x2
     int loop_fits(Net *net, bool alone, bool *fits, std::string *err);

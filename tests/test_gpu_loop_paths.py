@@ -1,0 +1,110 @@
+"""Which launches run a network's passes, seen from the launch counts of
+rn_set_timing: resident loops where its workgroups fit the chip, of every shape
+they are built for, and one launch per pass where a loop is turned away at its
+gate (RN_LOOPS=2), with the bits of a context without loops (RN_LOOPS=0)."""
+import numpy as np
+import pytest
+
+from paper_1908_03301_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+# (nx, ny, nz), precision, and the launch plan that picks the loop kernel: path, tiles
+# per workgroup, tile depth. Of the small 2D tiles, up to 32 workgroups run on one XCD.
+FULL, SMALL, BLOCK = B.RN_PATH_2D_FULL, B.RN_PATH_2D_SMALL, B.RN_PATH_3D
+SHAPES = [((128, 128, 1), B.RN_MIXED, (SMALL, 1, 1)), ((64, 120, 1), B.RN_FP64, (SMALL, 1, 1)),
+          ((210, 160, 1), B.RN_MIXED, (SMALL, 1, 1)), ((201, 150, 1), B.RN_FP64, (SMALL, 1, 1)),
+          ((520, 515, 1), B.RN_MIXED, (FULL, 1, 1)), ((520, 515, 1), B.RN_FP64, (FULL, 1, 1)),
+          ((1500, 1420, 1), B.RN_MIXED, (FULL, 2, 1)), ((1390, 1400, 1), B.RN_FP64, (FULL, 2, 1)),
+          ((65, 40, 33), B.RN_MIXED, (BLOCK, 1, 2)), ((65, 40, 33), B.RN_FP64, (BLOCK, 1, 2)),
+          ((128, 120, 99), B.RN_MIXED, (BLOCK, 1, 4)), ((128, 120, 99), B.RN_FP64, (BLOCK, 1, 4))]
+
+
+def ident(v):
+    return "x".join(map(str, v)) if isinstance(v, tuple) else ("mixed" if v == B.RN_MIXED else "fp64")
+
+
+def network(size, seed):
+    import torch
+    rng = np.random.default_rng(seed)
+    shape = size[::-1] if size[2] > 1 else size[1::-1]
+    return [torch.from_numpy(np.exp(rng.standard_normal(shape))).cuda() for _ in shape]
+
+
+def problem(size, g, p_out=None):
+    return B.problem(dim=len(g), nx=size[0], ny=size[1], nz=size[2], axis=0, g=g, p_out=p_out)
+
+
+def context(monkeypatch, loops):
+    monkeypatch.setenv("RN_LOOPS", loops)
+    c = B.Context(0)
+    monkeypatch.delenv("RN_LOOPS")
+    return c
+
+
+def tolerance(size):
+    return 1e-8 if size[0] * size[1] * size[2] < 100000 else 1e-6
+
+
+def bits(r):
+    return r.K, r.G, r.Q_in, r.Q_out, r.rel_resid, r.iters, r.refreshes
+
+
+def timed(ctx, prob, o):
+    """The solve's result and its timed launches, all of them of its own path and precision."""
+    ctx.set_timing(True)
+    r = ctx.solve(prob, o)
+    launches = ctx.stats()["pass_timed_launches"]
+    ctx.set_timing(False)
+    return r, launches
+
+
+@pytest.mark.parametrize("size,precision,plan", SHAPES, ids=ident)
+def test_loops_run(size, precision, plan, monkeypatch):
+    import torch
+    B.rn_tune_reset()
+    g = network(size, 3)
+    p = B.rn_plan(problem(size, g), B.opts(precision))
+    assert (p["path"], p["tiles_per_wg"], p["tile_z"]) == plan
+    torch.cuda.synchronize()
+    with context(monkeypatch, "1") as ctx:
+        r, launches = timed(ctx, problem(size, g), B.opts(precision, tolerance(size)))
+    n = launches[plan[0]][precision]
+    # without a loop every pass is a launch; with them a refresh and the passes up to the next one are two
+    assert 0 < n < (r.iters + r.refreshes) / 2, (n, r.iters, r.refreshes)
+    assert sum(map(sum, launches)) == n
+
+
+@pytest.mark.parametrize("size,precision,plan", SHAPES, ids=ident)
+def test_turned_away_bits(size, precision, plan, monkeypatch):
+    import torch
+    B.rn_tune_reset()
+    g = network(size, 4)
+    o = B.opts(precision, tolerance(size), max_iter=4000)
+    pw, pg = (torch.zeros(g[0].shape, dtype=torch.float64, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    with context(monkeypatch, "0") as plain, context(monkeypatch, "2") as away:
+        want = plain.solve(problem(size, g, pw), o, check=False)
+        for _ in range(2):
+            got, launches = timed(away, problem(size, g, pg), o)
+            assert bits(got) == bits(want)
+            assert torch.equal(pg, pw)
+            # the host has noticed: every pass was a launch
+            assert launches[plan[0]][precision] >= got.iters + got.refreshes
+
+
+@pytest.mark.parametrize("precision", [B.RN_MIXED, B.RN_FP64], ids=ident)
+def test_turned_away_gang_bits(precision, monkeypatch):
+    import torch
+    B.rn_tune_reset()
+    sizes = [(70, 60, 1), (200, 150, 1), (520, 515, 1), (20, 18, 17), (70, 66, 64), (64, 48, 40), (130, 70, 1)]
+    nets = [(s, network(s, 10 + i)) for i, s in enumerate(sizes)]
+    pw, pg = ([torch.zeros(g[0].shape, dtype=torch.float64, device="cuda") for _, g in nets] for _ in range(2))
+    o = B.opts(precision, 1e-6, max_iter=4000)
+    torch.cuda.synchronize()
+    with context(monkeypatch, "0") as plain, context(monkeypatch, "2") as away:
+        want = [plain.solve(problem(s, g, q), o, check=False) for (s, g), q in zip(nets, pw)]
+        got = away.solve_batch([problem(s, g, q) for (s, g), q in zip(nets, pg)], o, check=False)
+    for a, b, qa, qb in zip(got, want, pg, pw):
+        assert bits(a) == bits(b)
+        assert torch.equal(qa, qb)
