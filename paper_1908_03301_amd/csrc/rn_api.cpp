@@ -95,8 +95,8 @@ int tick(rn_ctx *ctx, Sched *S, bool *progressed)
         void *p = nullptr;
         hipError_t he = hipSuccess;
         // optional cap on the memory of the networks in flight (RN_ACTIVE_BYTES)
-        const bool capped = ctx->active_cap && ctx->pool.in_use() > 0 &&
-                            ctx->pool.in_use() + net->L.total > ctx->active_cap;
+        const size_t held = ctx->pool.in_use() - ctx->engine.exchange_bytes();
+        const bool capped = ctx->active_cap && held > 0 && held + net->L.total > ctx->active_cap;
         if (!capped) p = ctx->pool.alloc(net->L.total, &he);
         if (!p) {
             if (he != hipSuccess) {              // the device itself is out of memory
@@ -237,7 +237,10 @@ int drive_until(rn_ctx *ctx, Sched *S, const std::vector<Net *> &nets)
         if (r) return r;
         if (!prog) idle_wait(S);
     }
-    return RN_OK;
+    // the networks' last launches have ended: take their last status off the
+    // engine's books, which returns what it held for them
+    std::vector<Net *> none;
+    return ctx->engine.active_count() ? RN_OK : ctx->engine.collect(&none, true, ctx->stream, &ctx->err);
 }
 
 void fail_all(rn_ctx *ctx, Sched *S, int status)
@@ -707,6 +710,7 @@ int solve_many(rn_ctx *ctx, int32_t count, const rn_problem *probs, const rn_opt
                 fail_all(ctx, S, r);
                 (void)hipStreamSynchronize(ctx->stream);
                 (void)hipStreamSynchronize(ctx->side);
+                ctx->engine.release_exchange();
             }
         }
     }
@@ -858,7 +862,7 @@ int rn_create(int device, size_t budget, rn_ctx **out)
     if (hipStreamCreateWithFlags(&ctx->own, hipStreamNonBlocking) != hipSuccess) return fail();
     if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess) return fail();
     ctx->stream = ctx->own;
-    if (ctx->engine.init(ctx->stream, &ctx->err)) return fail();
+    if (ctx->engine.init(&ctx->pool, &ctx->err)) return fail();
     ctx->engine_ok = true;
     if (hipHostMalloc((void **)&ctx->h_small, 32 * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess)
         return fail();

@@ -414,9 +414,9 @@ void Pool::free(void *ptr)
 
 // ------------------------------------------------------------------ engine
 
-int Engine::init(hipStream_t st, std::string *err)
+int Engine::init(Pool *pool, std::string *err)
 {
-    (void)st;
+    pool_ = pool;
     std::fill(&loop_cap_[0][0][0][0], &loop_cap_[0][0][0][0] + sizeof(loop_cap_) / sizeof(int), -1);
     // Graph replay of pass rounds is opt-in (RN_GRAPHS=1): on a launch-bound
     // 128^2 solve it measured 5% slower than direct launches, since the time
@@ -442,6 +442,7 @@ int Engine::init(hipStream_t st, std::string *err)
     ENG_TRY(hipMemset(d_gate_, 0, kGates * kGateBytes));
     ENG_TRY(hipMalloc(&d_lpart_, loop_part_bytes()));
     ENG_TRY(hipMalloc(&d_coef_, kLoopMembers * kLoopCoefBytes));
+    ENG_TRY(hipMemset(d_coef_, 0, kLoopMembers * kLoopCoefBytes));
     ENG_TRY(hipMalloc(&d_gang_, sizeof(GangTables)));
     ENG_TRY(hipHostMalloc((void **)&h_gang_, 2 * sizeof(GangTables), hipHostMallocDefault));
     ENG_TRY(hipMalloc(&d_err_, 256));
@@ -480,9 +481,8 @@ void Engine::destroy()
     (void)hipFree(d_gang_);
     (void)hipHostFree(h_gang_);
     d_gang_ = h_gang_ = nullptr;
-    (void)hipFree(d_xch_);
-    d_coef_ = d_xch_ = nullptr;
-    xch_cap_ = 0;
+    release_exchange();
+    d_coef_ = nullptr;
     d_gate_ = nullptr;
     d_lpart_ = nullptr;
     (void)hipFree(d_err_);
@@ -886,26 +886,49 @@ size_t Engine::loop_words(const Net *net) const
                         : loop_exchange_words<float>(kind_dim(k), tz, net->L.ntiles);
 }
 
-// Exchange memory of two slots of `words` words. It holds nothing but tagged
+// Exchange memory of two slots of `words` words, from the context's pool: it
+// counts against the budget, and where the pool has none left (or the device)
+// there are no loops this chunk (*got false). It holds nothing but tagged
 // words: zero (no tag) when it is new and before the tags would start over.
-int Engine::loop_memory(size_t words, hipStream_t st, std::string *err)
+int Engine::loop_memory(size_t words, hipStream_t st, bool *got, std::string *err)
 {
-    const bool grow = 2 * words > xch_cap_, over = loop_tag_ > 0xf0000000u;
-    if (grow) {
+    *got = false;
+    if (2 * words > xch_cap_) {
+        if (xch_none_) return RN_OK;
         if (d_xch_) ENG_TRY(hipStreamSynchronize(st));
-        (void)hipFree(d_xch_);
-        d_xch_ = nullptr;
-        xch_cap_ = 0;
-        const size_t cap = std::max<size_t>(2 * words, (size_t)1 << 18);
-        ENG_TRY(hipMalloc(&d_xch_, cap * sizeof(unsigned long long)));
-        xch_cap_ = cap;
+        release_exchange();
+        // the gangs of a batch change from chunk to chunk: as much as they ever took, if there is room
+        const size_t most = active_.size() > 1 ? std::max<size_t>(xch_most_, (size_t)1 << 18) : 0;
+        hipError_t he = hipSuccess;
+        for (size_t cap : {std::max(2 * words, most), 2 * words}) {
+            d_xch_ = static_cast<unsigned long long *>(pool_->alloc(cap * sizeof(unsigned long long), &he));
+            if (!d_xch_) continue;
+            xch_cap_ = cap;
+            break;
+        }
+        if (!d_xch_) {
+            xch_none_ = he != hipSuccess;
+            return RN_OK;
+        }
+        xch_most_ = std::max(xch_most_, 2 * words);
+        ENG_TRY(launch_clear_u64(d_xch_, (int)xch_cap_, st));
     }
-    if (grow || over) {
+    if (loop_tag_ > kTagEnd) {
         ENG_TRY(launch_clear_u64(d_xch_, (int)xch_cap_, st));
         ENG_TRY(launch_clear_u64(d_coef_, (int)(kLoopMembers * kLoopCoefBytes / sizeof(unsigned long long)), st));
-        if (over) loop_tag_ = 1;
+        loop_tag_ = 1;
     }
+    *got = true;
     return RN_OK;
+}
+
+// Give the exchange memory back (nothing in flight uses it).
+void Engine::release_exchange()
+{
+    if (d_xch_) pool_->free(d_xch_);
+    d_xch_ = nullptr;
+    xch_cap_ = 0;
+    xch_none_ = false;
 }
 
 // Arguments of the next loop launch: its gates (kGates sets in turn) and tags.
@@ -937,17 +960,13 @@ LoopArgs Engine::loop_args(size_t words, int limit)
 // one is due) and a loop of up to kGangLimit passes: networks that reach a
 // refresh earlier wait for the others, hence the small limit. The rounds of a
 // chunk are even in number, so the parities of waiting networks stay right.
-int Engine::launch_gangs(bool first, int *launched, hipStream_t st, std::string *err)
+// plan_gangs picks the networks and writes their tables; *most: words of an
+// exchange slot.
+std::vector<Engine::Gang> Engine::plan_gangs(size_t *most)
 {
-    struct Gang {
-        int kind, tpw, tz;
-        std::vector<Net *> nets;
-        size_t words = 0;
-        int pass0 = 0, npass = 0, loop0 = 0, nloop = 0, net0 = 0;
-    };
     std::vector<Gang> gangs;
     for (Net *n : active_) {
-        if (!n->in_loop) continue;
+        if (!n->fits_loop) continue;
         const int tz = n->L.dim == 3 ? n->L.tile_z : 0;
         Gang *g = nullptr;
         for (Gang &q : gangs)
@@ -960,7 +979,7 @@ int Engine::launch_gangs(bool first, int *launched, hipStream_t st, std::string 
     }
     gang_half_ ^= 1;
     GangTables *h = h_gang_ + gang_half_;
-    size_t most = 0;
+    *most = 0;
     int np = 0, nl = 0, nn = 0;
     for (Gang &g : gangs) {
         // the ones that have waited longest first (a stable order otherwise)
@@ -981,8 +1000,6 @@ int Engine::launch_gangs(bool first, int *launched, hipStream_t st, std::string 
         g.net0 = nn;
         int member = 0, block0 = 0;
         for (Net *n : g.nets) {
-            n->gang_seq = chunk_seq_ + 1;
-            n->loop_used = true;
             for (int b = 0; b < n->L.grid; ++b) h->pass[np++] = make_uint2((unsigned)n->slot, (unsigned)b);
             const int m = loop_blocks(dim, n->L.tpw, n->L.grid);
             for (int b = 0; b < m; ++b) h->loop[nl++] = make_uint2((unsigned)n->slot, (unsigned)(member << 16 | b));
@@ -993,11 +1010,20 @@ int Engine::launch_gangs(bool first, int *launched, hipStream_t st, std::string 
         }
         g.npass = block0;
         g.nloop = blocks;
-        most = std::max(most, g.words);
+        *most = std::max(*most, g.words);
     }
-    int r = loop_memory(most, st, err);
-    if (r) return r;
-    ENG_TRY(hipMemcpyAsync(d_gang_, h, sizeof(GangTables), hipMemcpyHostToDevice, st));
+    return gangs;
+}
+
+int Engine::launch_gangs(const std::vector<Gang> &gangs, bool first, int *launched, hipStream_t st, std::string *err)
+{
+    int r = RN_OK;
+    for (const Gang &g : gangs)
+        for (Net *n : g.nets) {
+            n->gang_seq = chunk_seq_ + 1;
+            n->loop_used = true;
+        }
+    ENG_TRY(hipMemcpyAsync(d_gang_, h_gang_ + gang_half_, sizeof(GangTables), hipMemcpyHostToDevice, st));
     recording_ = timing_;
     tmirror_ = next_mirror_;
     if (recording_ && first) r = record_timing(-1, st, err);   // else the shared rounds began the chunk's record
@@ -1051,12 +1077,7 @@ int Engine::launch_loops(Net *net, int *launched, hipStream_t st, std::string *e
     }
     const int tz = net->L.dim == 3 ? net->L.tile_z : 0;
     const size_t words = loop_words(net);
-    int r = loop_memory(words, st, err);
-    if (r) {
-        recording_ = false;
-        return r;
-    }
-    int n = 0;
+    int r = RN_OK, n = 0;
     auto one = [&](bool loop) -> int {
         const int par = (int)(rounds_ & 1);
         if (loop) {
@@ -1117,16 +1138,29 @@ int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
     // networks that fit resident loops run in those, the others in shared rounds
     size_t loops = 0;
     for (Net *n : active_) {
-        bool fits = false;
-        int r = loop_fits(n, active_.size() == 1, &fits, err);
+        int r = loop_fits(n, active_.size() == 1, &n->fits_loop, err);
         if (r) return r;
-        if (fits != n->in_loop) dirty_ = true;
-        n->in_loop = fits;
-        loops += fits ? 1 : 0;
+        loops += n->fits_loop ? 1 : 0;
+    }
+    std::vector<Gang> gangs;
+    if (loops) {
+        size_t words = 0;
+        if (active_.size() == 1) words = loop_words(active_[0]);
+        else gangs = plan_gangs(&words);
+        bool got = false;
+        int r = loop_memory(words, st, &got, err);
+        if (r) return r;
+        if (!got) loops = 0;
+    }
+    for (Net *n : active_) {
+        const bool in_loop = loops && n->fits_loop;
+        if (in_loop != n->in_loop) dirty_ = true;
+        n->in_loop = in_loop;
     }
     if (loops == active_.size()) {
         int launched = 0;
-        int r = loops == 1 ? launch_loops(active_[0], &launched, st, err) : launch_gangs(true, &launched, st, err);
+        int r = loops == 1 ? launch_loops(active_[0], &launched, st, err)
+                           : launch_gangs(gangs, true, &launched, st, err);
         return r ? r : queue_status(launched, st, err);
     }
     if (loops) rounds += rounds & 1;   // the networks in loops sit out an even number of rounds
@@ -1169,7 +1203,7 @@ int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
         if (nblk_[k]) launches_ += (persist_ && kind_coh_[k] != 0) ? 1 : rounds;
     if (loops) {
         int launched = 0;
-        int r = launch_gangs(false, &launched, st, err);
+        int r = launch_gangs(gangs, false, &launched, st, err);
         if (r) return r;
         rounds += launched;
     }
@@ -1259,6 +1293,7 @@ int Engine::collect(std::vector<Net *> *finished, bool all, hipStream_t st, std:
         if (min_iters != INT64_MAX) next = (int)std::min<int64_t>(next, std::max<int64_t>(16, min_iters / 4));
         chunk_ = active_.empty() ? 16 : next;
     }
+    if (active_.empty() && outstanding_.empty()) release_exchange();
     return RN_OK;
 }
 

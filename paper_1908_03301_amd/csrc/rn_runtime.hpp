@@ -113,6 +113,7 @@ struct Net {
     double prev_est = -1.0;
     int64_t prev_iters = 0;
     bool loop_ok = true;            // may run in resident loops (no launch of one was turned away yet)
+    bool fits_loop = false;         // a resident loop of it fits the chip
     bool in_loop = false;           // runs in resident loops this chunk
     bool loop_local = false;        // ... on one XCD
     int64_t gang_seq = 0;           // last chunk it ran in beside others
@@ -128,7 +129,7 @@ public:
     // kinds: 0 2D full tiles, 1 3D, 2 and 3 the same in FP64, 4 2D small tiles, 5 the same in FP64
     static constexpr int kKinds = 6;
 
-    int init(hipStream_t st, std::string *err);
+    int init(Pool *pool, std::string *err);
     void destroy();
     bool full() const { return free_slots_.empty(); }
     // enqueue upload, validation, connectivity and counters of a network
@@ -149,6 +150,9 @@ public:
     int64_t launches() const { return launches_; }
     int64_t chunk_seq() const { return chunk_seq_; }
     int peak_active() const { return peak_active_; }
+    // bytes of the pool that the engine itself holds while networks run in resident loops
+    size_t exchange_bytes() const { return xch_cap_ * sizeof(unsigned long long); }
+    void release_exchange();
     // forget every network (after a device error): slots, tables, mirrors
     void abort_all();
     // stream for setup and output copies (nullptr: everything on the compute stream)
@@ -233,14 +237,24 @@ private:
     GangTables *d_gang_ = nullptr, *h_gang_ = nullptr;   // host staging x2
     int loop_fits(Net *net, bool alone, bool *fits, std::string *err);
     size_t loop_words(const Net *net) const;
-    int loop_memory(size_t words, hipStream_t st, std::string *err);
+    int loop_memory(size_t words, hipStream_t st, bool *got, std::string *err);
     LoopArgs loop_args(size_t words, int limit);
     int launch_loops(Net *net, int *launched, hipStream_t st, std::string *err);
-    int launch_gangs(bool first, int *launched, hipStream_t st, std::string *err);
+    struct Gang {                            // networks of one loop kernel that run beside each other
+        int kind, tpw, tz;
+        std::vector<Net *> nets;
+        size_t words = 0;
+        int pass0 = 0, npass = 0, loop0 = 0, nloop = 0, net0 = 0;
+    };
+    std::vector<Gang> plan_gangs(size_t *most);
+    int launch_gangs(const std::vector<Gang> &gangs, bool first, int *launched, hipStream_t st, std::string *err);
     int queue_status(int rounds, hipStream_t st, std::string *err);
     char *d_gate_ = nullptr;                 // kGates sets of gates, used in turn, each cleared kGates / 2 launches later
     unsigned long long *d_xch_ = nullptr, *d_coef_ = nullptr;   // edge values and coefficients of the loops
-    size_t xch_cap_ = 0;                     // words of d_xch_ (at most 44 MB, freed with the engine)
+    Pool *pool_ = nullptr;                   // d_xch_ comes from it and goes back when no network is left
+    size_t xch_cap_ = 0, xch_most_ = 0;      // words of d_xch_ (at most 44 MB), the most any chunk took
+    bool xch_none_ = false;                  // the device refused it: not asked again before the engine is idle
+    static constexpr unsigned kTagEnd = 0xf0000000u;
     unsigned loop_tag_ = 1;                  // first pass number of the next loop
     double *d_lpart_ = nullptr;              // partial sums of a resident loop
     int gate_ = 0;
