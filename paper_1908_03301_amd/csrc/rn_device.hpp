@@ -250,7 +250,6 @@ struct LoopArgs {
     int limit;
     const uint2 *blk;        // nullptr: one network
     const LoopNet *net;
-    int turn_away;           // 1: the gate admits nobody (a check of what follows then)
 };
 constexpr int kLoopMembers = 64, kLoopGateWords = 16;
 constexpr size_t kLoopCoefBytes = 2048;
@@ -272,6 +271,10 @@ size_t loop_exchange_words(int dim, int tile_z, int ntiles);
 template <typename T>
 hipError_t launch_loop(int dim, int tpw, int tile_z, bool local, int blocks, const PassArgs<T> *tab, Scalars *scal, int parity,
                        int slot, const LoopArgs &r, hipStream_t st);
+
+// make the gates of the loop launch behind this one turn everybody away (a
+// check of what follows then)
+hipError_t launch_shut_gates(unsigned *gate, hipStream_t st);
 
 // tile geometry of the pass kernels: a 2D workgroup tile is 64 kSEG2f x
 // 4 kTY2f (FP32) or 64 kSEG2d x 4 kTY2d (FP64): each wave holds kTY2f / kTY2d

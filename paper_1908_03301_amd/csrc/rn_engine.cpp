@@ -947,7 +947,6 @@ LoopArgs Engine::loop_args(size_t words, int limit)
     a.limit = limit;
     a.blk = nullptr;
     a.net = nullptr;
-    a.turn_away = loops_mode_ == 2 ? 1 : 0;
     return a;
 }
 
@@ -1035,6 +1034,7 @@ int Engine::launch_gangs(const std::vector<Gang> &gangs, bool first, int *launch
                 hipError_t e;
                 if (loop) {
                     LoopArgs a = loop_args(g.words, kGangLimit);
+                    if (loops_mode_ == 2) ENG_TRY(launch_shut_gates(a.gate, st));
                     a.blk = d_gang_->loop + g.loop0;
                     a.net = d_gang_->net + g.net0;
                     e = kind_fp64(g.kind)
@@ -1086,6 +1086,7 @@ int Engine::launch_loops(Net *net, int *launched, hipStream_t st, std::string *e
             const bool wide = 4 * net->L.grid > loop_cap_[k][net->L.tpw - 1][tz][0];
             const LoopArgs a = loop_args(words, wide ? kLoopLimit / 2 : kLoopLimit);
             const int blocks = net->loop_local ? net->L.grid : loop_blocks(dim, net->L.tpw, net->L.grid);
+            if (loops_mode_ == 2) ENG_TRY(launch_shut_gates(a.gate, st));
             if (!kind_fp64(k)) ENG_TRY(launch_loop<float>(dim, net->L.tpw, tz, net->loop_local, blocks, d_tabf_, d_scal_, par, slot, a, st));
             else ENG_TRY(launch_loop<double>(dim, net->L.tpw, tz, net->loop_local, blocks, d_tabd_, d_scal_, par, slot, a, st));
         } else if (!kind_fp64(k)) {

@@ -178,12 +178,10 @@ __device__ __forceinline__ int pass_gate(unsigned *gate, bool has_place, unsigne
     return state == kGateGo;
 }
 
-// This workgroup's network and its place in it (kNoPlace and any number past
-// the network's workgroups: none). One workgroup is launched per place, or
+// This workgroup's network and its place in it (negative, or past the network's
+// workgroups: none). One workgroup is launched per place, or
 // (LOCAL) per place and XCD, those on XCD 0 claiming one. r: the launch's
-// arguments, made this network's. With turn_away the gate waits for a
-// workgroup that was never launched, or no XCD is the one.
-constexpr int kNoPlace = 1 << 30;
+// arguments, made this network's.
 struct Place {
     int slot, lb;
 };
@@ -196,8 +194,7 @@ __device__ __forceinline__ Place loop_place(LoopArgs &r, int slot)
     Place p = {slot, (int)blockIdx.x};
     if constexpr (LOCAL) {
         __shared__ int place;
-        const int xcd = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20)) & 7;   // XCC_ID
-        if (xcd || r.turn_away) return {slot, kNoPlace};
+        if (__builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20)) & 7) return {slot, -1};   // XCC_ID
         if (threadIdx.x == 0)
             place = (int)__hip_atomic_fetch_add(r.gate + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
@@ -230,7 +227,7 @@ struct LoopState {
 // The gate's answer for the whole workgroup.
 __device__ __forceinline__ bool loop_gate(LoopShared &sh, bool has_place, int places, Scalars *s, const LoopArgs &r)
 {
-    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, has_place, (unsigned)(places + (r.turn_away ? 1 : 0)), s);
+    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, has_place, (unsigned)places, s);
     __syncthreads();
     return sh.go != 0;
 }
@@ -499,7 +496,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
     const int grid = a.grid, lb = at_.lb;
     if constexpr (LOCAL) {
         if (s->mode != MODE_CG) return;
-        if (lb >= grid) {                          // no place
+        if (lb < 0 || lb >= grid) {                // no place
             if ((int)blockIdx.x < grid && !loop_gate(sh, false, grid, s, r)) move_state(a, (int)blockIdx.x, grid);
             return;
         }
@@ -890,6 +887,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     __shared__ double fl[TZ * R][kBlock];
     __shared__ LoopShared sh;
     const Place at_ = loop_place<false>(r, slot);
+    if (at_.lb < 0) return;
     const PassArgs<T> &a = tab[2 * at_.slot + parity];
     Scalars *s = scal + at_.slot;
     const int grid = a.grid, lb = at_.lb;
@@ -1270,6 +1268,19 @@ size_t loop_exchange_words(int dim, int tile_z, int ntiles)
 {
     const size_t values = dim == 3 ? face_words3d(tile_z) : dim == 2 ? edge_words2d<T, 0>() : edge_words2d<T, 1>();
     return values * (sizeof(T) / 4) * (size_t)ntiles;
+}
+
+// A launch that every gate turns away: no count reaches the number that opens
+// it, and (LOCAL) every place is taken.
+__global__ void shut_gates_kernel(unsigned *gate)
+{
+    gate[threadIdx.x * kLoopGateWords] = gate[threadIdx.x * kLoopGateWords + 2] = 1u << 30;
+}
+
+hipError_t launch_shut_gates(unsigned *gate, hipStream_t st)
+{
+    shut_gates_kernel<<<1, kLoopMembers, 0, st>>>(gate);
+    return hipGetLastError();
 }
 
 template <typename T>
