@@ -1082,10 +1082,10 @@ int Engine::launch_loops(Net *net, int *launched, hipStream_t st, std::string *e
         const int par = (int)(rounds_ & 1);
         if (loop) {
             // a loop that holds more than a quarter of the chip makes way for other
-            // streams' kernels twice as often (every 1 to 5 ms)
-            const bool wide = 4 * net->L.grid > loop_cap_[k][net->L.tpw - 1][tz][0];
-            const LoopArgs a = loop_args(words, wide ? kLoopLimit / 2 : kLoopLimit);
+            // streams' kernels twice as often (every 1 to 5 ms); one on a single XCD never does
             const int blocks = net->loop_local ? net->L.grid : loop_blocks(dim, net->L.tpw, net->L.grid);
+            const bool wide = !net->loop_local && 4 * blocks > loop_cap_[k][net->L.tpw - 1][tz][0];
+            const LoopArgs a = loop_args(words, wide ? kLoopLimit / 2 : kLoopLimit);
             if (loops_mode_ == 2) ENG_TRY(launch_shut_gates(a.gate, st));
             if (!kind_fp64(k)) ENG_TRY(launch_loop<float>(dim, net->L.tpw, tz, net->loop_local, blocks, d_tabf_, d_scal_, par, slot, a, st));
             else ENG_TRY(launch_loop<double>(dim, net->L.tpw, tz, net->loop_local, blocks, d_tabd_, d_scal_, par, slot, a, st));

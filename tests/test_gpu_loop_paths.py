@@ -108,3 +108,22 @@ def test_turned_away_gang_bits(precision, monkeypatch):
     for a, b, qa, qb in zip(got, want, pg, pw):
         assert bits(a) == bits(b)
         assert torch.equal(qa, qb)
+
+
+def test_launches_do_not_depend_on_earlier_calls(monkeypatch):
+    """1,000 passes on one XCD are two loops of at most 512, before and after a batch ran the same shape
+    on the whole chip."""
+    import torch
+    B.rn_tune_reset()
+    size = (64, 120, 1)
+    g = network(size, 6)
+    o = B.opts(B.RN_FP64, 1e-30, max_iter=1000)
+    torch.cuda.synchronize()
+    with context(monkeypatch, "1") as ctx:
+        first, a = timed(ctx, problem(size, g), o)
+        ctx.solve_batch([problem(size, g), problem(size, g)], o, check=False)
+        again, b = timed(ctx, problem(size, g), o)
+    assert bits(first) == bits(again) and first.iters == 1000
+    # a chunk is a pass and a loop, twice, the first with a pass more (two refreshes): all iterations
+    # in the first, the last refresh in the second, and the idle chunk that is on its way by then
+    assert a == b and a[SMALL][B.RN_FP64] == 5 + 4 + 4
