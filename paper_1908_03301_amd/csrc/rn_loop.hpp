@@ -224,10 +224,12 @@ struct LoopState {
     double alpha, beta, sa;
 };
 
-// The gate's answer for the whole workgroup.
-__device__ __forceinline__ bool loop_gate(LoopShared &sh, bool has_place, int places, Scalars *s, const LoopArgs &r)
+// The gate's answer for the whole workgroup. A network that was turned away
+// once is turned away at once by the loops launched before the host knew.
+__device__ __forceinline__ bool loop_gate(LoopShared &sh, bool has_place, int places, Scalars *s, const Scalars *copy,
+                                          const LoopArgs &r)
 {
-    if (threadIdx.x == 0) sh.go = pass_gate(r.gate, has_place, (unsigned)places, s);
+    if (threadIdx.x == 0) sh.go = copy->loop_aborts ? 0 : pass_gate(r.gate, has_place, (unsigned)places, s);
     __syncthreads();
     return sh.go != 0;
 }
@@ -251,7 +253,7 @@ __device__ __forceinline__ bool loop_begin(LoopShared &sh, LoopState &L, Scalars
     L.sa = s->sigma * s->alpha;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    return loop_gate(sh, true, 8 * div_up(grid >> 3, nlb), s, r);
+    return loop_gate(sh, true, 8 * div_up(grid >> 3, nlb), s, &sh.sl[0], r);
 }
 
 // The four sums of a workgroup of the pass kernels, as in finish_pass: thread
@@ -497,7 +499,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
     if constexpr (LOCAL) {
         if (s->mode != MODE_CG) return;
         if (lb < 0 || lb >= grid) {                // no place
-            if ((int)blockIdx.x < grid && !loop_gate(sh, false, grid, s, r)) move_state(a, (int)blockIdx.x, grid);
+            if ((int)blockIdx.x < grid && !loop_gate(sh, false, grid, s, s, r)) move_state(a, (int)blockIdx.x, grid);
             return;
         }
     } else if (lb >= grid || s->mode != MODE_CG) {

@@ -127,3 +127,28 @@ def test_launches_do_not_depend_on_earlier_calls(monkeypatch):
     # a chunk is a pass and a loop, twice, the first with a pass more (two refreshes): all iterations
     # in the first, the last refresh in the second, and the idle chunk that is on its way by then
     assert a == b and a[SMALL][B.RN_FP64] == 5 + 4 + 4
+
+
+def test_turned_away_waits_once(monkeypatch):
+    """A gate gives up after 0.5 ms. The loops that were launched before the host knew (two chunks of two,
+    the last of them after four iterations) do not wait again: the device is held by one such wait, not three."""
+    import torch
+    B.rn_tune_reset()
+    size = (64, 120, 1)
+    g = network(size, 7)
+    o = B.opts(B.RN_FP64, 1e-30, max_iter=4)     # few passes: all else is some tens of microseconds
+    torch.cuda.synchronize()
+
+    def device_time(ctx):
+        best = 1e9
+        for _ in range(8):
+            ctx.set_timing(True)
+            ctx.solve(problem(size, g), o)
+            best = min(best, sum(map(sum, ctx.stats()["pass_device_s"])))
+            ctx.set_timing(False)
+        return best
+
+    with context(monkeypatch, "0") as plain, context(monkeypatch, "2") as away:
+        more = device_time(away) - device_time(plain)
+    print(f"turned away: {1e3 * more:.3f} ms more", flush=True)
+    assert more < 1.0e-3
