@@ -37,10 +37,10 @@
 // All workgroups have to run at once. They are admitted by a gate: each counts
 // itself in, and the launch goes ahead only if all arrive in time; otherwise
 // they move z and u to the parity of the next round, change nothing else, and
-// the host goes on with one launch per pass. Who moves what does not depend on
-// who got a place: the dispatcher need not have dealt the workgroups of a LOCAL
-// launch evenly to the XCDs (a stream with a CU mask, another partition mode),
-// so the first of them wait for the gate's answer wherever they are.
+// the host goes on with one launch per pass. In a LOCAL launch that does not
+// depend on who got a place, since the dispatcher need not have dealt its
+// workgroups evenly to the XCDs (a stream with a CU mask, another partition
+// mode): the first one waits for the gate's answer wherever it is and moves all.
 // Behind the gate every wait is bounded too (kSpinTicks).
 //
 // The arithmetic and its order are those of the pass kernels (tile by tile,
@@ -441,13 +441,13 @@ __device__ __forceinline__ void sti(T *base, int i, T v)
     *reinterpret_cast<RN_GLOBAL T *>((RN_GLOBAL char *)base + (unsigned)i * (unsigned)sizeof(T)) = v;
 }
 
-// A LOCAL launch that was turned away: workgroup b of `blocks` moves its share
-// of z and u to the parity that the next round reads.
+// A LOCAL launch that was turned away: one workgroup moves z and u (at most
+// 16,384 nodes) to the parity that the next round reads.
 template <typename T>
-__device__ __forceinline__ void move_state(const PassArgs<T> &a, int b, int blocks)
+__device__ __forceinline__ void move_state(const PassArgs<T> &a)
 {
     const int n = a.nx * a.ny * a.nz;
-    for (int i = b * kBlock + (int)threadIdx.x; i < n; i += blocks * kBlock) {
+    for (int i = (int)threadIdx.x; i < n; i += kBlock) {
         sti(a.dst.z, i, ldi(a.src.z, i));
         sti(a.dst.u, i, ldi(a.src.u, i));
     }
@@ -498,8 +498,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
     const int grid = a.grid, lb = at_.lb;
     if constexpr (LOCAL) {
         if (s->mode != MODE_CG) return;
-        if (lb < 0 || lb >= grid) {                // no place
-            if ((int)blockIdx.x < grid && !loop_gate(sh, false, grid, s, s, r)) move_state(a, (int)blockIdx.x, grid);
+        if (__builtin_expect(lb < 0 || lb >= grid, 0)) {                // no place
+            if (blockIdx.x == 0 && !loop_gate(sh, false, grid, s, s, r)) move_state(a);
             return;
         }
     } else if (lb >= grid || s->mode != MODE_CG) {
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
     const bool admitted = loop_begin<LOCAL>(sh, L, s, r, lbs, LB, grid);
 
     int it = 0;
-    for (bool on = admitted; on; ++it) {
+    for (bool on = __builtin_expect(admitted, 1); on; ++it) {
         Spin spin(s);
         const T alpha = (T)rfl(L.alpha), beta = (T)rfl(L.beta);
         const double sa = rfl(L.sa);
@@ -837,11 +837,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
     // ---- the state of the last pass, as a pass kernel leaves it (alpha is the
     // one pending step). A launch that was turned away moves z and u to the
     // other parity, where the next round reads them, and no more.
-    if constexpr (LOCAL)
-        if (!admitted) {
-            if ((int)blockIdx.x < grid) move_state(a, (int)blockIdx.x, grid);
-            return;
-        }
     const int64_t done = passes0 + it - 1;
     T *pd = a.pbuf[a.npbuf == 5 ? (int)(done % 5) : (int)(done % 3)];
 #pragma unroll
@@ -863,6 +858,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LB > 1 ?
                 }
     if (admitted && lb == 0)                               // wave 0 ran the last step on this copy
         store_loop_end(reinterpret_cast<u64 *>(s), reinterpret_cast<const volatile u64 *>(&sh.sl[0]), (int)threadIdx.x);
+    if constexpr (LOCAL)
+        if (!admitted && blockIdx.x == 0) move_state(a);
 }
 
 // ---------------------------------------------------------------- 3D
@@ -1041,7 +1038,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     const bool admitted = loop_begin<false>(sh, L, s, r, lbs, 1, grid);
 
     int it = 0;
-    for (bool on = admitted; on; ++it) {
+    for (bool on = __builtin_expect(admitted, 1); on; ++it) {
         Spin spin(s);
         const T alpha = (T)rfl(L.alpha), beta = (T)rfl(L.beta);
         const double sa = rfl(L.sa);
