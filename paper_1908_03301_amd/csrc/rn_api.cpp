@@ -238,7 +238,7 @@ int drive_until(rn_ctx *ctx, Sched *S, const std::vector<Net *> &nets)
         if (!prog) idle_wait(S);
     }
     // the networks' last launches have ended: take their last status off the
-    // engine's books, which returns what it held for them
+    // engine's books, so that it counts as idle
     std::vector<Net *> none;
     return ctx->engine.active_count() ? RN_OK : ctx->engine.collect(&none, true, ctx->stream, &ctx->err);
 }
@@ -1210,7 +1210,7 @@ int rn_stats(rn_ctx *ctx, rn_stats_t *out)
     out->preparing = (int64_t)S->preparing.size();
     out->active = ctx->engine.active_count();
     out->finishing = (int64_t)S->finishing.size();
-    out->bytes_in_use = (int64_t)ctx->pool.in_use();
+    out->bytes_in_use = (int64_t)(ctx->pool.in_use() - ctx->engine.exchange_bytes());
     out->budget = (int64_t)ctx->pool.budget();
     out->launches = ctx->engine.launches();
     out->peak_active = ctx->engine.peak_active();

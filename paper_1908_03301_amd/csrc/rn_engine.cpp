@@ -326,6 +326,13 @@ void Pool::release_all()
 
 void *Pool::alloc(size_t bytes, hipError_t *err)
 {
+    void *p = carve(bytes, err);
+    if (!p && give_back_ && give_back_()) p = carve(bytes, err);
+    return p;
+}
+
+void *Pool::carve(size_t bytes, hipError_t *err)
+{
     *err = hipSuccess;
     bytes = align256(bytes ? bytes : 256);
     for (auto &s : slabs_) {
@@ -417,6 +424,13 @@ void Pool::free(void *ptr)
 int Engine::init(Pool *pool, std::string *err)
 {
     pool_ = pool;
+    // the exchange memory stays with the engine from solve to solve (its words
+    // need no clearing then) until the pool has no room for something else
+    pool->set_give_back([this] {
+        if (!d_xch_ || !active_.empty() || !outstanding_.empty()) return false;
+        release_exchange();
+        return true;
+    });
     std::fill(&loop_cap_[0][0][0][0], &loop_cap_[0][0][0][0] + sizeof(loop_cap_) / sizeof(int), -1);
     // Graph replay of pass rounds is opt-in (RN_GRAPHS=1): on a launch-bound
     // 128^2 solve it measured 5% slower than direct launches, since the time
@@ -1294,7 +1308,7 @@ int Engine::collect(std::vector<Net *> *finished, bool all, hipStream_t st, std:
         if (min_iters != INT64_MAX) next = (int)std::min<int64_t>(next, std::max<int64_t>(16, min_iters / 4));
         chunk_ = active_.empty() ? 16 : next;
     }
-    if (active_.empty() && outstanding_.empty()) release_exchange();
+    if (active_.empty() && outstanding_.empty()) xch_none_ = false;
     return RN_OK;
 }
 

@@ -12,6 +12,7 @@
 #include <condition_variable>
 #include <cstdint>
 #include <deque>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <string>
@@ -33,6 +34,8 @@ public:
     size_t in_use() const { return in_use_; }
     // nullptr with *err = hipSuccess when the request does not fit the budget now
     void *alloc(size_t bytes, hipError_t *err);
+    // asked when a request finds no room: returns whether it freed any (a workspace kept for later)
+    void set_give_back(std::function<bool()> f) { give_back_ = std::move(f); }
     void free(void *p);
     void release_all();
     // hipFree every slab that nothing is carved from
@@ -46,6 +49,8 @@ private:
         std::map<size_t, size_t> free_;   // offset -> length
         std::map<size_t, size_t> used_;   // offset -> length
     };
+    void *carve(size_t bytes, hipError_t *err);
+    std::function<bool()> give_back_;
     std::vector<Slab> slabs_;
     size_t budget_ = 0, reserved_ = 0, in_use_ = 0;
 };
@@ -150,8 +155,8 @@ public:
     int64_t launches() const { return launches_; }
     int64_t chunk_seq() const { return chunk_seq_; }
     int peak_active() const { return peak_active_; }
-    // bytes of the pool that the engine itself holds while networks run in resident loops
-    size_t exchange_bytes() const { return xch_cap_ * sizeof(unsigned long long); }
+    // bytes of the pool that the engine itself holds for resident loops
+    size_t exchange_bytes() const { return (xch_cap_ * sizeof(unsigned long long) + 255) & ~(size_t)255; }
     void release_exchange();
     // forget every network (after a device error): slots, tables, mirrors
     void abort_all();
@@ -251,7 +256,7 @@ private:
     int queue_status(int rounds, hipStream_t st, std::string *err);
     char *d_gate_ = nullptr;                 // kGates sets of gates, used in turn, each cleared kGates / 2 launches later
     unsigned long long *d_xch_ = nullptr, *d_coef_ = nullptr;   // edge values and coefficients of the loops
-    Pool *pool_ = nullptr;                   // d_xch_ comes from it and goes back when no network is left
+    Pool *pool_ = nullptr;                   // d_xch_ comes from it, is kept, and goes back when the pool needs it
     size_t xch_cap_ = 0, xch_most_ = 0;      // words of d_xch_ (at most 44 MB), the most any chunk took
     bool xch_none_ = false;                  // the device refused it: not asked again before the engine is idle
     static constexpr unsigned kTagEnd = 0xf0000000u;

@@ -1,6 +1,6 @@
 """The words that resident loops exchange live in the context's HBM budget: a
 budget that leaves them no room keeps a network on one launch per pass, with the
-same bits, and what they took goes back when the solve ends."""
+same bits, and what they keep makes way for a request that needs it."""
 import numpy as np
 import pytest
 
@@ -43,6 +43,26 @@ def test_budget_without_room(n, precision):
             print(f"{used} bytes taken, budget {budget}", flush=True)
             assert tight.stats()["bytes_in_use"] == 0
     assert used <= budget + (2 << 20), (used, budget)
+
+
+def test_kept_memory_makes_way():
+    """What a solve left for the next is given back to a request that needs the whole budget."""
+    import torch
+    B.rn_tune_reset()
+    small, big = network(700, 1), network(1600, 2)
+    torch.cuda.synchronize()
+    pb = B.problem(dim=2, nx=1600, ny=1600, nz=1, axis=0, g=big)
+    o = B.opts(B.RN_MIXED, 1e-8, max_iter=40)
+    ps = B.problem(dim=2, nx=700, ny=700, nz=1, axis=0, g=small)
+    with B.Context(0, B.rn_footprint(pb, o)) as ctx:
+        for _ in range(2):
+            ctx.set_timing(True)
+            r = ctx.solve(ps, o, check=False)
+            n = ctx.stats()["pass_timed_launches"][B.RN_PATH_2D_FULL][B.RN_MIXED]
+            ctx.set_timing(False)
+            assert r.iters == 40 and n < 40          # in loops
+            r = ctx.solve(pb, o, check=False)
+            assert r.iters == 40 and r.status == B.RN_ENOCONV
 
 
 def test_batch_in_a_budget_without_room():
