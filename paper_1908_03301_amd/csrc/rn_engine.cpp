@@ -699,6 +699,7 @@ int Engine::after_prepare(Net *net, hipStream_t st, std::string *err)
     net->prev_iters = 0;
     net->loop_ok = true;
     net->loop_used = false;
+    net->shared_rounds = 0;
     net->phase = NET_ACTIVE;
     active_.push_back(net);
     dirty_ = true;
@@ -1216,6 +1217,8 @@ int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
     rounds_ += rounds;
     for (int k = 0; k < kKinds; ++k)
         if (nblk_[k]) launches_ += (persist_ && kind_coh_[k] != 0) ? 1 : rounds;
+    for (Net *n : active_)
+        if (!n->in_loop) n->shared_rounds += rounds;
     if (loops) {
         int launched = 0;
         int r = launch_gangs(gangs, false, &launched, st, err);
@@ -1345,7 +1348,8 @@ int Engine::finalize(Net *net, const Scalars &h, hipStream_t st, std::string *er
     r.n_live = net->n_live;
     // a resident loop runs many pass rounds in one launch: count the passes then
     r.passes = net->loop_used ? h.passes : rounds_ - net->round0;
-    if (net->loop_used) launches_ += h.passes;
+    // (a network turned away by a loop ran its last ones in shared rounds, counted there)
+    if (net->loop_used) launches_ += std::max<int64_t>(h.passes - net->shared_rounds, 0);
     if (r.status == 0 && !r.converged) r.status = RN_ENOCONV;
     net->status = r.status;
     const double *P_final = (const double *)(base + L.off_P) + (size_t)(h.refreshes & 1) * n;

@@ -123,6 +123,7 @@ struct Net {
     bool loop_local = false;        // ... on one XCD
     int64_t gang_seq = 0;           // last chunk it ran in beside others
     bool loop_used = false;         // a chunk of resident loops was launched
+    int64_t shared_rounds = 0;      // rounds shared with others, or alone without a loop
     int64_t first_chunk = 0;        // first chunk whose status mirror covers this network
     // host copies (server path: the caller's buffers stay valid until completion)
 };

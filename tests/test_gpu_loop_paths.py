@@ -152,3 +152,21 @@ def test_turned_away_waits_once(monkeypatch):
         more = device_time(away) - device_time(plain)
     print(f"turned away: {1e3 * more:.3f} ms more", flush=True)
     assert more < 1.0e-3
+
+
+def test_launch_count_of_a_network_turned_away(monkeypatch):
+    """rn_stats.launches of a solve that starts in loops and goes on without: each pass once, and at most
+    the idle rounds of a chunk (256) more."""
+    import torch
+    B.rn_tune_reset()
+    size = (64, 120, 1)
+    g = network(size, 8)
+    o = B.opts(B.RN_FP64, 1e-30, max_iter=2000)
+    torch.cuda.synchronize()
+    with context(monkeypatch, "2") as away:
+        for k in range(1, 3):
+            r = away.solve(problem(size, g), o)
+            passes = r.iters + r.refreshes
+            assert passes > 1000
+            n = away.stats()["launches"]
+            assert k * passes - 8 <= n <= k * (passes + 2 * 256), (n, k, passes)
