@@ -405,7 +405,8 @@ typedef struct {
     int64_t budget;       /* the context's HBM budget */
     int64_t launches;     /* pass kernel launches issued so far; of a network that ran in resident
                              loops, many passes to a launch, its passes, once it has finished */
-    int64_t peak_active;  /* most networks that have shared one pass launch */
+    int64_t peak_active;  /* most networks that have run in the same pass rounds (those waiting for
+                             their turn in resident loops not counted) */
     /* With rn_set_timing on: device time of the pass kernel launches, by the
      * path that ran them (RN_PATH_*) and their inner precision (RN_FP64,
      * RN_MIXED), measured with HIP events recorded on the launch stream

@@ -1149,7 +1149,6 @@ int Engine::capture(hipStream_t st, std::string *err)
 int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
 {
     if (active_.empty()) return RN_OK;
-    peak_active_ = std::max(peak_active_, (int)active_.size());
     tkind_[next_mirror_].clear();
     // networks that fit resident loops run in those, the others in shared rounds
     size_t loops = 0;
@@ -1168,11 +1167,15 @@ int Engine::launch_chunk(int rounds, hipStream_t st, std::string *err)
         if (r) return r;
         if (!got) loops = 0;
     }
+    int running = 0;               // networks that run in this chunk: others wait their turn in loops
     for (Net *n : active_) {
         const bool in_loop = loops && n->fits_loop;
         if (in_loop != n->in_loop) dirty_ = true;
         n->in_loop = in_loop;
+        running += in_loop ? 0 : 1;
     }
+    for (const Gang &g : gangs) running += loops ? (int)g.nets.size() : 0;
+    peak_active_ = std::max(peak_active_, std::max(running, 1));
     if (loops == active_.size()) {
         int launched = 0;
         int r = loops == 1 ? launch_loops(active_[0], &launched, st, err)

@@ -206,7 +206,7 @@ private:
     int64_t rounds_ = 0;                    // pass rounds issued (parity of the next round)
     int64_t launches_ = 0;
     int chunk_ = 16;
-    int peak_active_ = 0;                   // most networks that shared one launch
+    int peak_active_ = 0;                   // most networks that ran in one chunk
     // hipGraph of kGraphRounds pass rounds for the current block tables,
     // replayed for the bulk of each chunk (the round count is even, so the
     // parities baked into the graph stay valid from replay to replay)

@@ -170,3 +170,21 @@ def test_launch_count_of_a_network_turned_away(monkeypatch):
             assert passes > 1000
             n = away.stats()["launches"]
             assert k * passes - 8 <= n <= k * (passes + 2 * 256), (n, k, passes)
+
+
+def test_peak_counts_networks_that_run(monkeypatch):
+    """Three networks of 456 workgroups each, where the chip holds 1,024 in loops: two at a time."""
+    import torch
+    B.rn_tune_reset()
+    size = (700, 600, 1)
+    g = network(size, 9)
+    o = B.opts(B.RN_FP64, 1e-30, max_iter=4000)
+    probs = [problem(size, g) for _ in range(3)]
+    assert B.rn_plan(probs[0], o)["workgroups"] == 456
+    torch.cuda.synchronize()
+    with context(monkeypatch, "1") as ctx:
+        ctx.solve_batch(probs, o, check=False)
+        assert ctx.stats()["peak_active"] == 2
+    with context(monkeypatch, "0") as ctx:
+        ctx.solve_batch(probs, o, check=False)
+        assert ctx.stats()["peak_active"] == 3
