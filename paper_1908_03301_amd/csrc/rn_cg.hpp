@@ -196,12 +196,12 @@ __device__ __forceinline__ double jscale(double v, double d) { return v / d; }
 template <typename T>
 __device__ __forceinline__ T apply_minv(T v, T d, bool jacobi) { return jacobi ? jscale(v, d) : v; }
 
-// z - alpha u, z + beta p and the stencil's sums with their roundings written
-// out. Which product of a sum the compiler fuses is its own choice, made
-// kernel by kernel; the pass kernels and the resident loop have to agree on
-// every bit, so none is left to it.
-__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// z - alpha u, z + beta p, the stencil's sums, the sums over nodes and r.z of
+// the next pass with their roundings written out. Which product of a sum the
+// compiler fuses is its own choice, made kernel by kernel; the pass kernels and
+// the resident loop have to agree on every bit, so none is left to it.
+__host__ __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__host__ __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 template <typename T>
 __device__ __forceinline__ T step_z(T z, T alpha, T u) { return fma_(-alpha, u, z); }
@@ -233,8 +233,14 @@ __device__ __forceinline__ T stencil3d(T gxl, T dl, T gxr, T dr, T gyl, T db, T 
     return fma_(gzr, du, q);
 }
 
+// r.z of the next pass from this one's sums.
+__host__ __device__ __forceinline__ double next_rz(double alpha, double zq, double qq, double rz)
+{
+    return fma_(alpha * alpha, qq, fma_(-2.0 * alpha, zq, rz));
+}
+
 // Scalar update after a CG pass. t = (p.q, z.q, q.D^-1 q, r.z, 0).
-__device__ inline void step_after_cg(Scalars *s, const double *t)
+__host__ __device__ inline void step_after_cg(Scalars *s, const double *t)
 {
     const double pq = t[0], zq = t[1], qq = t[2], rz = t[3];
     // a pass that left the FP64 field alone leaves the steps before it
@@ -270,7 +276,7 @@ __device__ inline void step_after_cg(Scalars *s, const double *t)
         return;
     }
     const double alpha = rz / pq;
-    double rho_next = rz - 2.0 * alpha * zq + alpha * alpha * qq;
+    double rho_next = next_rz(alpha, zq, qq, rz);
     if (!(rho_next > 0.0)) rho_next = 0.0;
     const double est = s->kappa * s->sigma * sqrt(rho_next) / s->bhat;
     s->est_rel = est;

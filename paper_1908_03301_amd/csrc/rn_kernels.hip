@@ -475,10 +475,10 @@ __device__ __forceinline__ void cg2d_tile(const PassArgs<T> &a, double *__restri
             }
             const double dq = (double)qv, du = (double)uv;
             const double dp = (double)pc, dz = live ? (double)zc : 0.0;
-            acc[0] += dp * dq;
-            acc[1] += dz * dq;
-            acc[2] += dq * du;
-            acc[3] += (double)(jacobi ? d : T(1)) * dz * dz;
+            acc[0] = fma_(dp, dq, acc[0]);
+            acc[1] = fma_(dz, dq, acc[1]);
+            acc[2] = fma_(dq, du, acc[2]);
+            acc[3] = fma_((double)(jacobi ? d : T(1)) * dz, dz, acc[3]);
         }
     }
 }
@@ -779,10 +779,10 @@ __device__ __forceinline__ void cg3d_tile(const PassArgs<T> &a, double *__restri
             }
             const double dp = (double)p0, dq = (double)qv, du = (double)uv;
             const double dz = live ? (double)zvc[j] : 0.0;
-            acc[0] += dp * dq;
-            acc[1] += dz * dq;
-            acc[2] += dq * du;
-            acc[3] += (double)(jacobi ? d : T(1)) * dz * dz;
+            acc[0] = fma_(dp, dq, acc[0]);
+            acc[1] = fma_(dz, dq, acc[1]);
+            acc[2] = fma_(dq, du, acc[2]);
+            acc[3] = fma_((double)(jacobi ? d : T(1)) * dz, dz, acc[3]);
         }
         // rotate
 #pragma unroll

@@ -358,7 +358,7 @@ __device__ __forceinline__ bool loop_step(Scalars *sl, LoopState &L, const doubl
     const double pq = t[0], zq = t[1], qq = t[2], rz = t[3];
     const double root = sqrt(fmax(rz, 0.0));
     const double alpha = rz / pq;
-    double rho = fma_(alpha * alpha, qq, fma_(-2.0 * alpha, zq, rz));
+    double rho = next_rz(alpha, zq, qq, rz);
     if (!(rho > 0.0)) rho = 0.0;
     const double rmax = fmax(sl->rmax, root);
     const double rroot = sqrt(rho);

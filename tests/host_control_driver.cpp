@@ -3,6 +3,7 @@
 // returns 0 when the check named holds. Nothing here reaches a GPU.
 #include "../paper_1908_03301_amd/csrc/rn_cg.hpp"
 
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 
@@ -44,12 +45,42 @@ void loop_end_keeps_failure()
     expect(mem.iters == 90 && mem.mode == MODE_REFRESH && mem.xr == 2.5, "the loop's own state is not stored");
 }
 
+// The scalar step of the pass kernels and of the resident loops have to give
+// the same bits whatever the compiler makes of a sum of products: r.z of the
+// next pass is two fused operations, on a host that fuses none by itself.
+void step_rounds_as_written()
+{
+    unsigned long long h = 88172645463325252ull;
+    auto uniform = [&] {
+        h ^= h << 13;
+        h ^= h >> 7;
+        h ^= h << 17;
+        return 0.5 + (double)(h >> 11) * 0x1p-53;
+    };
+    int wrong = 0;
+    for (int k = 0; k < 1000; ++k) {
+        const double rz = uniform(), pq = 2.0 * uniform(), zq = 0.3 * uniform(), qq = 4.0 * uniform();
+        const double t[kRed] = {pq, zq, qq, rz, 0.0};
+        Scalars s;
+        std::memset(&s, 0, sizeof(s));
+        s.sigma = s.kappa = s.bhat = 1.0;
+        s.max_iter = 1000;
+        s.kpend = 4;
+        step_after_cg(&s, t);
+        const double alpha = rz / pq, next = std::fma(alpha * alpha, qq, std::fma(-2.0 * alpha, zq, rz));
+        if (!(next > 0.0)) continue;
+        wrong += s.mode != MODE_CG || s.alpha != alpha || s.beta != next / rz || s.est_rel != std::sqrt(next);
+    }
+    expect(wrong == 0, "a step with another rounding");
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
     const char *want = argc > 1 ? argv[1] : "";
     if (!std::strcmp(want, "loop_end_keeps_failure")) loop_end_keeps_failure();
+    else if (!std::strcmp(want, "step_rounds_as_written")) step_rounds_as_written();
     else expect(false, "no such check");
     std::printf("%s: %d failures\n", want, fails);
     return fails != 0;
