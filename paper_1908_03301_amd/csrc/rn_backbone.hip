@@ -56,6 +56,17 @@ constexpr unsigned kNone = 0xffffffffu;
 // T is 1, the components follow.
 constexpr unsigned kPosT = 1u, kPosFirst = 2u;
 
+// The indices 0 .. n - 1 that fall to this thread of a launch: of nodes (fewer
+// than 2^31) and of positions of the tour (up to twice as many).
+__device__ __forceinline__ Strided<false> each(int n)
+{
+    return {{blockIdx.x * kBbBlock + threadIdx.x, gridDim.x * kBbBlock, (unsigned)n}};
+}
+__device__ __forceinline__ Strided<true> each_position(unsigned n)
+{
+    return {{blockIdx.x * kBbBlock + threadIdx.x, gridDim.x * kBbBlock, n}};
+}
+
 struct BbGraph {
     const double *g[3];
     const uint8_t *mask;
@@ -139,7 +150,7 @@ struct BbWork {
 __global__ void bb_tree(BbGraph G, BbWork W)
 {
     const int V = G.n + 2;
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < V; v += gridDim.x * blockDim.x) {
+    for (const int v : each(V)) {
         W.uf[v] = v;
         W.in[v] = v == G.T ? kPosT : kNone;
         W.last[v] = v == G.T ? kPosT : 0u;
@@ -175,7 +186,7 @@ __global__ void bb_tree(BbGraph G, BbWork W)
 // from S is a head's).
 __global__ void bb_starts(BbGraph G, BbWork W)
 {
-    for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < W.groups; g += gridDim.x * blockDim.x) {
+    for (const int g : each(W.groups)) {
         unsigned h = (unsigned)g * 0x9e3779b1u;
         h ^= h >> 15;
         h *= 0x85ebca6bu;
@@ -233,7 +244,7 @@ __device__ __forceinline__ bool walker(const BbWork &W, int i, int &v, int &r, u
 __global__ void bb_walk(BbGraph G, BbWork W)
 {
     const int total = W.groups + (int)W.counter[0];
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+    for (const int i : each(total)) {
         int v, r;
         unsigned bits, len = 0u, to = (unsigned)i;
         if (walker(W, i, v, r, bits)) {
@@ -260,7 +271,7 @@ __global__ void bb_jump(BbWork W, int from)
     const int total = W.groups + (int)W.counter[0];
     const unsigned long long *src = W.jump[from];
     unsigned long long *dst = W.jump[from ^ 1];
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+    for (const int i : each(total)) {
         unsigned long long a = src[i], far = a >> 32;
         for (int k = 1; k < 4; ++k) {
             a = src[(unsigned)a];
@@ -274,7 +285,7 @@ __global__ void bb_jump(BbWork W, int from)
 __global__ void bb_ranges(BbWork W, int from)
 {
     const int heads = (int)W.counter[0];
-    for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < heads; h += gridDim.x * blockDim.x) {
+    for (const int h : each(heads)) {
         const unsigned long long a = W.jump[from][W.groups + h];
         const unsigned t = (unsigned)a, size = (unsigned)(a >> 32) + W.len[t];
         W.end[t] = kPosFirst + atomicAdd(W.counter + 1, size) + size;
@@ -289,7 +300,7 @@ __global__ void bb_ranges(BbWork W, int from)
 __global__ void bb_number(BbGraph G, BbWork W, int from)
 {
     const int total = W.groups + (int)W.counter[0];
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+    for (const int i : each(total)) {
         int v, r;
         unsigned bits;
         if (!walker(W, i, v, r, bits)) continue;
@@ -316,7 +327,7 @@ __global__ void bb_number(BbGraph G, BbWork W, int from)
 // first arrival.
 __global__ void bb_clear(BbGraph G, BbWork W)
 {
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+    for (const int v : each(G.n)) {
         const unsigned a = W.in[v], b = W.last[v];
         if (a > b && a != kNone) {
             W.in[v] = b;
@@ -324,7 +335,7 @@ __global__ void bb_clear(BbGraph G, BbWork W)
         }
     }
     const unsigned m = kPosFirst + W.counter[1];
-    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
+    for (const unsigned i : each_position(m)) {
         W.lo[0][i] = kNone;
         W.hi[0][i] = 0u;
     }
@@ -340,7 +351,7 @@ __device__ __forceinline__ bool is_tree(const BbGraph &G, const BbWork &W, int v
 // low / high of every live vertex's own non-tree edges, at its first arrival.
 __global__ void bb_reach(BbGraph G, BbWork W)
 {
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+    for (const int v : each(G.n)) {
         if (!W.adj[v]) continue;
         int c[3];
         coords(G, v, c);
@@ -363,7 +374,7 @@ __global__ void bb_level(BbWork W, int level)
     unsigned below = kPosFirst + W.counter[1];
     for (int k = 1; k < level; ++k) below = (below + kFan - 1) / kFan;
     const unsigned m = (below + kFan - 1) / kFan;
-    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
+    for (const unsigned i : each_position(m)) {
         unsigned l = kNone, h = 0u;
         for (unsigned k = i * kFan; k < min(below, (i + 1u) * kFan); ++k) {
             l = min(l, W.lo[level - 1][k]);
@@ -446,7 +457,7 @@ __device__ __forceinline__ void uf_union_tour(int *uf, const unsigned *in, int a
 // 4. Joins along the tree: low / high over the subtree of v from the hierarchy.
 __global__ void bb_join_tree(BbGraph G, BbWork W)
 {
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+    for (const int v : each(G.n)) {
         if (!W.adj[v]) continue;
         int c[3];
         coords(G, v, c);
@@ -483,7 +494,7 @@ __global__ void bb_join_tree(BbGraph G, BbWork W)
 // Shorten the chains of joined tree edges.
 __global__ void bb_shorten(BbGraph G, BbWork W)
 {
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+    for (const int v : each(G.n)) {
         if (!W.adj[v]) continue;
         int p = uf_get(W.uf, v);
         const int was = p;
@@ -506,7 +517,7 @@ __device__ __forceinline__ bool ancestor(const BbWork &W, int a, int v)
 // edge to T).
 __global__ void bb_join_cross(BbGraph G, BbWork W)
 {
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+    for (const int v : each(G.n)) {
         if (!W.adj[v]) continue;
         int c[3];
         coords(G, v, c);
@@ -522,7 +533,7 @@ __global__ void bb_join_cross(BbGraph G, BbWork W)
 __global__ void bb_mark(BbGraph G, BbWork W, uint8_t *on)
 {
     const int rt = uf_find(W.uf, G.T);
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < G.n; v += gridDim.x * blockDim.x) {
+    for (const int v : each(G.n)) {
         if (!W.adj[v] || uf_find(W.uf, v) != rt) continue;
         on[v] = 1;
         int c[3];
@@ -534,13 +545,13 @@ __global__ void bb_mark(BbGraph G, BbWork W, uint8_t *on)
 
 __global__ void bb_zero(uint8_t *p, int n)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
+    for (const int i : each(n)) p[i] = 0;
 }
 
 __global__ void bb_apply(uint8_t *mask, const uint8_t *on, int n, unsigned long long *count)
 {
     int c = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    for (const int i : each(n))
         if (on[i]) {
             mask[i] |= 8u;
             ++c;
@@ -567,7 +578,7 @@ __global__ void bb_apply(uint8_t *mask, const uint8_t *on, int n, unsigned long 
 // Pieces of dangling nodes: union over occupied bonds between two of them.
 __global__ void bb_piece_union(BbGraph G, int *uf, int *att)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < G.n; i += gridDim.x * blockDim.x) {
+    for (const int i : each(G.n)) {
         if (G.mask[i] != 3) continue;
         att[i] = -1;
         int c[3];
@@ -583,7 +594,7 @@ __global__ void bb_piece_union(BbGraph G, int *uf, int *att)
 // dangling node next to it writes the same index).
 __global__ void bb_piece_attach(BbGraph G, int *uf, int *att)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < G.n; i += gridDim.x * blockDim.x) {
+    for (const int i : each(G.n)) {
         if (G.mask[i] != 3) continue;
         int c[3];
         coords(G, i, c);
@@ -600,7 +611,7 @@ __global__ void bb_piece_attach(BbGraph G, int *uf, int *att)
 __global__ void bb_prune(BbGraph G, double *g0, double *g1, double *g2)
 {
     double *gk[3] = {g0, g1, g2};
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < G.n; i += gridDim.x * blockDim.x) {
+    for (const int i : each(G.n)) {
         int c[3];
         coords(G, i, c);
         const bool di = G.mask[i] == 3;
@@ -615,7 +626,7 @@ __global__ void bb_prune(BbGraph G, double *g0, double *g1, double *g2)
 // Pressures of the dangling nodes: that of the backbone node their piece hangs from.
 __global__ void bb_fill(const uint8_t *mask, int *uf, const int *att, double *P, int n)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    for (const int i : each(n)) {
         if (mask[i] != 3) continue;
         const int a = att[uf_find(uf, i)];
         if (a >= 0) P[i] = P[a];
@@ -624,7 +635,7 @@ __global__ void bb_fill(const uint8_t *mask, int *uf, const int *att, double *P,
 
 __global__ void bb_iota(int *uf, int n)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) uf[i] = i;
+    for (const int i : each(n)) uf[i] = i;
 }
 
 BbGraph graph_of(const Lat &L, const double *const g[3], const uint8_t *mask)

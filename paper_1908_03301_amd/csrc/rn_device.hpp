@@ -303,6 +303,29 @@ constexpr int kTY2f = RN_TY2F, kTY2d = RN_TY2D, kSEG2f = RN_SEG2F, kSEG2d = RN_S
 constexpr int kTY2fS = 2, kTY2dS = 1;   // rows per wave of the small 2D tile (one 64-column segment)
 
 
+// first, first + step, ... below n, for a thread of a launch. The sum that ends
+// the loop may lie past n: as an int it overflows where n is within a stride
+// (at most 2^21) of 2^31, so indices are unsigned; and with n within a stride of 2^32
+// it wraps round to a small index, and the loop would never end (positions of
+// the tour of a lattice of 46,340^2 nodes end 361,000 below 2^32). FAR: n may
+// be that large; the sum is then not formed.
+template <bool FAR>
+struct Strided {
+    struct It {
+        unsigned i, step, n;
+        __host__ __device__ unsigned operator*() const { return i; }
+        __host__ __device__ bool operator!=(const It &) const { return i < n; }
+        __host__ __device__ It &operator++()
+        {
+            i = !FAR || step < n - i ? i + step : n;
+            return *this;
+        }
+    };
+    It b;
+    __host__ __device__ It begin() const { return b; }
+    __host__ __device__ It end() const { return b; }
+};
+
 __host__ __device__ inline int div_up(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace rn

@@ -74,6 +74,36 @@ void step_rounds_as_written()
     expect(wrong == 0, "a step with another rounding");
 }
 
+// The indices of a thread of a launch, also where n is within a stride of 2^31
+// (nodes) or 2^32 (positions of a tour).
+template <bool FAR>
+void strided(unsigned long long n)
+{
+    for (unsigned step : {256u, 2097152u}) {
+        if (n > 10000000ull && step == 256u) continue;
+        for (unsigned first : {0u, 1u, step / 2, step - 1}) {
+            const unsigned long long expected = n > first ? (n - first + step - 1) / step : 0;
+            unsigned long long count = 0, next = first;
+            bool inside = true;
+            for (const unsigned i : Strided<FAR>{{first, step, (unsigned)n}}) {
+                inside = inside && i == next && i < n;
+                next += step;
+                if (++count > expected) break;
+            }
+            expect(inside && count == expected, "indices of a thread");
+        }
+    }
+}
+
+void strides_end()
+{
+    for (unsigned long long n : {0ull, 1ull, 255ull, 256ull, 257ull, 1000ull, 5ull << 20, 2147483645ull}) {
+        strided<false>(n);
+        strided<true>(n);
+    }
+    for (unsigned long long n : {4294605841ull, 4294967295ull}) strided<true>(n);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -81,6 +111,7 @@ int main(int argc, char **argv)
     const char *want = argc > 1 ? argv[1] : "";
     if (!std::strcmp(want, "loop_end_keeps_failure")) loop_end_keeps_failure();
     else if (!std::strcmp(want, "step_rounds_as_written")) step_rounds_as_written();
+    else if (!std::strcmp(want, "strides_end")) strides_end();
     else expect(false, "no such check");
     std::printf("%s: %d failures\n", want, fails);
     return fails != 0;

@@ -24,7 +24,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["loop_end_keeps_failure", "step_rounds_as_written"])
+@pytest.mark.parametrize("check", ["loop_end_keeps_failure", "step_rounds_as_written", "strides_end"])
 def test_control(driver, check):
     run = subprocess.run([driver, check], capture_output=True, text=True, timeout=60)
     assert run.returncode == 0, run.stdout + run.stderr
