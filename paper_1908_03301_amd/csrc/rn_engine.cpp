@@ -447,8 +447,11 @@ int Engine::init(Pool *pool, std::string *err)
     if (persist_) use_graph_ = false;
     // RN_LOOPS=0: no resident loops. RN_LOOPS=2: every one is turned away at its
     // gate, as where another stream holds the CUs (a check of that path).
+    // RN_LOOPS=3: pass numbers start close to where they start over, 4 * 10^9
+    // passes on (a check of that).
     const char *lo = std::getenv("RN_LOOPS");
     loops_mode_ = lo && (lo[0] == '0' || lo[0] == '2') ? lo[0] - '0' : 1;
+    if (lo && lo[0] == '3') loop_tag_ = kTagEnd - 700;
     ENG_TRY(hipMalloc(&d_queue_, kQueueWords * sizeof(unsigned long long) * kKinds));
     ENG_TRY(hipMalloc(&d_xoff_, sizeof(int) * 16 * kKinds));
     ENG_TRY(hipHostMalloc((void **)&h_xoff_, sizeof(int) * 16 * kKinds * 2, hipHostMallocDefault));

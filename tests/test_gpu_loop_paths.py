@@ -93,6 +93,24 @@ def test_turned_away_bits(size, precision, plan, monkeypatch):
             assert launches[plan[0]][precision] >= got.iters + got.refreshes
 
 
+@pytest.mark.parametrize("size,precision,plan", SHAPES, ids=ident)
+def test_pass_numbers_start_over(size, precision, plan, monkeypatch):
+    """The tags of the words that loops exchange start over with cleared words: in the first solve or the second."""
+    import torch
+    B.rn_tune_reset()
+    g = network(size, 5)
+    o = B.opts(precision, tolerance(size))
+    pw, pg = (torch.zeros(g[0].shape, dtype=torch.float64, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    with context(monkeypatch, "0") as plain, context(monkeypatch, "3") as loop:
+        want = plain.solve(problem(size, g, pw), o)
+        for _ in range(3):
+            got, launches = timed(loop, problem(size, g, pg), o)
+            assert bits(got) == bits(want)
+            assert torch.equal(pg, pw)
+            assert launches[plan[0]][precision] < (got.iters + got.refreshes) / 2
+
+
 @pytest.mark.parametrize("precision", [B.RN_MIXED, B.RN_FP64], ids=ident)
 def test_turned_away_gang_bits(precision, monkeypatch):
     import torch
