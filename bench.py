@@ -11,7 +11,8 @@ by device pointer.
 Prints one JSON line: value = network solves/s, the members' completion
 latencies, the dominant pass kernel's roofline (floor bytes per swept node
 over its device time, from HIP events the library records on the launch
-stream around every launch), the plain FP64 CG comparisons (batched, one at a
+stream around every launch; taken in a leg of its own with one launch per
+pass, since the state of a resident loop does not travel), the plain FP64 CG comparisons (batched, one at a
 time, and a Poisson-served stream against FIFO), and the CPU oracle's full
 solves of a seeded sample of the members. The single-network workloads
 (--workload fbm2d_2048, iid2d_128, strat3d_256) and the study workloads
@@ -94,7 +95,7 @@ def cpu_info() -> str:
 
 def kernel_hash() -> str:
     h = hashlib.sha256()
-    for f in ("rn_kernels.hip", "rn_device.hpp"):
+    for f in ("rn_kernels.hip", "rn_cg.hpp", "rn_device.hpp"):
         h.update(open(os.path.join(ROOT, "paper_1908_03301_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -136,6 +137,20 @@ def copy_ceiling_gbps(mib: int = 1024) -> float:
     del a, b
     torch.cuda.empty_cache()
     return 2 * nbytes / best / 1e9
+
+
+def pass_context(B):
+    """A context without resident loops (RN_LOOPS=0): one launch per pass, whose
+    bytes pass through memory. The rooflines are of these launches."""
+    old = os.environ.get("RN_LOOPS")
+    os.environ["RN_LOOPS"] = "0"
+    try:
+        return B.Context(0)
+    finally:
+        if old is None:
+            del os.environ["RN_LOOPS"]
+        else:
+            os.environ["RN_LOOPS"] = old
 
 
 def run_solves(ctx, B, prob_by_axis, precision, tol, steps, warmup, max_iter=2_000_000, backbone=False,
@@ -243,18 +258,23 @@ def main():
     solves = len(lat_m)
     value = solves / total_m
 
-    # roofline of the pass kernel (mixed leg: FP32 inner passes and FP64 refreshes)
-    # (each axis has its own live set)
+    # roofline of the pass kernel (FP32 inner passes and FP64 refreshes), from
+    # solves of one launch per pass (each axis has its own live set)
     n = net.n
     n_live = res_m[0][1]["n_live"]
     pb = pass_bytes(net.dim, n, 4, n_live)
-    loop_t = sum(r["t_loop_s"] for _, r in res_m)
-    launches = sum(r["passes"] for _, r in res_m)
-    iters = sum(r["iters"] for _, r in res_m)
-    refr = sum(r["refreshes"] for _, r in res_m)
+    pctx = pass_context(B)
+    _, res_p = run_solves(pctx, B, probs, B.RN_MIXED, args.tol, 1, min(args.warmup, 1))
+    pctx.close()
+    loop_t = sum(r["t_loop_s"] for _, r in res_p)
+    launches = sum(r["passes"] for _, r in res_p)
+    iters = sum(r["iters"] for _, r in res_p)
+    refr = sum(r["refreshes"] for _, r in res_p)
     alg_bytes = sum(r["iters"] * pass_bytes(net.dim, n, 4, r["n_live"])["cg"] +
-                    r["refreshes"] * pass_bytes(net.dim, n, 4, r["n_live"])["refresh"] for _, r in res_m)
+                    r["refreshes"] * pass_bytes(net.dim, n, 4, r["n_live"])["refresh"] for _, r in res_p)
     live_iters = sum(r["n_live"] * r["iters"] for _, r in res_m)
+    run_loop_t = sum(r["t_loop_s"] for _, r in res_m)
+    run_passes = sum(r["iters"] + r["refreshes"] for _, r in res_m)
     avg_launch_s = loop_t / max(launches, 1)
     achieved = alg_bytes / loop_t / 1e9
     tr = traffic_from_profiles(args.workload, "mixed")
@@ -267,7 +287,8 @@ def main():
                 "traffic_frac": round(traffic / avg_launch_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
                 "kernel": f"pass{net.dim}d_kernel<float>", "avg_launch_us": round(avg_launch_s * 1e6, 2),
                 "launches": launches, "cg_passes": iters, "refresh_passes": refr,
-                "bytes_per_cg_pass": pb["cg"], "bytes_per_refresh_pass": pb["refresh"]}
+                "bytes_per_cg_pass": pb["cg"], "bytes_per_refresh_pass": pb["refresh"],
+                "of": "solves with one launch per pass (RN_LOOPS=0)"}
 
     out = {"metric": METRIC, "value": round(value, 4), "unit": "solves/s", "n_gpus": 1, "steps": args.steps,
            "warmup": args.warmup, "ms_per_step": round(1e3 * total_m / args.steps, 3), "higher_is_better": True,
@@ -277,7 +298,8 @@ def main():
            "latency_ms": {"p50": round(1e3 * float(np.percentile(lat_m, 50)), 3),
                           "p99": round(1e3 * float(np.percentile(lat_m, 99)), 3)},
            "roofline": roofline,
-           "live_node_iters_per_s": round(live_iters / loop_t, 1)}
+           "loop_us_per_pass": round(1e6 * run_loop_t / run_passes, 2),
+           "live_node_iters_per_s": round(live_iters / run_loop_t, 1)}
     out["results"] = {f"K_axis{ax}": r["K"] for ax, r in res_m[: len(wl["axes"])]}
     out["iters_mixed"] = {f"axis{ax}": r["iters"] for ax, r in res_m[: len(wl["axes"])]}
 
@@ -446,8 +468,8 @@ def batch_bench(args, B, I, np):
     value = networks solved per second over the timed batches. Latency is the
     completion time of each member from the call. The roofline is the pass
     kernel with the most device time (HIP events around every launch, on the
-    launch stream, over the timed batches): the floor bytes of every CG
-    iteration and FP64 outer step of its members over its device time.
+    launch stream, over one batch without resident loops): the floor bytes of
+    every CG iteration and FP64 outer step of its members over its device time.
     Compared with the same batch in FP64, with plain FP64 CG run one network
     at a time, and with a Poisson-served stream against plain FP64 CG served
     first in first out (--requests 0 skips it). The CPU oracle solves a seeded
@@ -482,22 +504,22 @@ def batch_bench(args, B, I, np):
     probs = [B.problem(dim=n.dim, nx=n.nx, ny=n.ny, nz=n.nz, axis=0, g=g) for n, g in zip(nets, gd)]
     ctx = B.Context(0)
 
-    def run(prec, steps, timed_stats=False):
+    def run(prec, steps, timed_stats=False, ctx=ctx, warmup=args.warmup, name="batch"):
         walls, per_step, lat = [], [], []
-        for it in range(args.warmup + steps):
-            if timed_stats and it == args.warmup:
+        for it in range(warmup + steps):
+            if timed_stats and it == warmup:
                 ctx.set_timing(True)           # clears the accumulated launch times
             torch.cuda.synchronize()
             t = time.perf_counter()
             res = ctx.solve_batch(probs, B.opts(prec, args.tol))
             w = time.perf_counter() - t
             bad = [r.status for r in res if r.status != 0]
-            print(f"[bench] batch prec={'mixed' if prec == B.RN_MIXED else 'fp64'} "
-                  f"{'warmup' if it < args.warmup else 'step'} {it}: {w:.3f}s failed={len(bad)}",
+            print(f"[bench] {name} prec={'mixed' if prec == B.RN_MIXED else 'fp64'} "
+                  f"{'warmup' if it < warmup else 'step'} {it}: {w:.3f}s failed={len(bad)}",
                   file=sys.stderr, flush=True)
             if bad:
                 raise SystemExit(f"batch members failed: {bad[:5]}")
-            if it >= args.warmup:
+            if it >= warmup:
                 walls.append(w)
                 per_step.append(res)
                 lat.extend(r.t_total_s for r in res)
@@ -522,7 +544,16 @@ def batch_bench(args, B, I, np):
                          "of": "completion time of each batch member from the rn_solve_batch call"}
     out["batch_wall_s"] = [round(w, 3) for w in walls_m]
     out["launch_shapes"] = shapes
-    kern = kernel_accounting(B, nets, probs, steps_m, B.RN_MIXED, st_m)
+    # device time of the timed batches by tile family: pass launches and resident loops
+    out["device_s_per_batch"] = {
+        f"{PATHS[p]}_fp32": round(st_m["pass_device_s"][p][B.RN_MIXED] / len(walls_m), 4) for p in range(3)}
+    # the pass kernels' own rates, from a batch with one launch per pass
+    pctx = pass_context(B)
+    walls_p, steps_p, _, st_p = run(B.RN_MIXED, 1, timed_stats=True, ctx=pctx, warmup=min(args.warmup, 1),
+                                    name="one launch per pass:")
+    pctx.close()
+    out["one_launch_per_pass_solves_per_s"] = round(len(probs) / min(walls_p), 4)
+    kern = kernel_accounting(B, nets, probs, steps_p, B.RN_MIXED, st_p)
     if not kern:
         # no per-launch times: pass rounds replayed from a hipGraph (RN_GRAPHS=1) record no events
         out["roofline"] = None
@@ -546,13 +577,15 @@ def batch_bench(args, B, I, np):
         "live_node_GBps": round(dom["live_node_bytes"] / dom["device_s"] / 1e9, 1),
         "traffic_GBps": round(traffic["bytes_per_launch"] / (dom["device_s"] / dom["launches"]) / 1e9, 1)
         if traffic else None,
-        "timing": "HIP events recorded by the library on the launch stream between consecutive pass launches"}
+        "timing": "HIP events recorded by the library on the launch stream between consecutive pass launches",
+        "of": "a batch with one launch per pass (RN_LOOPS=0): in the timed batches networks that fit the chip run "
+              "in resident loops, whose state stays in registers and LDS"}
     out["kernels"] = {k: {kk: (round(vv, 3) if isinstance(vv, float) else vv) for kk, vv in v.items()}
                       for k, v in kern.items()}
     all_secs = sum(v["device_s"] for v in kern.values())
     all_floor = sum(v["floor_bytes"] for v in kern.values())
     out["all_pass_kernels_floor_GBps"] = round(all_floor / all_secs / 1e9, 1)
-    out["pass_device_s_per_batch"] = round(all_secs / len(walls_m), 4)
+    out["pass_device_s_per_batch"] = round(all_secs / len(walls_p), 4)
     out["live_node_iters_per_s"] = round(sum(r.n_live * r.iters for res in steps_m for r in res) / tot_m, 1)
     out["iters_mixed"] = {"median": int(np.median([r.iters for r in res_m])),
                           "max": int(max(r.iters for r in res_m))}

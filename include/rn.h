@@ -184,9 +184,11 @@ int rn_opts_default(rn_opts *opts);
  *                 placed on one XCD (other kinds: one launch per round);
  *   RN_GRAPHS=1   rounds replayed from a captured hipGraph;
  *   otherwise one launch per round and kind, and many rounds of a network
- *   that fits the chip in one launch (a resident loop); with RN_LOOPS=0 none
- *   of those, with RN_LOOPS=2 every resident loop is turned away at its start,
- *   as it is where other work holds the chip (a check of that path).
+ *   that fits the chip in one launch (a resident loop). A loop holds its part
+ *   of the chip for up to 5 ms, so kernels of other streams and contexts may
+ *   wait that long; where other work holds the chip when it starts, the
+ *   network goes on with one launch per round. RN_LOOPS=0: no resident loops;
+ *   RN_LOOPS=2: every one is turned away at its start (a check of that path).
  * Errors: RN_EINVAL (NULL out, bad device), RN_EDEVICE.
  */
 int rn_create(int device, size_t hbm_budget_bytes, rn_ctx **out);
@@ -270,8 +272,9 @@ int rn_build_mask_noalloc(rn_ctx *ctx, const rn_problem *prob, int64_t *n_live_o
  * 3. *n_live_out and *n_backbone_out (nullable) receive the counts. Removing
  * the live nodes off the backbone changes no flux, and leaves a network whose
  * live set is the backbone. Memory: prob->mem for g and mask_out; the call
- * takes about 37 device bytes per node from the context's pool and
- * synchronises its stream once per 32 levels of the search.
+ * takes about 41 device bytes per node from the context's pool, and 8 per
+ * node and direction for bonds in host memory, and synchronises its stream
+ * twice (once the bonds are checked, and at the end).
  * Errors: RN_EINVAL (bad problem, NULL mask_out, nx*ny*nz + 2 >= 2^31, while
  * the request server runs), RN_ENOMEM, RN_EDEVICE; outputs untouched on error.
  */
@@ -410,7 +413,8 @@ typedef struct {
     /* With rn_set_timing on: device time of the pass kernel launches, by the
      * path that ran them (RN_PATH_*) and their inner precision (RN_FP64,
      * RN_MIXED), measured with HIP events recorded on the launch stream
-     * between consecutive launches, and the number of launches timed. */
+     * between consecutive launches, and the number of launches timed. A
+     * resident loop is one launch of the path whose passes it runs. */
     double pass_device_s[3][2];
     int64_t pass_timed_launches[3][2];
 } rn_stats_t;
@@ -420,7 +424,7 @@ int rn_stats(rn_ctx *ctx, rn_stats_t *out);
 /*
  * Turn the per-launch timing of rn_stats on (enable = 1) or off (0). While it
  * is on, one HIP event is recorded on the launch stream after every pass
- * launch (and one before each chunk of launches); the elapsed time between
+ * launch and resident loop (and one before each chunk of launches); the elapsed time between
  * consecutive events is added to pass_device_s of the launch's path and
  * precision when the chunk's control blocks are read back. Turning it on
  * clears the accumulated times. Off by default; ignored while pass rounds

@@ -227,7 +227,7 @@ hipError_t launch_pass_persist(int dim, int coh, const PassArgs<T> *tab, const u
 
 // Resident CG loops (rn_loop.hpp): one launch runs up to `limit` CG passes of
 // the one network in `slot`, or of every network of the table `blk`, with their
-// state in registers. `dim` as for launch_pass; tpw and tile_z are the
+// state in registers and LDS. `dim` as for launch_pass; tpw and tile_z are the
 // networks'. Entry blk[b] = (network, member << 16 | block of the network),
 // members numbered from 0, each network's blocks in order from a multiple of 8.
 // gate: kLoopMembers gates of kLoopGateWords words, zero before the launch, a
@@ -262,12 +262,12 @@ inline size_t loop_part_bytes() { return (size_t)kLoopSlots * kLoopRed * kLoopGr
 // at once (0: no loop kernel for it)
 template <typename T>
 hipError_t loop_capacity(int dim, int tpw, int tile_z, bool local, int *cap);
-// words of one exchange slot of a network of `ntiles` tiles
 // workgroups that a loop launches for a network of `grid` workgroups
 int loop_blocks(int dim, int tpw, int grid);
-// `blocks`: of the one network (its grid when local), or of the whole table
+// words of one exchange slot of a network of `ntiles` tiles
 template <typename T>
 size_t loop_exchange_words(int dim, int tile_z, int ntiles);
+// `blocks`: of the one network (its grid when local), or of the whole table
 template <typename T>
 hipError_t launch_loop(int dim, int tpw, int tile_z, bool local, int blocks, const PassArgs<T> *tab, Scalars *scal, int parity,
                        int slot, const LoopArgs &r, hipStream_t st);

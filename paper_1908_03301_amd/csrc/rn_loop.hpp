@@ -5,9 +5,9 @@
 // step, kernel end, next launch, control block, tile loads. Below a few
 // million nodes that chain is the iteration, not the bytes (7 us at 128^2, of
 // which the tile's own arithmetic is under 1 us). Here one launch runs many
-// CG passes of one network. Every workgroup keeps its tile's z, u, p, bonds
-// and FP64 field in registers; per pass it sends out only the u of its edge
-// nodes and its four partial sums:
+// CG passes of one network. Every workgroup keeps its tile's z, u, p and FP64
+// field in registers and LDS, and its bonds too where there is room; per pass it
+// sends out only the u of its edge nodes and its four partial sums:
 //   - a neighbour keeps z and p of its halo nodes itself, from the same
 //     arithmetic as their owner, so u is the only value a halo node needs;
 //   - up to kDirect workgroups, each sums everyone's partials in the order of
