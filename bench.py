@@ -564,7 +564,8 @@ def batch_bench(args, B, I, np):
         return out
     dom_key = max(kern, key=lambda k: kern[k]["device_s"])
     dom = kern[dom_key]
-    traffic = traffic_from_profiles("batch512", dom_key)
+    # the counts are of the shipped shapes
+    traffic = traffic_from_profiles("batch512", dom_key) if args.shapes == "cache" else None
     achieved = dom["floor_GBps"]
     out["roofline"] = {
         "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

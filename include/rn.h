@@ -379,7 +379,8 @@ int rn_plan(const rn_problem *prob, const rn_opts *opts, rn_plan_t *out);
  * 2^25 nodes (at most 256 copies; the objective is the throughput of large
  * batches), are solved together for 64 CG passes and the pass kernels'
  * device time per node and working pass is taken from the event timing of
- * rn_set_timing (the faster of two runs). With RN_TUNE_QUICK a round moves
+ * rn_set_timing (the faster of two runs; where a candidate has a resident
+ * loop, its passes run in it as in a solve). With RN_TUNE_QUICK a round moves
  * about 2^22 nodes (at most 16 copies). The fastest shape of each class, or
  * the built-in one unless the fastest beats it by 3% or more, is
  * installed process-wide and, if cache_path is not NULL, written to that file
