@@ -669,10 +669,13 @@ namespace {
 size_t backbone_layout(int64_t n, char *scratch, BbWork *W)
 {
     const size_t V = (size_t)n + 2;
+    // small lattices: arrays packed closer, so that their rounding does not
+    // exceed the 34 bytes a node that the search may take
+    const size_t pad = n < 4096 ? 63 : 255;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         char *r = scratch + off;
-        off += (bytes + 255) & ~(size_t)255;
+        off += (bytes + pad) & ~pad;
         return r;
     };
     W->tree = (uint8_t *)take(V);
@@ -697,6 +700,7 @@ size_t backbone_layout(int64_t n, char *scratch, BbWork *W)
     for (int l = 0; l < kFanLevels; ++l) {
         W->lo[l] = (unsigned *)take(4 * m);
         W->hi[l] = (unsigned *)take(4 * m);
+        if (m <= kFan) break;                        // no level above it is built or read
         m = (m + kFan - 1) / kFan;
     }
     return std::max(off, one);
