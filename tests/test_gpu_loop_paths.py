@@ -75,6 +75,28 @@ def test_loops_run(size, precision, plan, monkeypatch):
     assert sum(map(sum, launches)) == n
 
 
+@pytest.mark.parametrize("precision", [B.RN_MIXED, B.RN_FP64], ids=ident)
+def test_gangs_run(precision, monkeypatch):
+    """Two networks of every shape in one batch: each path's passes run in loops beside each other."""
+    import torch
+    B.rn_tune_reset()
+    sizes = [s for s, p, _ in SHAPES if p == precision and s[0] * s[1] * s[2] < 400000]
+    g = {s: network(s, 13) for s in sizes}
+    o = B.opts(precision, 1e-6)
+    probs = [problem(s, g[s]) for s in sizes for _ in range(2)]
+    paths = [B.rn_plan(p, o)["path"] for p in probs]
+    assert sorted(set(paths)) == [FULL, SMALL, BLOCK]
+    torch.cuda.synchronize()
+    with context(monkeypatch, "1") as ctx:
+        ctx.set_timing(True)
+        res = ctx.solve_batch(probs, o)
+        launches = ctx.stats()["pass_timed_launches"]
+    for path in (FULL, SMALL, BLOCK):
+        passes = max(r.iters + r.refreshes for r, p in zip(res, paths) if p == path)
+        # without loops a path's launches are at least the passes of its longest solve
+        assert 0 < launches[path][precision] < passes / 2, (path, launches, passes)
+
+
 @pytest.mark.parametrize("size,precision,plan", SHAPES, ids=ident)
 def test_turned_away_bits(size, precision, plan, monkeypatch):
     import torch
